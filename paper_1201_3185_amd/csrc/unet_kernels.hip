@@ -318,10 +318,229 @@ void launch_dilate(Tensor src, Tensor dst, int c, hipStream_t s)
 }
 
 // Weight gradient: partial[split, co, kk] = sum over the split's output voxels
-// o of dy[o, co] X[o, kk], X[o, tap cin + ci] = x[s o + d(tap), ci].  One wave
-// per (16 co x 16 kk) tile and split; rows = co, columns = kk, K = voxels.
+// o of dy[o, co] X[o, kk], X[o, tap cin + ci] = x[s o + d(tap), ci].  Rows = co,
+// columns = kk, K = voxels, 32 consecutive o per MFMA from the split's start,
+// so every column is one chain of MFMAs whichever columns share a tile.
+//
+// Channel-last tensors have K as their slow axis, so the operands are
+// transposed on their way through LDS.  A workgroup takes one split, 16 input
+// channels, 16 NBW output channels and one dz; wave w owns the three taps of
+// row shift (dy, dz) = (w - 1, dz).  It stages its own shifted row of x as
+// [channel][voxel] in a ring of three chunks of C voxels; in linear voxel order
+// the taps of one (dy, dz) are the same row displaced by one voxel, so one
+// 16-byte LDS read and the two dwords beside it give all three fragments.  Rows
+// outside the grid are staged as zeros, row ends are masked (mask rows staged
+// beside dy).  With stride 2 the even and the odd x of the row are two rows of
+// their own and the fragment of tap dx = -1 is the odd row displaced by one; the
+// odd row ends in a zero, so no masks are needed.  What bounds it is the latency
+// of a wave's global loads and the address and packing work per chunk (the
+// fixed splits leave 1300 to 2600 waves for the chip), hence 16-byte loads
+// issued DEPTH chunks ahead into register sets of their own and small
+// workgroups that spread over all CUs.
+//
+// The form before this one (wgrad_gather_k) gathered every fragment from global
+// memory with 2-byte loads, 16 of them and 8 index divisions per MFMA; it
+// serves pointers that are not aligned to 16 bytes.  Measured, same sums bit for
+// bit: 48 -> 16 channels at 129^3 5217 -> 540 us, 96 -> 32 at 65^3 1144 ->
+// 284 us, 32 -> 32 at 65^3 882 -> 95 us, 128 -> 64 at 33^3 1046 -> 114 us; the
+// eleven layers of a 129^3 training step 14.9 -> 1.6 ms.  With one 9-wave
+// workgroup per split and channel group and loads one chunk ahead they took
+// 2.2 ms (147 workgroups for 256 CUs in the first of these layers).
+template <int NBW, int STRIDE>
+__global__ void __launch_bounds__(192)
+wgrad_rows_k(Tensor x, int cin, Tensor dy, int cout, int kpad, int per_split, float *__restrict__ partial)
+{
+    static_assert(NBW <= 3, "wave w stages the output channels 16 w .. 16 w + 15");
+    constexpr int DEPTH = 3;
+    constexpr int C = STRIDE == 1 ? 64 : 32;     // voxels per chunk
+    constexpr int RING = 3 * C, PITCH = RING + 8;   // bf16 per staged row: rows 16-byte aligned, halves 32 banks apart
+    constexpr int NX = STRIDE;                   // staged rows per channel (stride 2: even and odd x)
+    __shared__ __attribute__((aligned(16))) __bf16 xs[3][NX][16][PITCH];
+    __shared__ __attribute__((aligned(16))) __bf16 ys[NBW * 16][PITCH];
+    __shared__ __attribute__((aligned(16))) unsigned msk[2][RING / 2];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int g = lane >> 4, r16 = lane & 15;
+    const int nout = dy.n, nin = x.n, Nout = nout * nout * nout;
+    const int dz = blockIdx.z % 3;
+    const int split = blockIdx.x, c0 = blockIdx.y * 16, co0 = (blockIdx.z / 3) * 16 * NBW;
+    const int sy = w - 1, sz = dz - 1;
+    const int ob = split * per_split, oe = min(Nout, ob + per_split);
+
+    // Staging: this lane's voxel pair of a chunk and its 8 channels (half);
+    // with stride 2 also the row it stages (even or odd x).
+    const int pair = STRIDE == 1 ? (lane & 31) : (lane & 15);
+    const int half = STRIDE == 1 ? (lane >> 5) : ((lane >> 4) & 1);
+    const int odd = STRIDE == 1 ? 0 : (lane >> 5);
+    const bool chan_ok = c0 + 8 * half < cin;
+    int o = ob + 2 * pair, i, j, k;              // the pair's first voxel of the next chunk to load
+    decode3(o, nout, i, j, k);
+    const int di = C % nout, dj = C / nout % nout, dk = C / nout / nout;   // one chunk further
+    const __bf16 *xp = x.p + (chan_ok ? c0 + 8 * half : c0);
+    const bool stage_y = w < NBW && (STRIDE == 1 || lane < 32);
+    const __bf16 *yp = dy.p + (stage_y ? co0 + 16 * w + 8 * half : co0);
+    struct Set {
+        bf16x8 x[2], y[2];
+        unsigned m, okx, oky;
+    };
+    // Every lane loads from an address clamped into the tensors and masks what it stores: a load in a
+    // branch, or a value masked at once, would be waited for where it is issued.
+    auto load = [&](Set &r) {
+        int a = i, b = j, c = k;
+        r.m = r.okx = r.oky = 0;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int oo = o + e;
+            const int xi = STRIDE * a + odd, xj = STRIDE * b + sy, xk = STRIDE * c + sz;
+            const int ci = min(xi, nin - 1), cj = min(max(xj, 0), nin - 1), ck = min(max(xk, 0), nin - 1);
+            r.x[e] = *reinterpret_cast<const bf16x8 *>(xp + (size_t)(ci + nin * (cj + nin * ck)) * x.cs);
+            r.y[e] = *reinterpret_cast<const bf16x8 *>(yp + (size_t)(stage_y ? min(oo, Nout - 1) : 0) * dy.cs);
+            const unsigned h = e ? 0xffff0000u : 0xffffu;
+            if (chan_ok && oo < Nout && xi == ci && xj == cj && xk == ck) r.okx |= h;
+            if (oo < oe) r.oky |= h;
+            if (oo < oe && a != (half ? nout - 1 : 0)) r.m |= h;
+            ++a;
+            const int wa = a == nout;
+            a = wa ? 0 : a;
+            b += wa;
+            const int wb = b == nout;
+            b = wb ? 0 : b;
+            c += wb;
+        }
+        o += C;
+        i += di;
+        const int wi = i >= nout;
+        i -= wi ? nout : 0;
+        j += dj + wi;
+        const int wj = j >= nout;
+        j -= wj ? nout : 0;
+        k += dk + wj;
+    };
+    auto store = [&](const Set &r, int slot) {
+        const int p = slot * C + 2 * pair;
+        union U {
+            bf16x8 v;
+            unsigned short h[8];
+        };
+        U a, b;
+        a.v = r.x[0];
+        b.v = r.x[1];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            *reinterpret_cast<unsigned *>(&xs[w][odd][8 * half + q][p]) =
+                ((unsigned)a.h[q] | ((unsigned)b.h[q] << 16)) & r.okx;
+        if (stage_y) {
+            a.v = r.y[0];
+            b.v = r.y[1];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                *reinterpret_cast<unsigned *>(&ys[16 * w + 8 * half + q][p]) =
+                    ((unsigned)a.h[q] | ((unsigned)b.h[q] << 16)) & r.oky;
+        }
+        if (STRIDE == 1 && w == 2) msk[half][p >> 1] = r.m;
+    };
+
+    f32x4 acc[3][NBW];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int b = 0; b < NBW; ++b) acc[d][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // The last slot is read as the voxels before the split's first one (tap
+    // dx = -1 of voxel ob): the last voxel of the split before, from the same row.
+    if (lane < 16 * NX) {
+        __bf16 v = (__bf16)0.f;
+        const int ch = lane & 15, row = lane >> 4;
+        if (ob > 0) {
+            int pi, pj, pk;
+            decode3(ob - 1, nout, pi, pj, pk);
+            const int xi = STRIDE * pi + row, xj = STRIDE * pj + sy, xk = STRIDE * pk + sz;
+            if (c0 + ch < cin && xi < nin && xj >= 0 && xj < nin && xk >= 0 && xk < nin)
+                v = x.p[(size_t)(xi + nin * (xj + nin * xk)) * x.cs + c0 + ch];
+        }
+        xs[w][row][ch][RING - 2] = (__bf16)0.f;
+        xs[w][row][ch][RING - 1] = v;
+    }
+
+    // chunk c from its slot: MFMAs of 32 voxels each
+    auto compute = [&](int c, int slot) {
+#pragma unroll
+        for (int st = 0; st < C / 32; ++st) {
+            if (ob + c * C + 32 * st >= oe) break;
+            const int p = slot * C + 32 * st + 8 * g;
+            bf16x8 a[NBW];
+#pragma unroll
+            for (int b = 0; b < NBW; ++b) a[b] = *reinterpret_cast<const bf16x8 *>(&ys[16 * b + r16][p]);
+            union F {
+                bf16x8 v;
+                unsigned d[4];
+            };
+            F f0, f1, f2, m;
+            const __bf16 *row = xs[w][NX - 1][r16];
+            m.v = *reinterpret_cast<const bf16x8 *>(row + p);
+            const unsigned before = *reinterpret_cast<const unsigned *>(row + (p == 0 ? RING - 2 : p - 2));
+            f0.d[0] = __builtin_amdgcn_alignbit(m.d[0], before, 16);
+            f0.d[1] = __builtin_amdgcn_alignbit(m.d[1], m.d[0], 16);
+            f0.d[2] = __builtin_amdgcn_alignbit(m.d[2], m.d[1], 16);
+            f0.d[3] = __builtin_amdgcn_alignbit(m.d[3], m.d[2], 16);
+            if constexpr (STRIDE == 1) {
+                const unsigned after = *reinterpret_cast<const unsigned *>(row + (p + 8 == RING ? 0 : p + 8));
+                f1.v = m.v;
+                f2.d[0] = f0.d[1];
+                f2.d[1] = f0.d[2];
+                f2.d[2] = f0.d[3];
+                f2.d[3] = __builtin_amdgcn_alignbit(after, m.d[3], 16);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f0.d[q] &= msk[0][(p >> 1) + q];
+                    f2.d[q] &= msk[1][(p >> 1) + q];
+                }
+            } else {
+                f1.v = *reinterpret_cast<const bf16x8 *>(&xs[w][0][r16][p]);
+                f2.v = m.v;
+            }
+#pragma unroll
+            for (int b = 0; b < NBW; ++b) {
+                acc[0][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[b], f0.v, acc[0][b], 0, 0, 0);
+                acc[1][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[b], f1.v, acc[1][b], 0, 0, 0);
+                acc[2][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[b], f2.v, acc[2][b], 0, 0, 0);
+            }
+        }
+    };
+
+    // Step c stores chunk c + 1, asks for chunk c + 1 + DEPTH and works on chunk
+    // c.  dy and the masks of chunk c were stored by their waves before the
+    // barrier of step c; a wave past it stores chunk c + 2, whose slot held
+    // chunk c - 1, which no wave reads any more.
+    Set r[DEPTH];
+    load(r[0]);
+    store(r[0], 0);
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load(r[d]);
+    const int nchunk = (oe - ob + C - 1) / C;
+    for (int c = 0; c < nchunk; c += DEPTH) {     // slot of chunk c: c mod 3, and DEPTH = 3
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {     // past the last chunk: nothing to compute, clamped loads
+            store(r[d], (d + 1) % 3);
+            load(r[d]);
+            __syncthreads();
+            compute(c + d, d);
+        }
+    }
+    if (c0 + r16 >= cin) return;
+    float *P = partial + (size_t)split * cout * kpad;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int b = 0; b < NBW; ++b)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+                P[(size_t)(co0 + 16 * b + 4 * g + r4) * kpad + (3 * (w + 3 * dz) + d) * cin + c0 + r16] = acc[d][b][r4];
+}
+
+// The same sums with every fragment gathered by 2-byte loads, one wave per
+// (16 co x 16 kk) tile and split: takes pointers of any alignment.
 __global__ void __launch_bounds__(256)
-wgrad_k(Tensor x, int cin, Tensor dy, int cout, int kpad, int stride, int nsplit, int per_split,
+wgrad_gather_k(Tensor x, int cin, Tensor dy, int cout, int kpad, int stride, int nsplit, int per_split,
         float *__restrict__ partial)
 {
     const int lane = threadIdx.x & 63;
@@ -367,13 +586,25 @@ wgrad_k(Tensor x, int cin, Tensor dy, int cout, int kpad, int stride, int nsplit
     for (int r = 0; r < 4; ++r) P[(size_t)(ct * 16 + 4 * g + r) * kpad + kk] = acc[r];
 }
 
-// out[t] = sum_s partial[s, t] in fixed order
-__global__ void split_reduce_k(const float *__restrict__ partial, int nsplit, int count, float *__restrict__ out)
+// out[t] = sum_s partial[s, t] in fixed order, 0 in the padding of a weight
+// row (t % kpad >= kreal); 16 loads in flight per thread, added in order.
+__global__ void split_reduce_k(const float *__restrict__ partial, int nsplit, int count, int kpad, int kreal,
+                               float *__restrict__ out)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= count) return;
     float s = 0.f;
-    for (int q = 0; q < nsplit; ++q) s += partial[(size_t)q * count + t];
+    if (t % kpad < kreal) {
+        int q = 0;
+        for (; q + 16 <= nsplit; q += 16) {
+            float v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = partial[(size_t)(q + e) * count + t];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s += v[e];
+        }
+        for (; q < nsplit; ++q) s += partial[(size_t)q * count + t];
+    }
     out[t] = s;
 }
 
@@ -389,17 +620,39 @@ int wgrad_splits(int cout, int kpad, int nout)
     return ns;
 }
 
+template <int STRIDE>
+static void wgrad_rows(Tensor x, int cin, Tensor dy, int cout, int kpad, int nsplit, int per, float *partial, hipStream_t s)
+{
+    const unsigned cg = (unsigned)((cin + 15) / 16);
+    const int nct = cout / 16;
+    // two tiles of output channels share the staged x while 3 waves are left for every CU
+    const bool two = nct % 2 == 0 && nsplit * (int)cg * 3 * (nct / 2) >= 256;
+    const dim3 grid((unsigned)nsplit, cg, (unsigned)(3 * (two ? nct / 2 : nct)));
+    if (two)
+        hipLaunchKernelGGL((wgrad_rows_k<2, STRIDE>), grid, dim3(192), 0, s, x, cin, dy, cout, kpad, per, partial);
+    else
+        hipLaunchKernelGGL((wgrad_rows_k<1, STRIDE>), grid, dim3(192), 0, s, x, cin, dy, cout, kpad, per, partial);
+}
+
 void launch_wgrad(Tensor x, int cin, Tensor dy, int cout, int kpad, int stride, float *partial, float *dw, hipStream_t s)
 {
     const int nsplit = wgrad_splits(cout, kpad, dy.n);
     const int Nout = dy.n * dy.n * dy.n;
     int per = (Nout + nsplit - 1) / nsplit;
     per = (per + 31) / 32 * 32;
-    const int waves = (cout / 16) * (kpad / 16) * nsplit;
-    hipLaunchKernelGGL(wgrad_k, dim3((waves + 3) / 4), dim3(256), 0, s, x, cin, dy, cout, kpad, stride, nsplit, per,
-                       partial);
+    // slot widths are multiples of 8 channels, so an aligned base aligns every 8-channel load
+    const bool aligned = (((uintptr_t)x.p | (uintptr_t)dy.p) & 15) == 0 && x.cs % 8 == 0 && dy.cs % 8 == 0;
+    if (aligned && stride == 1) {
+        wgrad_rows<1>(x, cin, dy, cout, kpad, nsplit, per, partial, s);
+    } else if (aligned) {
+        wgrad_rows<2>(x, cin, dy, cout, kpad, nsplit, per, partial, s);
+    } else {
+        const int waves = (cout / 16) * (kpad / 16) * nsplit;
+        hipLaunchKernelGGL(wgrad_gather_k, dim3((waves + 3) / 4), dim3(256), 0, s, x, cin, dy, cout, kpad, stride, nsplit,
+                           per, partial);
+    }
     const int cnt = cout * kpad;
-    hipLaunchKernelGGL(split_reduce_k, dim3((cnt + 255) / 256), dim3(256), 0, s, partial, nsplit, cnt, dw);
+    hipLaunchKernelGGL(split_reduce_k, dim3((cnt + 255) / 256), dim3(256), 0, s, partial, nsplit, cnt, kpad, 27 * cin, dw);
 }
 
 // Splits of a voxel range for the fixed-order reductions below: at most
@@ -436,7 +689,7 @@ void launch_bgrad(Tensor dy, int c, float *partial, float *db, hipStream_t s)
     const int nsplit = reduce_splits(N);
     const int per = (N + nsplit - 1) / nsplit;
     hipLaunchKernelGGL(bgrad_k, dim3(nsplit), dim3(256), 0, s, dy, c, per, partial);
-    hipLaunchKernelGGL(split_reduce_k, dim3((c + 255) / 256), dim3(256), 0, s, partial, nsplit, c, db);
+    hipLaunchKernelGGL(split_reduce_k, dim3((c + 255) / 256), dim3(256), 0, s, partial, nsplit, c, c, c, db);
 }
 
 // ---------------------------------------------------------- elementwise
@@ -629,7 +882,7 @@ void launch_head_bwd(const float *dyh, Tensor x, int c, const float *w, Tensor d
     const int nsplit = reduce_splits(N);
     const int per = (N + nsplit - 1) / nsplit;
     hipLaunchKernelGGL(head_bwd_w_k, dim3(nsplit), dim3(256), 0, s, dyh, x, c, per, partial);
-    hipLaunchKernelGGL(split_reduce_k, dim3(1), dim3(256), 0, s, partial, nsplit, c + 1, dwb);
+    hipLaunchKernelGGL(split_reduce_k, dim3(1), dim3(256), 0, s, partial, nsplit, c + 1, c + 1, c + 1, dwb);
 }
 
 // Mean squared error over interior nodes; dy = 2 (yhat - t) / N_int there, 0 on
