@@ -1,22 +1,42 @@
 // Two red-black Gauss-Seidel sweeps in one pass over u and f (Sec. 2: the
 // smoother of the multigrid solves of Eq. 1 and Eq. 2), with the four
-// half-sweeps of a z-march skewed two planes apart.
+// half-sweeps of a z-march skewed one plane apart.
 //
-// Step s of the march updates the red nodes of plane s (first sweep), the
-// black nodes of plane s - 2 (first sweep), the red nodes of plane s - 4
-// (second sweep) and the black nodes of plane s - 6 (second sweep).  Each of
-// these reads only nodes of the other colour on its plane and the two next to
-// it, and none of those is written in the same step: the red updates of steps
-// s - 1 and s - 5 and the black updates of step s - 1 are the newest values any
-// of them needs, so the four stages run together between one pair of
-// barriers, and every node update sees exactly the values it sees in two
-// sequential sweeps.  In x and y each stage covers one ring fewer than the one
-// before (the tile plus three, two, one and zero nodes), recomputing the
-// neighbours' ring nodes from the same inputs, so the tile's values equal the
-// sequential sweeps' bit for bit.  LDS holds ten planes (s - 7 .. s + 2) of
-// the tile plus a four-node ring; a plane of u and the f values of a step are
-// requested two steps before use.  A workgroup marches the whole column.
-// Red nodes are those with i + j + k even.
+// A thread owns one x-pair of nodes (one red, one black: i + j + k even and
+// odd) of the tile plus a four-node ring and marches along z.  Step s updates
+// the red node of plane s (first sweep), the black one of plane s - 1 (first
+// sweep), the red one of plane s - 2 (second sweep) and the black one of plane
+// s - 3 (second sweep).  A node's z neighbours and one of its x neighbours
+// belong to its own thread and stay in registers, those of this step among
+// them; only the other x neighbour and the two y neighbours come from LDS, on
+// the same plane, where the stage before left them in the step before.  So
+// LDS holds two half-planes (one colour) per stage, indexed by the thread: all
+// accesses of a wavefront are consecutive, the twelve reads of a step are
+// independent, and one barrier per plane separates the steps.  Of a pair, all
+// four stages of a step update the same node.  Every node update sees exactly
+// the values it sees in two sequential sweeps.  In x and y each stage covers
+// one ring fewer than the one before (the tile plus three, two, one and zero
+// nodes), recomputing the neighbours' ring nodes from the same inputs, so the
+// tile's values equal the sequential sweeps' bit for bit.  A plane of u and of
+// f is requested two steps before use.
+//
+// A workgroup marches planes K0 .. K1 - 1 of its column: the whole column, or a
+// chunk of it on grids whose columns alone leave CUs idle (257^3: 64 columns of
+// 64x16 for 256 CUs).  A chunk needs u four planes and the stages three, two
+// and one plane beyond its ends, which it recomputes as it does the ring: the
+// march starts at step K0 - 3 and ends with step K1 + 2, and what the stages
+// write further out is read by no value that is kept.
+//
+// Bound: 513^3 by HBM (two sweeps move 24 B per node once: 592 us FP64 = 5.5
+// TB/s), smaller grids by the step's issue and latency (about 0.7 us on 64x16
+// columns).  The form before this one skewed the stages two planes apart and
+// read all six neighbours from ten LDS planes of both colours, at a stride of
+// two values: 1.4 us per step, 726 us at 513^3.  FP64 pairs, before -> now (with
+// the correction): 513^3 726 -> 592 (862 -> 697) us; 257^3, there two single
+// sweeps, 203 -> 92 (235 -> 111) us in 64-plane chunks; 129^3 45 -> 24 (59 -> 31)
+// us in 8-plane chunks; 65^3, there 8^3 bricks, 18 -> 15 (26 -> 19) us.  64x16
+// columns waste least on the ring (1.7 nodes per node of the tile; 1.9 at 32x16,
+// 2.5 at 32x8) and win from 129^3 up; the small ones fill the chip at 65^3.
 #include "common.h"
 
 namespace qm {
@@ -25,34 +45,36 @@ namespace {
 
 // ZERO: the iterate is zero (uin is not read).  PROLONG: the coarse-grid
 // correction u += P uc (uc on the grid of nc = (n + 1) / 2 points) is added to
-// every interior node as its plane is stored to LDS, with the trilinear
+// every interior node as its plane enters the march, with the trilinear
 // expression of the prolong-add kernel evaluated in the same order (along x,
 // then y, then z) on coarse planes staged in LDS, so the result is that of a
 // prolong-add launch followed by the two sweeps, bit for bit.
 template <typename T, int TX, int TY, int NT, bool ZERO, bool PROLONG>
 __global__ void __launch_bounds__(NT)
 rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restrict__ f, int n, T h2,
-             const T *__restrict__ uc, int nc)
+             const T *__restrict__ uc, int nc, int kchunk, int nchunk)
 {
 #pragma clang fp contract(off)
     typedef T pair_t __attribute__((ext_vector_type(2), aligned(sizeof(T))));
-    constexpr int RG = 4;                                  // ring of the region held in LDS
-    constexpr int PX = TX + 2 * RG, PY = TY + 2 * RG, PL = PX * PY;
-    constexpr int NS = 10;                                 // planes s - 7 .. s + 2
-    constexpr int HPX = PX / 2, NPL = HPX * PY;            // x-pairs of nodes of an LDS plane
-    constexpr int HP = PX / 2, NP = HP * (TY + 6);         // node pairs: four-node ring in x, three in y
-    static_assert(TX % 2 == 0 && NP <= NT, "at most one pair of nodes per thread");
-    // coarse rows of the LDS region (tile origins are odd): TY / 2 + 5; a coarse
-    // plane is staged interpolated along x, on the region's fine columns
-    constexpr int CPY = TY / 2 + 5, XPL = PX * CPY, NXL = (XPL + NT - 1) / NT;
-    static_assert(NPL <= NT, "one pair of an LDS plane per thread");
-    __shared__ T pl[NS][PL];
+    constexpr int RG = 4;                                  // ring of the region a workgroup owns
+    constexpr int HP = TX / 2 + RG, PY = TY + 2 * RG, NP = HP * PY;   // its x-pairs and rows
+    static_assert(TX % 2 == 0 && TY % 2 == 0 && NP <= NT, "one pair of nodes per thread");
+    constexpr int PAD = HP + 1, ROW = NP + 2 * PAD;        // reads of the outermost pairs stay inside
+    // coarse rows of the region (tile origins are odd): TY / 2 + 5; a coarse
+    // plane is staged interpolated along x on the region's fine columns, the
+    // even and the odd of a pair apart
+    constexpr int CPY = TY / 2 + 5, XPL = 2 * HP * CPY, NXL = (XPL + NT - 1) / NT;
+    __shared__ T half[4][2][ROW];   // [black, red 1, black 1, red 2][plane parity]
     __shared__ T cpl[PROLONG ? 3 : 1][PROLONG ? XPL : 1];   // coarse plane c, along x, in slot c % 3
     const T sixth = T(1) / T(6);
     const int tid = threadIdx.x;
     const unsigned tl = xcd_tile(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z),
                                  gridDim.x * gridDim.y * gridDim.z);
-    const int bx = tl % gridDim.x, by = (tl / gridDim.x) % gridDim.y, pb = tl / (gridDim.x * gridDim.y);
+    const int bx = tl % gridDim.x, by = (tl / gridDim.x) % gridDim.y, bz = tl / (gridDim.x * gridDim.y);
+    const int pb = bz / nchunk, ch = bz - pb * nchunk;
+    // kchunk is even and at least 4, so every march starts with an odd step
+    const int K0 = max(1, ch * kchunk), K1 = min(n - 1, (ch + 1) * kchunk);
+    const int s0 = max(1, K0 - 3), umax = min(n - 1, K1 + 3), fmax = min(n - 2, K1 + 2);
     const int i0 = 1 + bx * TX, j0 = 1 + by * TY;
     const size_t nn = (size_t)n * n;
     if (!ZERO) uin += (size_t)pb * nn * n;
@@ -60,50 +82,56 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
     f += (size_t)pb * nn * n;
     if (PROLONG) uc += (size_t)pb * nc * nc * nc;
 
-    // A plane of u arrives as one x-pair of nodes per thread (iq, iq + 1 of
-    // row jq; LDS offset lq): one 16-byte load from a base clamped into the
-    // grid's row (node iq + e sits at element e + sh of the load), requested
-    // into registers as it is and masked where it is stored, two steps later,
-    // so nothing waits for the load in between; a lane with nothing to load
-    // reads the tile's corner pair (lanes of all workgroups meeting on one
-    // cache line would queue on it).
-    const int qa = tid % HPX, qb = tid / HPX;
-    const int iq = i0 - RG + 2 * qa, jq = j0 - RG + qb, lq = qb * PX + 2 * qa;
-    const bool qrow = tid < NPL && jq >= 0 && jq < n;
-    const int sh = iq - min(max(iq, 0), n - 2);
-    const bool in0 = qrow && iq >= 0 && iq <= n - 1, in1 = qrow && iq + 1 >= 0 && iq + 1 <= n - 1;
+    // This thread's pair: nodes (il, jp), (il + 1, jp).  Bit 2w + e of ok says
+    // that node e is an interior node on the tile plus a ring of width w.
+    const int q = tid % HP, br = tid / HP;
+    const int il = i0 - RG + 2 * q, jp = j0 - RG + br;
+    unsigned ok = 0;
+    if (tid < NP && jp >= 1 && jp <= n - 2) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int a = 2 * q + e, i = il + e;
+                if (a >= RG - w && a <= RG + TX - 1 + w && br >= RG - w && br <= RG + TY - 1 + w && i >= 1 && i <= n - 2)
+                    ok |= 1u << (2 * w + e);
+            }
+    }
+    const int me = PAD + min(tid, NP - 1);     // LDS place of the pair
+    // u of the pair on a plane: one 16-byte load from a base clamped into the
+    // grid's row (node il + e sits at element e + sh of the load), taken as it
+    // is and masked where it is used, two steps later, so nothing waits for the
+    // load in between; a lane with nothing to load reads the tile's corner pair
+    // (lanes of all workgroups meeting on one cache line would queue on it).
+    const bool row = tid < NP && jp >= 0 && jp < n;
+    const int ic = min(max(il, 0), n - 2), sh = il - ic;
+    const bool in0 = row && il >= 0 && il <= n - 1, in1 = row && il + 1 >= 0 && il + 1 <= n - 1;
     const int idle = i0 + n * j0;
-    const int qoff = qrow ? min(max(iq, 0), n - 2) + n * jq : idle;
-    auto fetch = [&](int k, pair_t &vv) {
-        if (ZERO) return;
-        vv = *reinterpret_cast<const pair_t *>(uin + (size_t)k * nn + qoff);
+    const int uoff = row ? ic + n * jp : idle;
+    auto fetch = [&](int k, pair_t &v) {
+        if (!ZERO) v = *reinterpret_cast<const pair_t *>(uin + (size_t)k * nn + uoff);
     };
-    // The correction's coarse data: per staged entry r of this thread (fine
-    // column a = t % PX, coarse row cj0 + t / PX of the region), the two
-    // coarse nodes its x-interpolation weighs (xo, or -1 where the column is
-    // not interior or the row is outside the grid: a lane with nothing to load
-    // reads the first of the region's coarse nodes) and the column's parity;
-    // per node e of the thread's pair that is interior in x and y, the offset
-    // of its column and lower coarse row in the staged plane with the parity
-    // of j in bit 16 (else -1).
+    // f of the pair (in range: both columns lie in the grid when either is
+    // interior on the widest ring)
+    const int foff = (ok >> 6) != 0 ? il + n * jp : idle;
+    auto f_pair = [&](int k) { return *reinterpret_cast<const pair_t *>(f + (size_t)k * nn + foff); };
+
+    // The correction's coarse data: per staged entry r of this thread (pair t %
+    // HP, parity and coarse row from t / HP), the two coarse nodes its
+    // x-interpolation weighs (xo, or -1 where the column is not interior or the
+    // row is outside the grid: a lane with nothing to load reads the first of
+    // the region's coarse nodes); odd columns of the grid are interpolated.
     const int cj0 = (j0 - RG) >> 1;
-    int xo[NXL], cnb[2] = {-1, -1};
+    int xo[NXL];
     bool xodd[NXL];
     const int cidle = max((i0 - RG) >> 1, 0) + nc * max(cj0, 0);
     if constexpr (PROLONG) {
 #pragma unroll
         for (int r = 0; r < NXL; ++r) {
             const int t = tid + r * NT;
-            const int i = i0 - RG + t % PX, J = cj0 + t / PX;
+            const int e = (t / HP) & 1, i = i0 - RG + 2 * (t % HP) + e, J = cj0 + t / (2 * HP);
             xo[r] = (t < XPL && i >= 1 && i <= n - 2 && J >= 0 && J < nc) ? (i >> 1) + nc * J : -1;
             xodd[r] = i & 1;
-        }
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int a = 2 * qa + e, i = iq + e, j = jq;
-            cnb[e] = (tid < NPL && i >= 1 && i <= n - 2 && j >= 1 && j <= n - 2)
-                         ? a + PX * ((j >> 1) - cj0) + ((j & 1) << 16)
-                         : -1;
         }
     }
     T cv0[NXL], cv1[NXL];
@@ -131,140 +159,134 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
             }
         }
     };
-    // the correction at a node of plane k (1 <= k <= n - 2) from its packed offset:
+    // the correction at node e of the pair on plane k (1 <= k <= n - 2):
     // prolong_at's y and z steps on the staged planes
-    auto corr = [&](int cw, int k) {
-        const int o = cw & 0xffff, dj = (cw >> 16) & 1;
+    const int dj = jp & 1, crow = q + 2 * HP * max((jp >> 1) - cj0, 0);
+    const bool jin = tid < NP && jp >= 1 && jp <= n - 2;
+    const bool cin0 = jin && il >= 1 && il <= n - 2, cin1 = jin && il + 1 >= 1 && il + 1 <= n - 2;
+    auto corr = [&](int e, int k) {
         const T wja = dj ? T(0.5) : T(1), wjb = dj ? T(0.5) : T(0);
         const T wka = (k & 1) ? T(0.5) : T(1), wkb = (k & 1) ? T(0.5) : T(0);
         const T *Xa = cpl[(k >> 1) % 3], *Xb = cpl[((k + 1) >> 1) % 3];
-        const int oj = o + dj * PX;
+        const int o = crow + e * HP, oj = o + dj * 2 * HP;
         const T xa = Xa[o], xb = Xa[oj], xc = Xb[o], xd = Xb[oj];
         return wka * (wja * xa + wjb * xb) + wkb * (wja * xc + wjb * xd);
     };
-    // With the correction only the black node of a pair takes it: a red
-    // node's own value is replaced by the first sweep's red update before any
-    // update reads it, and red nodes of the outer ring are not read at all.
-    auto commit = [&](int k, const pair_t &vv) {
-        if (tid >= NPL) return;
-        T x0 = (!ZERO && in0) ? (sh == 0 ? vv.x : vv.y) : T(0);
-        T x1 = (!ZERO && in1) ? (sh == 0 ? vv.y : vv.x) : T(0);
-        if (PROLONG && k >= 1 && k <= n - 2) {
-            const int eb = (iq + jq + k + 1) & 1;   // the pair's black node
-            const int cw = eb ? cnb[1] : cnb[0];
-            if (cw >= 0) {
-                const T c = corr(cw, k);
-                if (eb) x1 += c;
-                else x0 += c;
-            }
-        }
-        T *P = pl[k % NS] + lq;
-        P[0] = x0;
-        P[1] = x1;
+    // The pair's red and black value as plane k enters (er: the red node).  With
+    // the correction only the black one takes it: a red node's own value is
+    // replaced by the first sweep's red update before any update reads it, and
+    // red nodes of the outer ring are not read at all.
+    auto enter = [&](int k, const pair_t &v, int er, T &r, T &b) {
+        const T x0 = (!ZERO && in0) ? (sh == 0 ? v.x : v.y) : T(0);
+        const T x1 = (!ZERO && in1) ? (sh == 0 ? v.y : v.x) : T(0);
+        r = er ? x1 : x0;
+        b = er ? x0 : x1;
+        if (PROLONG && k >= 1 && k <= n - 2 && (er ? cin0 : cin1)) b += corr(er ^ 1, k);
     };
 
-    // This thread's pair of nodes: grid columns il, il + 1 of row jp, LDS
-    // offsets cb, cb + 1.  Bit 2w + e of ok says that node e of the pair is an
-    // interior node on the tile plus a ring of width w (rings 3, 2, 1, 0 hold
-    // the four stages' nodes).
-    const int q = tid % HP, br = tid / HP;
-    const int il = i0 - RG + 2 * q, jp = j0 - 3 + br;
-    const int cb = (br + RG - 3) * PX + 2 * q;
-    unsigned ok = 0;
-    if (tid < NP && jp >= 1 && jp <= n - 2) {
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int a = 2 * q + e, b = br + RG - 3, i = il + e;
-                if (a >= RG - w && a <= RG + TX - 1 + w && b >= RG - w && b <= RG + TY - 1 + w && i >= 1 && i <= n - 2)
-                    ok |= 1u << (2 * w + e);
-            }
-    }
-    // f of the pair on plane k (in range: both columns lie in the grid when
-    // either is interior; else the tile's corner pair)
-    const bool fok = (ok >> 6) != 0;
-    const size_t frow = fok ? (size_t)il + (size_t)n * jp : (size_t)idle;
-    auto f_pair = [&](int k) { return *reinterpret_cast<const pair_t *>(f + (size_t)k * nn + frow); };
-    // node e of the pair on plane k takes its update from f value fv
-    auto update = [&](int k, int e, T fv) {
-        T *P = pl[k % NS];
-        const T *Pm = pl[(k - 1) % NS];
-        const T *Pp = pl[(k + 1) % NS];
-        const int c = cb + e;
-        const T s = P[c - 1] + P[c + 1] + P[c - PX] + P[c + PX] + Pm[c] + Pp[c];
-        const T v = (s - h2 * fv) * sixth;
-        P[c] = v;
-        return v;
-    };
-
-    // warm-up: planes 0, 1, 2 in LDS (with the correction: coarse planes 0, 1, 2
-    // first); planes 3, 4, the f pairs of planes 1, 2 and coarse plane 3 in flight
+    // Own values by plane.  Before step s: bz[0], bz[1] = black of planes s - 1, s
+    // as they entered; ra = red of plane s; r1 = red of planes s - 1, s - 2 after
+    // the first sweep; b1 = black of planes s - 2, s - 3; r2 = red of planes
+    // s - 3, s - 4 after the second.  hr, hb: h^2 f of the red node of planes
+    // s - 1, s - 2 and of the black node of planes s - 1 .. s - 3.
+    T bzm, bzc, ra, r1a, r1b, b1a = T(0), b1b = T(0), r2a = T(0), r2b = T(0);
+    T hr1 = T(0), hr2 = T(0), hb1 = T(0), hb2 = T(0), hb3 = T(0);
+    // warm-up: planes s0 - 1 and s0 enter (with the correction: coarse planes
+    // e, e + 1, e + 2 first, e = (s0 - 1) / 2); planes s0 + 1, s0 + 2, the f pairs
+    // of planes s0, s0 + 1 and coarse plane e + 3 in flight
+    int er = (il + jp + s0) & 1;         // the red node of the pair on plane s0
     {
-        pair_t w[3] = {};
-#pragma unroll
-        for (int z = 0; z < 3; ++z) fetch(z, w[z]);
+        pair_t w0 = {T(0), T(0)}, w1 = {T(0), T(0)};
+        fetch(s0 - 1, w0);
+        fetch(s0, w1);
         if constexpr (PROLONG) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                fetch_c(c);
-                store_c(c);
+                fetch_c((s0 - 1) / 2 + c);
+                store_c((s0 - 1) / 2 + c);
             }
             __syncthreads();
         }
-#pragma unroll
-        for (int z = 0; z < 3; ++z) commit(z, w[z]);
+        enter(s0 - 1, w0, er ^ 1, r1a, bzm);
+        enter(s0, w1, er, ra, bzc);
+        r1b = T(0);
     }
-    fetch_c(3);
+    fetch_c((s0 - 1) / 2 + 3);
     pair_t vA = {T(0), T(0)}, vB = {T(0), T(0)};
-    if (3 <= n - 1) fetch(3, vA);
-    if (4 <= n - 1) fetch(4, vB);
-    pair_t pA = {T(0), T(0)}, pB = {T(0), T(0)};
-    if (1 <= n - 2) pA = f_pair(1);
-    if (2 <= n - 2) pB = f_pair(2);
-    // f of the red node of planes s .. s - 4 and of the black node of planes s .. s - 6
-    T fr[5], fb[7];
-#pragma unroll
-    for (int r = 0; r < 5; ++r) fr[r] = T(0);
-#pragma unroll
-    for (int r = 0; r < 7; ++r) fb[r] = T(0);
+    fetch(min(s0 + 1, umax), vA);
+    fetch(min(s0 + 2, umax), vB);
+    pair_t pA = f_pair(min(s0, fmax)), pB = f_pair(min(s0 + 1, fmax));
+    if (tid < NP) half[0][s0 & 1][me] = bzc;
     __syncthreads();
 
-    const int smax = n + 4;   // the last black update of the second sweep is plane n - 2
+    const int smax = K1 + 2;   // the last black update of the second sweep is plane K1 - 1
+    T *const dst = uout + (size_t)n * jp + il;
     // even: s is even (the loop's second step of a pair); with the correction,
-    // an even step s stores coarse plane (s + 4) / 2, first read by the commit
-    // of fine plane s + 3 in step s + 1, and requests plane (s + 6) / 2
+    // an even step s stores coarse plane (s + 4) / 2, first read by fine plane
+    // s + 3, which enters in step s + 2, and requests plane (s + 6) / 2
     auto step = [&](int s, pair_t &vX, pair_t &pX, bool even) {
-        const int er = (il + jp + s) & 1;   // the red node of the pair on planes s, s - 4
-        const int eb = er ^ 1;              // the black one on planes s - 2, s - 6
-#pragma unroll
-        for (int r = 4; r > 0; --r) fr[r] = fr[r - 1];
-#pragma unroll
-        for (int r = 6; r > 0; --r) fb[r] = fb[r - 1];
-        fr[0] = er ? pX.y : pX.x;
-        fb[0] = er ? pX.x : pX.y;
-        if (s + 2 <= n - 1) commit(s + 2, vX);   // into the slot of plane s - 8, last read in step s - 1
-        if (PROLONG && even) {   // into the slot of coarse plane s / 2 - 1, last read in step s - 3
+        const int p = even ? 0 : 1;      // parity of plane s, s - 2
+        const int xn = me + (er ? 1 : -1);
+        // the three lateral neighbours of the four updates
+        const T ax = half[0][p][xn], ad = half[0][p][me - HP], au = half[0][p][me + HP];
+        const T bx1 = half[1][p ^ 1][xn], bd = half[1][p ^ 1][me - HP], bu = half[1][p ^ 1][me + HP];
+        const T cx = half[2][p][xn], cd = half[2][p][me - HP], cu = half[2][p][me + HP];
+        const T dx = half[3][p ^ 1][xn], dd = half[3][p ^ 1][me - HP], du = half[3][p ^ 1][me + HP];
+        const unsigned m = ok >> er;
+        // plane s + 1 enters
+        T rn, bn;
+        enter(s + 1, vX, er ^ 1, rn, bn);
+        const T hr0 = h2 * (er ? pX.y : pX.x), hb0 = h2 * (er ? pX.x : pX.y);
+        if (PROLONG && even) {   // into the slot of coarse plane s / 2 - 1, last read in step s - 2
             store_c((s + 4) / 2);
             fetch_c((s + 6) / 2);
         }
-        // the next requests, their planes clamped into the grid (what the last
-        // steps fetch beyond plane n - 1, or n - 2 for f, is never used)
-        fetch(min(s + 4, n - 1), vX);
-        pX = f_pair(min(s + 2, n - 2));
-        if (s <= n - 2 && ((ok >> (6 + er)) & 1)) update(s, er, fr[0]);
-        if (s - 2 >= 1 && s - 2 <= n - 2 && ((ok >> (4 + eb)) & 1)) update(s - 2, eb, fb[2]);
-        if (s - 4 >= 1 && s - 4 <= n - 2 && ((ok >> (2 + er)) & 1)) update(s - 4, er, fr[4]);
-        // plane s - 6 is final after its black update: the pair's tile nodes go out
-        const int k = s - 6;
-        if (k >= 1 && k <= n - 2 && (ok & 3)) {
-            T *dst = uout + (size_t)k * nn + (size_t)n * jp + il;
-            if ((ok >> eb) & 1) dst[eb] = update(k, eb, fb[6]);
-            if ((ok >> er) & 1) dst[er] = pl[k % NS][cb + er];
+        // the next requests, their planes clamped into the march's (what the last
+        // steps fetch beyond them is never used)
+        fetch(min(s + 3, umax), vX);
+        pX = f_pair(min(s + 2, fmax));
+        // sums in the order of the single sweep (x, y, z neighbours; the two of x commute)
+        const T r1n = (s <= n - 2 && (m & 64)) ? (bzc + ax + ad + au + bzm + bn - hr0) * sixth : ra;
+        const T b1n = (s - 1 >= 1 && s - 1 <= n - 2 && (m & 16)) ? (r1a + bx1 + bd + bu + r1b + r1n - hb1) * sixth : bzm;
+        const T r2n = (s - 2 >= 1 && s - 2 <= n - 2 && (m & 4)) ? (b1a + cx + cd + cu + b1b + b1n - hr2) * sixth : r1b;
+        const T b2n = (r2a + dx + dd + du + r2b + r2n - hb3) * sixth;
+        if (tid < NP) {
+            half[0][p ^ 1][me] = bn;
+            half[1][p][me] = r1n;
+            half[2][p ^ 1][me] = b1n;
+            half[3][p][me] = r2n;
         }
+        // plane s - 3 is final: its black node is node er of the pair
+        const int k = s - 3;
+        if (k >= K0 && k < K1 && (ok & 3)) {
+            T *d = dst + (size_t)k * nn;
+            if ((ok & 3) == 3) {
+                pair_t o;
+                o.x = er ? r2a : b2n;
+                o.y = er ? b2n : r2a;
+                *reinterpret_cast<pair_t *>(d) = o;
+            } else {                     // one node of the pair is on the far face
+                d[ok & 2 ? 1 : 0] = (er != 0) == ((ok & 2) != 0) ? b2n : r2a;
+            }
+        }
+        bzm = bzc;
+        bzc = bn;
+        ra = rn;
+        r1b = r1a;
+        r1a = r1n;
+        b1b = b1a;
+        b1a = b1n;
+        r2b = r2a;
+        r2a = r2n;
+        hr2 = hr1;
+        hr1 = hr0;
+        hb3 = hb2;
+        hb2 = hb1;
+        hb1 = hb0;
+        er ^= 1;
         __syncthreads();
     };
-    int s = 1;
+    int s = s0;
     for (; s + 1 <= smax; s += 2) {   // whole pairs of steps: no branch inside the loop
         step(s, vA, pA, false);
         step(s + 1, vB, pB, true);
@@ -275,35 +297,40 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
 }  // namespace
 
 template <typename T, int TX, int TY, int NT>
-static void skew_launch(int n, double h, const T *f, const T *uin, T *uout, hipStream_t s, int nb, const T *uc)
+static void skew_launch(int n, double h, const T *f, const T *uin, T *uout, hipStream_t s, int nb, const T *uc, int kchunk)
 {
     const int m = n - 2;
-    const dim3 grid((m + TX - 1) / TX, (m + TY - 1) / TY, nb);
+    // chunk c holds planes max(1, c kchunk) .. (c + 1) kchunk - 1 of 1 .. n - 2
+    const int kc = kchunk <= 0 || kchunk >= n - 1 ? n - 1 : (kchunk < 4 ? 4 : kchunk + (kchunk & 1));
+    const int nchunk = (n - 1 + kc - 1) / kc;
+    const dim3 grid((m + TX - 1) / TX, (m + TY - 1) / TY, nb * nchunk);
     const int nc = (n + 1) / 2;
     if (uc && uin)
         hipLaunchKernelGGL((rbgs2_skew_k<T, TX, TY, NT, false, true>), grid, dim3(NT), 0, s, uin, uout, f, n, T(h * h),
-                           uc, nc);
+                           uc, nc, kc, nchunk);
     else if (uc)
         hipLaunchKernelGGL((rbgs2_skew_k<T, TX, TY, NT, true, true>), grid, dim3(NT), 0, s, uin, uout, f, n, T(h * h),
-                           uc, nc);
+                           uc, nc, kc, nchunk);
     else if (uin)
         hipLaunchKernelGGL((rbgs2_skew_k<T, TX, TY, NT, false, false>), grid, dim3(NT), 0, s, uin, uout, f, n, T(h * h),
-                           uc, nc);
+                           uc, nc, kc, nchunk);
     else
         hipLaunchKernelGGL((rbgs2_skew_k<T, TX, TY, NT, true, false>), grid, dim3(NT), 0, s, uin, uout, f, n, T(h * h),
-                           uc, nc);
+                           uc, nc, kc, nchunk);
 }
 
 template <typename T>
-void launch_rbgs2_skew(int n, double h, const T *f, const T *uin, T *uout, hipStream_t s, int nb, const T *uc, int tile)
+void launch_rbgs2_skew(int n, double h, const T *f, const T *uin, T *uout, hipStream_t s, int nb, const T *uc, int tile,
+                       int kchunk)
 {
-    if (tile == 1) skew_launch<T, 32, 8, 320>(n, h, f, uin, uout, s, nb, uc);   // 55 KB of LDS: two workgroups per CU
-    else skew_launch<T, 64, 16, 1024>(n, h, f, uin, uout, s, nb, uc);          // 146 KB: one per CU
+    if (tile == 1) skew_launch<T, 32, 8, 320>(n, h, f, uin, uout, s, nb, uc, kchunk);
+    else if (tile == 2) skew_launch<T, 32, 16, 512>(n, h, f, uin, uout, s, nb, uc, kchunk);
+    else skew_launch<T, 64, 16, 896>(n, h, f, uin, uout, s, nb, uc, kchunk);
 }
 
 template void launch_rbgs2_skew<double>(int, double, const double *, const double *, double *, hipStream_t, int,
-                                        const double *, int);
+                                        const double *, int, int);
 template void launch_rbgs2_skew<float>(int, double, const float *, const float *, float *, hipStream_t, int,
-                                       const float *, int);
+                                       const float *, int, int);
 
 }  // namespace qm
