@@ -74,6 +74,8 @@ struct qumond_ctx {
     unsigned long long *d_count = nullptr;
     unsigned long long *h_count = nullptr;  // pinned
     unsigned long long *dep_scratch = nullptr;
+    void *sort_ws = nullptr;             // workspace of the sorted deposit, grown to the largest particle count seen
+    size_t sort_bytes = 0;
     // second solve chain (QUMOND potential) for qumond_solve, created on first use
     bool chain2 = false;
     hipStream_t s2 = nullptr;
@@ -208,6 +210,7 @@ qumond_status qumond_destroy(qumond_ctx *ctx)
     ctx->mix.mg.release();
     ctx->mix2.mg.release();
     for (void *p : ctx->owned) (void)hipFree(p);
+    if (ctx->sort_ws) (void)hipFree(ctx->sort_ws);
     if (ctx->h_count) (void)hipHostFree(ctx->h_count);
     delete ctx;
     return QUMOND_OK;
@@ -321,6 +324,43 @@ int64_t qumond_device_bytes(const qumond_ctx *ctx)
                : 0;
 }
 
+// Whether this deposit takes the sorted form: it is the faster one, its
+// workspace is there or can be had (without it the window form runs as it always
+// did), and the stream is not being captured (a captured graph would keep the
+// address of a workspace that a later, larger deposit replaces).
+static bool sort_workspace(qumond_ctx *ctx, int64_t np)
+{
+    if (!qm::deposit_sorts(ctx->n, ctx->cfg.nbox, np)) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (cap != hipStreamCaptureStatusNone) return false;
+    const size_t need = qm::deposit_sort_bytes(ctx->n, ctx->cfg.nbox, np);
+    if (need <= ctx->sort_bytes) return true;
+    // the allocation belongs to no capture: it must not end one that another stream has begun
+    struct Relaxed {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+        ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    } relaxed;
+    if (ctx->sort_ws) {
+        if (hipStreamSynchronize(ctx->s) != hipSuccess) return false;   // the last deposit may still use it
+        (void)hipFree(ctx->sort_ws);
+        ctx->bytes -= (int64_t)ctx->sort_bytes;
+        ctx->sort_ws = nullptr;
+        ctx->sort_bytes = 0;
+    }
+    if (hipMalloc(&ctx->sort_ws, need) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->sort_ws = nullptr;
+        return false;
+    }
+    ctx->sort_bytes = need;
+    ctx->bytes += (int64_t)need;
+    return true;
+}
 
 qumond_status qumond_deposit(qumond_ctx *ctx, const double *x, const double *y, const double *z, const double *m,
                              int64_t np, double total_mass, int64_t *n_outside)
@@ -355,7 +395,8 @@ qumond_status qumond_deposit(qumond_ctx *ctx, const double *x, const double *y, 
         qm::launch_fill<long long>(B.q, ctx->N, 0LL, ctx->s);
     }
     qm::launch_fill<unsigned long long>(ctx->d_count, 1, 0ULL, ctx->s);
-    qm::launch_deposit(a, x, y, z, m, np, ctx->d_count, ctx->s);
+    if (sort_workspace(ctx, np)) qm::launch_deposit_sorted(a, x, y, z, m, np, ctx->d_count, ctx->sort_ws, ctx->s);
+    else qm::launch_deposit(a, x, y, z, m, np, ctx->d_count, ctx->s);
     const double four_pi_G = 4.0 * M_PI * ctx->cfg.G;
     for (int b = 0; b < a.nbox; ++b)
         qm::launch_rhs_from_q(ctx->n, ctx->box[b].h, four_pi_G, shift, ctx->box[b].q, ctx->box[b].f, ctx->s);

@@ -260,6 +260,12 @@ void launch_bc_from_coarse(int n, const double *uc, double *u0, double *u1, hipS
 size_t deposit_scratch_bytes(int nbox);
 void launch_deposit(const DepositArgs &a, const double *x, const double *y, const double *z, const double *m,
                     int64_t np, unsigned long long *inside_count, hipStream_t s);
+// The same integers by way of a sort of the particles by cell tile; deposit_sorts
+// says where it is the faster, ws holds deposit_sort_bytes(n, nbox, np) bytes.
+bool deposit_sorts(int n, int nbox, int64_t np);
+size_t deposit_sort_bytes(int n, int nbox, int64_t np);
+void launch_deposit_sorted(const DepositArgs &a, const double *x, const double *y, const double *z, const double *m,
+                           int64_t np, unsigned long long *inside_count, void *ws, hipStream_t s);
 void launch_rhs_from_q(int n, double h, double four_pi_G, int shift, const long long *q, double *f, hipStream_t s);
 void launch_gather(const GatherArgs &a, const double *x, const double *y, const double *z, int64_t np, double *ax,
                    double *ay, double *az, uint8_t *box_used, hipStream_t s);

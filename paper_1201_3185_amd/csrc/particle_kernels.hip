@@ -128,6 +128,343 @@ void launch_deposit(const DepositArgs &a, const double *x, const double *y, cons
     hipLaunchKernelGGL(deposit_reduce_k, dim3((kWin + 255) / 256, a.nbox), dim3(256), 0, s, a, (int)blocks);
 }
 
+// ------------------------------------------------------------ sorted deposit
+//
+// Where a disk is wider than the window above, most corners of large particle
+// sets went to global 64-bit atomics, whose device-wide rate (about 17 G/s)
+// bound the deposit.  The sorted form first orders the particles by the 32x32x8
+// cell tile of the finest box that holds them, so that a workgroup takes
+// particles of one tile and adds all their corners, on that box and on every
+// coarser one, in LDS: in a box twice as large the tile is a block of half the
+// cells per axis, and the blocks of all boxes together hold at most 11 888 nodes
+// (95 KB).  Only the nodes a workgroup has touched go to the grids with global
+// atomics, once per kSegment particles or more.  The weights, their rounding
+// and the integer sums are those of the window form, so the grids are the same
+// integers whatever the order.
+//   1. tile_count_k: LDS histogram over the tiles per workgroup, kept per
+//      workgroup and added to the totals;
+//   2. tile_scan_k: start of every tile, list of segments;
+//   3. tile_scatter_k: particles as 32-byte records in tile order;
+//   4. tile_deposit_k: segments from a queue.
+// It is bound by its passes over the particles (24 + 32 + 32 + 32 B each) and by
+// the eight rounded weights per particle and box.  Deposit calls (with clearing
+// q and forming the right-hand side), window form -> sorted: 1e7 particles on
+// 513^3 3363 -> 1075 us, 2e7 in eleven 257^3 boxes 21.5 -> 3.0 ms, 3e6 in three
+// 257^3 boxes 1698 -> 422 us, 1e6 in four 129^3 boxes 351 -> 144 us.
+
+constexpr int kTileXY = 32, kTileZ = 8;
+constexpr int kSortBlocks = 256;
+constexpr int kSegment = 4096;
+constexpr int kWinAll = 11904;       // nodes of one tile's blocks on all boxes, at most
+constexpr int kWinOne = 33 * 33 * 9;
+
+struct TileGrid {
+    int cxy, cz;      // cells per tile
+    int sxy, sz;      // their logarithms
+    int txy, tz;      // tiles per axis
+    int per_box, nbin;
+};
+
+static TileGrid tile_grid(int n, int nbox)
+{
+    TileGrid t;
+    const int m = n - 1;             // a power of two
+    t.cxy = m < kTileXY ? m : kTileXY;
+    t.cz = m < kTileZ ? m : kTileZ;
+    t.sxy = __builtin_ctz((unsigned)t.cxy);
+    t.sz = __builtin_ctz((unsigned)t.cz);
+    t.txy = m / t.cxy;
+    t.tz = m / t.cz;
+    t.per_box = t.txy * t.txy * t.tz;
+    t.nbin = t.per_box * nbox;
+    return t;
+}
+
+// Tile of the finest box that holds the particle (the arithmetic of cic_cell), -1 outside all.
+__device__ __forceinline__ int tile_of(const DepositArgs &A, const TileGrid &T, double px, double py, double pz, bool &in0)
+{
+#pragma clang fp contract(off)
+    const double top = (double)(A.n - 1);
+    int bin = -1;
+    in0 = false;
+    for (int b = A.nbox - 1; b >= 0; --b) {
+        const BoxGeom &g = A.box[b];
+        const double ux = (px - g.xmin) * g.inv_h, uy = (py - g.xmin) * g.inv_h, uz = (pz - g.xmin) * g.inv_h;
+        const bool in = ux >= 0.0 && ux < top && uy >= 0.0 && uy < top && uz >= 0.0 && uz < top;
+        if (b == 0) in0 = in;
+        if (in && bin < 0)
+            bin = b * T.per_box + (((int)uz >> T.sz) * T.txy + ((int)uy >> T.sxy)) * T.txy + ((int)ux >> T.sxy);
+    }
+    return bin;
+}
+
+template <int MAXBIN>
+__global__ void __launch_bounds__(1024)
+tile_count_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const double *__restrict__ y,
+             const double *__restrict__ z, int np, int per_block, unsigned *__restrict__ hist, unsigned *__restrict__ total,
+             unsigned long long *__restrict__ inside_count)
+{
+    __shared__ unsigned H[MAXBIN];
+    __shared__ unsigned cnt_sh;
+    for (int e = threadIdx.x; e < T.nbin; e += 1024) H[e] = 0;
+    if (threadIdx.x == 0) cnt_sh = 0;
+    __syncthreads();
+    const int p0 = blockIdx.x * per_block, p1 = min(np, p0 + per_block);
+    unsigned in_n = 0;
+    for (int p = p0 + threadIdx.x; p < p1; p += 1024) {
+        bool in0;
+        const int bin = tile_of(A, T, x[p], y[p], z[p], in0);
+        in_n += in0;
+        if (bin >= 0) atomicAdd(&H[bin], 1u);
+    }
+    if (in_n) atomicAdd(&cnt_sh, in_n);
+    __syncthreads();
+    unsigned *row = hist + (size_t)blockIdx.x * T.nbin;
+    for (int e = threadIdx.x; e < T.nbin; e += 1024) {
+        const unsigned h = H[e];
+        row[e] = h;
+        if (h) atomicAdd(total + e, h);
+    }
+    if (threadIdx.x == 0 && cnt_sh) atomicAdd(inside_count, (unsigned long long)cnt_sh);
+}
+
+// One workgroup: start[bin] = particles before the bin, next[bin] the same (the
+// scatter's cursor); seg[] = {bin, first, end} of every segment of at most
+// seg_len particles; queue[0] = number of segments, queue[1] = 0.
+template <int MAXBIN>
+__global__ void __launch_bounds__(1024)
+tile_scan_k(int nbin, int seg_len, const unsigned *__restrict__ total, unsigned *__restrict__ next, int4 *__restrict__ seg,
+            unsigned *__restrict__ queue)
+{
+    constexpr int PER = MAXBIN / 1024;               // bins per thread, in order
+    __shared__ unsigned B[MAXBIN + 1024];            // one word of padding per thread's bins
+    __shared__ unsigned sp[1024], ss[1024];
+    for (int e = threadIdx.x; e < MAXBIN; e += 1024) B[e + e / PER] = e < nbin ? total[e] : 0u;
+    __syncthreads();
+    unsigned *mine = B + threadIdx.x * (PER + 1);
+    unsigned np = 0, ns = 0;
+    for (int k = 0; k < PER; ++k) {
+        np += mine[k];
+        ns += (mine[k] + seg_len - 1) / seg_len;
+    }
+    sp[threadIdx.x] = np;
+    ss[threadIdx.x] = ns;
+    __syncthreads();
+    for (int d = 1; d < 1024; d <<= 1) {
+        const unsigned a = (int)threadIdx.x >= d ? sp[threadIdx.x - d] : 0u;
+        const unsigned c = (int)threadIdx.x >= d ? ss[threadIdx.x - d] : 0u;
+        __syncthreads();
+        sp[threadIdx.x] += a;
+        ss[threadIdx.x] += c;
+        __syncthreads();
+    }
+    unsigned p = sp[threadIdx.x] - np, s = ss[threadIdx.x] - ns;
+    for (int k = 0; k < PER; ++k) {
+        const unsigned c = mine[k];
+        mine[k] = p;
+        for (unsigned o = 0; o < c; o += seg_len)
+            seg[s++] = make_int4(threadIdx.x * PER + k, (int)(p + o), (int)(p + min(c, o + seg_len)), 0);
+        p += c;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < nbin; e += 1024) next[e] = B[e + e / PER];
+    if (threadIdx.x == 1023) {
+        queue[0] = ss[1023];
+        queue[1] = 0;
+    }
+}
+
+template <int MAXBIN>
+__global__ void __launch_bounds__(1024)
+tile_scatter_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const double *__restrict__ y,
+               const double *__restrict__ z, const double *__restrict__ m, int np, int per_block,
+               const unsigned *__restrict__ hist, unsigned *__restrict__ next, double4 *__restrict__ rec)
+{
+    __shared__ unsigned H[MAXBIN];
+    const unsigned *row = hist + (size_t)blockIdx.x * T.nbin;
+    for (int e = threadIdx.x; e < T.nbin; e += 1024) {   // this workgroup's place in every tile it has particles of
+        const unsigned h = row[e];
+        H[e] = h ? atomicAdd(next + e, h) : 0u;
+    }
+    __syncthreads();
+    const int p0 = blockIdx.x * per_block, p1 = min(np, p0 + per_block);
+    for (int p = p0 + threadIdx.x; p < p1; p += 1024) {
+        bool in0;
+        const double px = x[p], py = y[p], pz = z[p];
+        const int bin = tile_of(A, T, px, py, pz, in0);
+        if (bin < 0) continue;
+        rec[atomicAdd(&H[bin], 1u)] = double4{px, py, pz, m[p]};
+    }
+}
+
+// Segments from the queue.  A thread adds the corners of its particles
+// that share a cell in registers before they go to LDS (in the coarse boxes of a deep
+// nesting a whole tile is a cell or two).
+template <int WIN>
+__global__ void __launch_bounds__(1024)
+tile_deposit_k(DepositArgs A, TileGrid T, const double4 *__restrict__ rec, const int4 *__restrict__ seg,
+               unsigned *__restrict__ queue)
+{
+#pragma clang fp contract(off)
+    __shared__ unsigned long long W[WIN];
+    __shared__ int4 sg;
+    __shared__ int more;
+    const unsigned nseg = queue[0];
+    for (;;) {
+        if (threadIdx.x == 0) {
+            const unsigned s = atomicAdd(queue + 1, 1u);
+            more = s < nseg;
+            if (more) sg = seg[s];
+        }
+        __syncthreads();
+        if (!more) return;           // the queue only grows: every workgroup gets here
+        const int bin = sg.x, first = sg.y, end = sg.z;
+        const int bf = bin / T.per_box;
+        int t = bin - bf * T.per_box;
+        const int tx = t % T.txy;
+        t /= T.txy;
+        const int ty = t % T.txy, tz = t / T.txy;
+        // the tile's cells on box bf, and on the coarser boxes: a box's middle half, (n - 1) / 4
+        // cells from its face, is the next one
+        const int off = (A.n - 1) / 4;
+        const int flo[3] = {tx * T.cxy, ty * T.cxy, tz * T.cz};
+        const int fhi[3] = {flo[0] + T.cxy - 1, flo[1] + T.cxy - 1, flo[2] + T.cz - 1};
+        for (int e = threadIdx.x; e < WIN; e += 1024) W[e] = 0ULL;
+        __syncthreads();
+        for (int i0 = first + (int)threadIdx.x; i0 < end; i0 += 4096) {
+            double4 r[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r[k] = rec[min(i0 + 1024 * k, end - 1)];
+            int lo[3] = {flo[0], flo[1], flo[2]}, hi[3] = {fhi[0], fhi[1], fhi[2]};
+            int base = 0;
+            for (int b = bf; b >= 0; --b) {
+                const int nx = hi[0] - lo[0] + 2, ny = hi[1] - lo[1] + 2, nz = hi[2] - lo[2] + 2;
+                const BoxGeom g = A.box[b];
+                unsigned long long sum[8];
+                int at = -1;         // LDS place of the cell whose corners are in sum
+                auto flush = [&]() {
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+                        atomicAdd(&W[at + (c & 1) + nx * (((c >> 1) & 1) + ny * (c >> 2))], sum[c]);
+                };
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    int ic[3];
+                    double w[3][2];
+                    if (i0 + 1024 * k >= end || !cic_cell(g, A.n, r[k].x, r[k].y, r[k].z, ic, w)) continue;
+                    const int lx = ic[0] - lo[0], ly = ic[1] - lo[1], lz = ic[2] - lo[2];
+                    const bool inwin = lx >= 0 && lx < nx - 1 && ly >= 0 && ly < ny - 1 && lz >= 0 && lz < nz - 1;
+                    const int here = base + lx + nx * (ly + ny * lz);
+                    if (inwin && here != at) {
+                        if (at >= 0) flush();
+                        at = here;
+#pragma unroll
+                        for (int c = 0; c < 8; ++c) sum[c] = 0ULL;
+                    }
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        const double wt = (w[0][c & 1] * w[1][(c >> 1) & 1]) * w[2][c >> 2];
+                        const unsigned long long qv = (unsigned long long)__double2ll_rn((wt * r[k].w) * A.scale);
+                        if (inwin) sum[c] += qv;
+                        // a rounding of the two boxes' cell coordinates that differs at a tile's face
+                        else atomicAdd(A.q[b] + id3(A.n, ic[0] + (c & 1), ic[1] + ((c >> 1) & 1), ic[2] + (c >> 2)), qv);
+                    }
+                }
+                if (at >= 0) flush();
+                base += nx * ny * nz;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    lo[d] = off + (lo[d] >> 1);
+                    hi[d] = off + (hi[d] >> 1);
+                }
+            }
+        }
+        __syncthreads();
+        int lo[3] = {flo[0], flo[1], flo[2]}, hi[3] = {fhi[0], fhi[1], fhi[2]};
+        int base = 0;
+        for (int b = bf; b >= 0; --b) {
+            const int nx = hi[0] - lo[0] + 2, ny = hi[1] - lo[1] + 2, nz = hi[2] - lo[2] + 2;
+            for (int e = threadIdx.x; e < nx * ny * nz; e += 1024) {
+                const unsigned long long v = W[base + e];
+                if (v) atomicAdd(A.q[b] + id3(A.n, lo[0] + e % nx, lo[1] + e / nx % ny, lo[2] + e / nx / ny), v);
+            }
+            base += nx * ny * nz;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                lo[d] = off + (lo[d] >> 1);
+                hi[d] = off + (hi[d] >> 1);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The window form stays where its window holds most of the disk or the passes
+// of the sort cost more than the atomics they save: at 65^3 and below (1e7
+// particles: 163 us against 357, six nested boxes 823 against 912) and for few
+// particles (129^3, 1e5: 48 against 59, 3e5: 68 against 63 us; 257^3, 1e5: 104
+// against 102), and where the tiles outgrow an LDS histogram (1025^3, or 513^3
+// in more than two boxes).
+bool deposit_sorts(int n, int nbox, int64_t np)
+{
+    return n >= 129 && np >= 250000 && tile_grid(n, nbox).nbin <= 32768;
+}
+
+constexpr int64_t kSortSlice = 1 << 26;   // particles sorted at a time
+
+static size_t round256(size_t b) { return (b + 255) / 256 * 256; }
+
+size_t deposit_sort_bytes(int n, int nbox, int64_t np)
+{
+    const TileGrid t = tile_grid(n, nbox);
+    const int64_t m = np < kSortSlice ? np : kSortSlice;
+    return round256((size_t)m * sizeof(double4)) + round256((size_t)kSortBlocks * t.nbin * 4) + 2 * round256((size_t)t.nbin * 4) +
+           round256(((size_t)m / kSegment + t.nbin + 1) * sizeof(int4)) + 256;
+}
+
+template <int MAXBIN>
+static void deposit_sorted(const DepositArgs &a, const TileGrid &t, const double *x, const double *y, const double *z,
+                           const double *m, int np, unsigned long long *inside_count, void *ws, hipStream_t s)
+{
+    char *w = (char *)ws;
+    double4 *rec = (double4 *)w;
+    w += round256((size_t)np * sizeof(double4));
+    unsigned *hist = (unsigned *)w;
+    w += round256((size_t)kSortBlocks * t.nbin * 4);
+    unsigned *total = (unsigned *)w;
+    w += round256((size_t)t.nbin * 4);
+    unsigned *next = (unsigned *)w;
+    w += round256((size_t)t.nbin * 4);
+    int4 *seg = (int4 *)w;
+    w += round256(((size_t)np / kSegment + t.nbin + 1) * sizeof(int4));
+    unsigned *queue = (unsigned *)w;
+    const int per_block = (np + kSortBlocks - 1) / kSortBlocks;
+    // long enough that touched nodes are flushed rarely, short enough for some 1000 segments
+    int seg_len = np / 1024;
+    seg_len = (seg_len < kSegment ? kSegment : seg_len + kSegment - 1) / kSegment * kSegment;
+    launch_fill<unsigned long long>((unsigned long long *)total, ((size_t)t.nbin + 1) / 2, 0ULL, s);   // room for 256 bytes' multiple
+    hipLaunchKernelGGL((tile_count_k<MAXBIN>), dim3(kSortBlocks), dim3(1024), 0, s, a, t, x, y, z, np, per_block, hist,
+                       total, inside_count);
+    hipLaunchKernelGGL((tile_scan_k<MAXBIN>), dim3(1), dim3(1024), 0, s, t.nbin, seg_len, total, next, seg, queue);
+    hipLaunchKernelGGL((tile_scatter_k<MAXBIN>), dim3(kSortBlocks), dim3(1024), 0, s, a, t, x, y, z, m, np, per_block,
+                       hist, next, rec);
+    if (a.nbox == 1)
+        hipLaunchKernelGGL((tile_deposit_k<kWinOne>), dim3(512), dim3(1024), 0, s, a, t, rec, seg, queue);
+    else
+        hipLaunchKernelGGL((tile_deposit_k<kWinAll>), dim3(256), dim3(1024), 0, s, a, t, rec, seg, queue);
+}
+
+void launch_deposit_sorted(const DepositArgs &a, const double *x, const double *y, const double *z, const double *m,
+                           int64_t np, unsigned long long *inside_count, void *ws, hipStream_t s)
+{
+    const TileGrid t = tile_grid(a.n, a.nbox);
+    for (int64_t p = 0; p < np; p += kSortSlice) {
+        const int c = (int)(np - p < kSortSlice ? np - p : kSortSlice);
+        if (t.nbin <= 8192) deposit_sorted<8192>(a, t, x + p, y + p, z + p, m + p, c, inside_count, ws, s);
+        else deposit_sorted<32768>(a, t, x + p, y + p, z + p, m + p, c, inside_count, ws, s);
+    }
+}
+
 // Batched single-box deposit: workgroup (g, p) takes a contiguous share of
 // problem p's particles, with the same LDS window, scratch slabs and integer
 // adds as above; problem p's grid starts at q + p n^3.
