@@ -14,12 +14,15 @@
 // eight consecutive K indices 8 (l / 16) .. 8 (l / 16) + 7, which are eight
 // consecutive channels of one tap: one 16-byte load.  The 4 accumulators of
 // lane l are column l % 16, rows 4 (l / 16) + r.
+#include <type_traits>
+
 #include "common.h"
 #include "unet.h"
 
 namespace qm {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 __device__ __forceinline__ void decode3(int v, int n, int &i, int &j, int &k)
@@ -127,106 +130,251 @@ conv3d_fwd_k(Tensor x, int cin, const __bf16 *__restrict__ wt, int kpad, const f
 
 // Stride-1 convolution with the input tile in LDS: a workgroup computes a
 // 16 x 4 x 4 block of output voxels (each wave 4 x-rows of 16 voxels, one
-// MFMA row block each) for all cout = 16 NB channels.  The input channels are
-// taken in chunks of up to 32; for each chunk the 18 x 6 x 6 input voxels
-// (block plus a one-voxel ring) are staged in LDS once and every one of the
-// 27 taps reads its activation fragments from there.  Within a chunk of cc
-// channels the K-steps of 32 cover 32 / cc taps at a time (cc = 8, 16 or 32),
+// MFMA column block each) for 16 NB output channels (blockIdx.y picks them).  The
+// input channels are taken in chunks of 32 and a rest of 16 or 8; for each chunk
+// the 18 x 6 x 6 input voxels (block plus a one-voxel ring) are staged in LDS
+// once and every one of the 27 taps reads its activation fragments from there.
+// Within a chunk of cc channels the K-steps of 32 cover 32 / cc taps at a time,
 // in the same (tap, channel) order as conv3d_fwd_k.
+//
+// A workgroup takes a run of tiles.  What bounds it is latency, then the LDS
+// reads (one per MFMA at 16 output channels): all loads of a chunk are in flight
+// at once, during the MFMAs of the chunk or tile before (a loop of load and
+// store had waited for each of its ten loads in turn); weights come a group of
+// taps ahead, or stay in registers for the run (16 and 8 input channels); with 32
+// channels an input row is read once for the up to three dy that meet it; and
+// output channels are the rows of the product, so a lane stores four of them at
+// once.  Before -> now, same bits: 48 -> 16 channels at 129^3 451 -> 230 us, 16 ->
+// 16 180 -> 87, 8 -> 16 104 -> 49, 96 -> 32 at 65^3 164 -> 134, 64 -> 64 at 17^3 55 -> 21.
 constexpr int kTileX = 16, kTileY = 4, kTileZ = 4;
 constexpr int kInX = kTileX + 2, kInY = kTileY + 2, kInZ = kTileZ + 2, kInV = kInX * kInY * kInZ;
-constexpr int kChunk = 32, kPitch = kChunk + 8;   // bf16 per staged voxel (padded against bank conflicts)
 
-template <int NB>
-__global__ void __launch_bounds__(256)
+template <int NB, int C0>
+__global__ void __launch_bounds__(256, 3)
 conv3d_fwd_lds_k(Tensor x, int cin, const __bf16 *__restrict__ wt, int kpad, const float *__restrict__ bias, Tensor y,
-                 int relu, int tx, int ty)
+                 int relu, int tx, int ty, int tiles, int per)
 {
     constexpr int RB = 4;
-    __shared__ __bf16 tile[kInV * kPitch];
+    constexpr int Q = C0 / 8, VS = 256 / Q, NL = (kInV + VS - 1) / VS;   // NL 16-byte loads per thread and chunk
+    constexpr int kPitch = C0 == 8 ? 8 : C0 + 8;   // bf16 per staged voxel (padded against bank conflicts)
+    __shared__ __attribute__((aligned(16))) __bf16 tile[kInV * kPitch];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, r16 = lane & 15;
     const int n = y.n;   // = x.n (stride 1)
-    int bid = blockIdx.x;
-    const int bx = bid % tx;
-    bid /= tx;
-    const int by = bid % ty;
-    const int bz = bid / ty;
-    const int X0 = bx * kTileX, Y0 = by * kTileY, Z0 = bz * kTileZ;
-    const size_t xcs = (size_t)x.cs;
-    f32x4 acc[RB][NB];
+    const int co0 = blockIdx.y * 16 * NB;
+    wt += (size_t)co0 * kpad;
+    int t = (int)xcd_tile(blockIdx.x, gridDim.x) * per;      // this workgroup's run of tiles
+    const int tend = min(tiles, t + per);
+    if (t >= tend) return;
+
+    // Staging: in round r this thread takes 8 channels (q) of voxel v0 + VS r;
+    // from clamped addresses, zeroed where it is stored outside the grid.
+    const int q = threadIdx.x % Q, v0 = threadIdx.x / Q;
+    unsigned okp = 0;
+    auto origin = [&](int tt, int &X0, int &Y0, int &Z0) {
+        X0 = tt % tx * kTileX;
+        Y0 = tt / tx % ty * kTileY;
+        Z0 = tt / tx / ty * kTileZ;
+    };
+    bf16x8 pre[NL];
+    auto fetch = [&](int tt, int cb) {
+        int X0, Y0, Z0;
+        origin(tt, X0, Y0, Z0);
+        // a rest of 16 or 8 channels: the other q load it again, unused
+        const __bf16 *src = x.p + min(cb + 8 * q, cin - 8);
+        okp = 0;
+        int vb = v0;
+        asm volatile("" : "+v"(vb));     // decoded anew for every tile: kept across them the decodings would spill
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[rb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // this lane's rows: wave w, row block rb -> output row (y, z) = (rb, w) of the block, x = r16
-    for (int cb = 0; cb < cin; cb += kChunk) {
-        const int cc = min(kChunk, cin - cb);     // 8, 16 or 32 (cin is a multiple of 8; chunks of 32 then the rest)
-        const int g8 = cc / 8;
-        __syncthreads();
-        for (int t = threadIdx.x; t < kInV * g8; t += 256) {
-            const int v = t / g8, q = t - v * g8;
-            const int a = v % kInX, b = (v / kInX) % kInY, c = v / (kInX * kInY);
-            const int i = X0 - 1 + a, j = Y0 - 1 + b, k = Z0 - 1 + c;
-            bf16x8 val = {};
-            if (i >= 0 && i < n && j >= 0 && j < n && k >= 0 && k < n)
-                val = *reinterpret_cast<const bf16x8 *>(x.p + (size_t)(i + n * (j + n * k)) * xcs + cb + 8 * q);
-            *reinterpret_cast<bf16x8 *>(tile + v * kPitch + 8 * q) = val;
+        for (int r = 0; r < NL; ++r) {
+            const int v = vb + VS * r;
+            const int i = X0 - 1 + v % kInX, j = Y0 - 1 + v / kInX % kInY, k = Z0 - 1 + v / (kInX * kInY);
+            const bool in = v < kInV && i >= 0 && i < n && j >= 0 && j < n && k >= 0 && k < n;
+            pre[r] = *reinterpret_cast<const bf16x8 *>(src + (size_t)(in ? i + n * (j + n * k) : 0) * x.cs);
+            okp |= (unsigned)in << r;
         }
-        __syncthreads();
-        const int steps = (27 * cc + 31) / 32;
-        // fragments of K-step st (activations from the tile, weights from global)
-        auto frags = [&](int st, bf16x8 *a, bf16x8 *w) {
-            const int kl = 32 * st + 8 * g;        // local K index of this lane's fragment
-            const int tap = kl / cc, cl = kl - tap * cc;
-            const bool live = tap < 27;
-            const int dx = tap % 3, dy = (tap / 3) % 3, dz = tap / 9;   // offsets + 1
+    };
+    auto commit = [&]() {
+#pragma unroll
+        for (int r = 0; r < NL; ++r)
+            if (v0 + VS * r < kInV)
+                *reinterpret_cast<bf16x8 *>(tile + (v0 + VS * r) * kPitch + 8 * q) = (okp >> r) & 1 ? pre[r] : bf16x8{};
+    };
+    f32x4 acc[RB][NB];
+    // this lane's rows: wave w, row block rb -> output row (y, z) = (rb, w) of the block, x = r16
+    const __bf16 *mine = tile + (r16 + kInX * kInY * wave) * kPitch;
+    const __bf16 *wrow = wt + (size_t)r16 * kpad;
+    auto frag = [&](const __bf16 *p) { return *reinterpret_cast<const bf16x8 *>(p); };
+    auto mac = [&](int rb, const bf16x8 &a, const bf16x8 *w) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            acc[rb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], a, acc[rb][b], 0, 0, 0);
+    };
+    // 32 channels, one tap per K-step: the three dx of an input row are read once
+    // per dz and serve the (up to three) dy that meet it
+    auto chunk32 = [&](int cb) {
+        const __bf16 *wp = wrow + cb + 8 * g;
+        auto weights = [&](int row, bf16x8 (*w)[NB]) {   // the three taps of row = dy + 3 dz
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) w[e][b] = frag(wp + (size_t)(b * 16) * kpad + (3 * row + e) * cin);
+        };
+        bf16x8 w[2][3][NB];
+        weights(0, w[0]);
+#pragma unroll 1
+        for (int dz = 0; dz < 3; ++dz) {
+            const __bf16 *p = mine + kInX * kInY * dz * kPitch + 8 * g;
+            bf16x8 a[RB + 2][3];
+#pragma unroll
+            for (int y = 0; y < RB; ++y)
+#pragma unroll
+                for (int e = 0; e < 3; ++e) a[y][e] = frag(p + (e + kInX * y) * kPitch);
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                weights(min(3 * dz + dy + 1, 8), w[(dy + 1) & 1]);
+                if (dy < 2)
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) a[RB + dy][e] = frag(p + (e + kInX * (RB + dy)) * kPitch);
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) mac(rb, a[rb + dy][e], w[dy & 1][e]);
+            }
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) w[0][e][b] = w[1][e][b];
+        }
+    };
+    // 16 or 8 channels: 2 or 4 taps per K-step, by the lane's quarter; the last
+    // step's taps beyond 26 count as zeros
+    auto chunk_small = [&](auto CC, int cb, auto &&weight) {
+        constexpr int cc = CC.value, TAPS = 32 / cc, STEPS = (27 * cc + 31) / 32;
+        const int sub = (8 * g) / cc, cl = (8 * g) % cc;        // this lane's tap of a step and its channels
+        bf16x8 w[3][NB];                                        // of this step and the next two
+        weight(0, w[0]);
+        weight(1, w[1]);
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const bool last = TAPS * (st + 1) > 27;
+            const bool live = !last || TAPS * st + sub < 27;
+            int to = 0;
+#pragma unroll
+            for (int u = 0; u < TAPS; ++u) {
+                const int tap = min(TAPS * st + u, 26);
+                const int o = (tap % 3 + kInX * (tap / 3 % 3 + kInY * (tap / 9))) * kPitch;
+                to = sub == u ? o : to;
+            }
+            if (st + 2 < STEPS) weight(st + 2, w[(st + 2) % 3]);
+            if (last && !live) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) w[st % 3][b] = bf16x8{};
+            }
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                const int v = (r16 + dx) + kInX * ((rb + dy) + kInY * (wave + dz));
-                a[rb] = live ? *reinterpret_cast<const bf16x8 *>(tile + v * kPitch + cl) : bf16x8{};
+                bf16x8 a = frag(mine + to + cl + kInX * rb * kPitch);
+                if (last && !live) a = bf16x8{};
+                mac(rb, a, w[st % 3]);
             }
-            const int kw = live ? tap * cin + cb + cl : 0;
+            __builtin_amdgcn_sched_barrier(0);   // keep the reads of later steps from piling up in registers
+        }
+    };
+    // weights of a small chunk from memory, each step's before its reads
+    auto from_memory = [&](auto CC, int cb) {
+        constexpr int cc = CC.value, TAPS = 32 / cc;
+        int first = (8 * g) / cc * cin + cb + (8 * g) % cc;
+        asm volatile("" : "+v"(first));      // addresses from here: kept across tiles they would spill
+        return [=](int st, bf16x8 *w) {
+            const int at = min(first + st * TAPS * cin, kpad - 8);   // the last step's dead taps stay in the row
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-                w[b] = live ? *reinterpret_cast<const bf16x8 *>(wt + (size_t)(b * 16 + r16) * kpad + kw) : bf16x8{};
+            for (int b = 0; b < NB; ++b) w[b] = *reinterpret_cast<const bf16x8 *>(wrow + b * 16 * kpad + at);
         };
-        bf16x8 a[RB], w[NB];
-        frags(0, a, w);
-        for (int st = 0; st < steps; ++st) {
-            bf16x8 an[RB], wn[NB];
-            if (st + 1 < steps) frags(st + 1, an, wn);   // in flight during this step's MFMAs
+    };
+    // ... of a layer of 16 or 8 input channels in registers, for the whole run of tiles
+    constexpr int KS = C0 == 32 ? 1 : (27 * C0 + 31) / 32;
+    constexpr bool KEEP = C0 < 32 && KS * NB <= 14;
+    bf16x8 kept[KEEP ? KS : 1][NB];
+    if constexpr (KEEP) {
+        auto get = from_memory(std::integral_constant<int, C0>{}, 0);
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
+        for (int st = 0; st < KS; ++st) get(st, kept[st]);
+    }
+    fetch(t, 0);
+    for (; t < tend; ++t) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    acc[rb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb], w[b], acc[rb][b], 0, 0, 0);
-            if (st + 1 < steps) {
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) a[rb] = an[rb];
+            for (int b = 0; b < NB; ++b) acc[rb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int cb = 0; cb < cin; cb += C0) {
+            __syncthreads();             // the fragments of the chunk before are read
+            commit();
+            __syncthreads();
+            if (cb + C0 < cin) fetch(t, cb + C0);
+            else if (t + 1 < tend) fetch(t + 1, 0);
+            if constexpr (C0 == 32) {
+                const int cc = min(C0, cin - cb);
+                const std::integral_constant<int, 16> c16;
+                if (cc == 32) chunk32(cb);
+                else chunk_small(c16, cb, from_memory(c16, cb));    // the rest of 48 channels
+            } else {
+                const std::integral_constant<int, C0> c0;
+                if constexpr (KEEP) {
+                    chunk_small(c0, cb, [&](int st, bf16x8 *w) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b) w[b] = wn[b];
+                        for (int b = 0; b < NB; ++b) w[b] = kept[st][b];
+                    });
+                } else {
+                    chunk_small(c0, cb, from_memory(c0, cb));
+                }
+            }
+        }
+        // lane: output voxel r16 of a row, channels 4 g .. 4 g + 3 of a block
+        int X0, Y0, Z0;
+        origin(t, X0, Y0, Z0);
+        const int i = X0 + r16, k = Z0 + wave;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int co = co0 + b * 16 + 4 * g;
+            float bb[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) bb[r] = bias ? bias[co + r] : 0.f;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const int j = Y0 + rb;
+                if (i >= n || j >= n || k >= n) continue;
+                bf16x4 o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float val = acc[rb][b][r] + bb[r];
+                    if (relu) val = val > 0.f ? val : 0.f;
+                    o[r] = (__bf16)val;
+                }
+                *reinterpret_cast<bf16x4 *>(y.p + (size_t)(i + n * (j + n * k)) * y.cs + co) = o;
             }
         }
     }
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int co = b * 16 + r16;
-        const float bb = bias ? bias[co] : 0.f;
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const int j = Y0 + rb, k = Z0 + wave;
-            if (j >= n || k >= n) continue;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = X0 + 4 * g + r;
-                if (i >= n) continue;
-                float val = acc[rb][b][r] + bb;
-                if (relu) val = val > 0.f ? val : 0.f;
-                y.p[(size_t)(i + n * (j + n * k)) * y.cs + co] = (__bf16)val;
-            }
-        }
-    }
+}
+
+template <int NB>
+static void conv_lds(Tensor x, int cin, const __bf16 *wt, int kpad, int cout, const float *bias, Tensor y, int relu,
+                     hipStream_t s)
+{
+    const int tx = (y.n + kTileX - 1) / kTileX, ty = (y.n + kTileY - 1) / kTileY, tz = (y.n + kTileZ - 1) / kTileZ;
+    const int tiles = tx * ty * tz, groups = cout / (16 * NB);
+    // as many workgroups as fit the CUs' LDS (51.8, 31.1 and 10.4 KB), each with a run of tiles whose loads it overlaps
+    const int fit = cin >= 32 ? 768 : (cin == 16 ? 1280 : 1536);
+    const int per = (tiles * groups + fit - 1) / fit;
+    const dim3 grid((unsigned)((tiles + per - 1) / per), (unsigned)groups);
+    if (cin >= 32)
+        hipLaunchKernelGGL((conv3d_fwd_lds_k<1, 32>), grid, dim3(256), 0, s, x, cin, wt, kpad, bias, y, relu, tx, ty,
+                           tiles, per);
+    else if (cin == 16)
+        hipLaunchKernelGGL((conv3d_fwd_lds_k<NB, 16>), grid, dim3(256), 0, s, x, cin, wt, kpad, bias, y, relu, tx, ty,
+                           tiles, per);
+    else
+        hipLaunchKernelGGL((conv3d_fwd_lds_k<NB, 8>), grid, dim3(256), 0, s, x, cin, wt, kpad, bias, y, relu, tx, ty,
+                           tiles, per);
 }
 
 template <int NB>
@@ -234,10 +382,17 @@ static void conv_fwd_nb(Tensor x, int cin, const __bf16 *wt, int kpad, const flo
                         int relu, hipStream_t s)
 {
     const int Nout = y.n * y.n * y.n;
-    if (stride == 1 && NB <= 4 && (cin % 32 == 0 || cin == 8 || cin == 16 || cin == 48)) {
-        const int tx = (y.n + kTileX - 1) / kTileX, ty = (y.n + kTileY - 1) / kTileY, tz = (y.n + kTileZ - 1) / kTileZ;
-        hipLaunchKernelGGL((conv3d_fwd_lds_k<NB <= 4 ? NB : 4>), dim3((unsigned)(tx * ty * tz)), dim3(256), 0, s, x,
-                           cin, wt, kpad, bias, y, relu, tx, ty);
+    // 96 and 128 output channels keep the order of conv3d_fwd_k, all channels of a tap before the next tap, which
+    // the tile kernel follows up to 32 input channels
+    if (stride == 1 && (cin == 8 || cin == 16 || cin == 32 || (NB <= 4 && (cin % 32 == 0 || cin == 48)))) {
+        const int blocks = ((y.n + kTileX - 1) / kTileX) * ((y.n + kTileY - 1) / kTileY) * ((y.n + kTileZ - 1) / kTileZ);
+        // One block of output channels per workgroup from 32 input channels up: two need 174 registers, two
+        // wavefronts per SIMD instead of three (96 -> 32 at 65^3: 153 us against 134).  With fewer input channels
+        // up to three blocks share a staged tile where that leaves two workgroups per CU.
+        const int want = 512;
+        if (NB % 3 == 0 && cin < 32 && blocks * (NB / 3) >= want) conv_lds<3>(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
+        else if (NB % 2 == 0 && cin < 32 && blocks * (NB / 2) >= want) conv_lds<2>(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
+        else conv_lds<1>(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
         return;
     }
     // RB row blocks per wave while the grid keeps at least ~1024 workgroups
