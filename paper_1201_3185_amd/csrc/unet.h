@@ -21,16 +21,22 @@ void launch_dilate(Tensor src, Tensor dst, int c, hipStream_t s);
 int wgrad_splits(int cout, int kpad, int nout);
 void launch_wgrad(Tensor x, int cin, Tensor dy, int cout, int kpad, int stride, float *partial, float *dw,
                   hipStream_t s);
-void launch_bgrad(Tensor dy, int c, float *partial, float *db, hipStream_t s);
-void launch_relu_bwd(Tensor g, Tensor y, int c, hipStream_t s);
-void launch_add(Tensor dst, Tensor src, int c, hipStream_t s);
+// g += add (add.p null: nothing) and 0 where the ReLU output y is 0, in place; db = its sums per channel
+void launch_pre_grad(Tensor g, Tensor add, Tensor y, int c, float *partial, float *db, hipStream_t s);
 void launch_upsample(Tensor src, Tensor dst, int c, hipStream_t s);
 void launch_upsample_adj(Tensor gf, Tensor gc, int c, hipStream_t s);
 void launch_head_fwd(Tensor x, int c, const float *w, const float *b, float *yh, hipStream_t s);
 void launch_head_bwd(const float *dyh, Tensor x, int c, const float *w, Tensor dx, float *partial, float *dwb,
                      hipStream_t s);
 void launch_mse(const float *yh, const float *tg, int n, float *dy, double *partial, double *loss, hipStream_t s);
-void launch_adam(float *w, float *m, float *v, const float *g, int count, float lr, int step, __bf16 *wb, hipStream_t s);
+// One parameter array of Adam: weights, moments, gradient and (or null) the BF16 copy.
+struct AdamArray {
+    float *w, *m, *v;
+    const float *g;
+    __bf16 *wb;
+    int count;
+};
+void launch_adam(const AdamArray *arrays, int n, int total, float lr, int step, hipStream_t s);
 void launch_to_bf16(const float *src, __bf16 *dst, int count, hipStream_t s);
 // channel 0 = (phin - base) inv_cn, channel 1 = S h2_cs
 void launch_prep_input(int n, const double *phin, const double *base, const double *S, double inv_cn, double h2_cs,

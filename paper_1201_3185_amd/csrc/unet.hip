@@ -38,7 +38,10 @@ struct qumond_unet {
     int n[4] = {0, 0, 0, 0};
     Conv L[11];
     // head (1x1x1, 16 -> 1)
-    float *hw = nullptr, *hgw = nullptr, *hm = nullptr, *hv = nullptr;   // 17 values: 16 weights + bias
+    float *hw = nullptr, *hgw = nullptr, *hm = nullptr, *hv = nullptr;   // 17 values: 16 weights + bias; behind
+                                                                         // hgw's the bias gradients of layer 10
+    qm::AdamArray *adam = nullptr;   // device table of all parameter arrays
+    int n_adam = 0, n_param = 0;
     // activations
     Tensor x0, a0, c0, s0, d0, a1, c1, s1, d1, a2, c2, s2, d2, a3, b3;
     // gradients
@@ -101,15 +104,18 @@ void conv_fwd(qumond_unet *u, int l, Tensor in, Tensor out)
     qm::launch_conv3d_fwd(in, c.cin, c.wb, c.kpad, c.cout, c.b, out, c.stride, 1, u->s);
 }
 
-// Backward through layer l whose input was `in` and ReLU output `out`: g is
-// the gradient of out (overwritten by the pre-activation gradient); gin (may
-// have p == nullptr) receives the gradient of the input.
-void conv_bwd(qumond_unet *u, int l, Tensor in, Tensor out, Tensor g, Tensor gin)
+const Tensor kNone{nullptr, 0, 0};
+
+// Backward through layer l whose input was `in` and ReLU output `out`: g (plus
+// skip, where that has a p) is the gradient of out, overwritten by the
+// pre-activation gradient (out.p null: it already is that, and its bias
+// gradient is formed); gin (may have p == nullptr) receives the gradient of the
+// input.
+void conv_bwd(qumond_unet *u, int l, Tensor in, Tensor out, Tensor g, Tensor gin, Tensor skip = kNone)
 {
     Conv &c = u->L[l];
-    qm::launch_relu_bwd(g, out, c.cout, u->s);
+    if (out.p) qm::launch_pre_grad(g, skip, out, c.cout, u->partial, c.gb, u->s);
     qm::launch_wgrad(in, c.cin, g, c.cout, c.kpad, c.stride, u->partial, c.gw, u->s);
-    qm::launch_bgrad(g, c.cout, u->partial, c.gb, u->s);
     if (!gin.p) return;
     qm::launch_dgrad_weights(c.wb, c.cin, c.cout, c.kpad, c.wd, c.kpad_d, u->s);
     if (c.stride == 2) {
@@ -144,12 +150,8 @@ void forward(qumond_unet *u)
 
 void backward(qumond_unet *u)
 {
-    Tensor none;
-    none.p = nullptr;
-    none.n = 0;
-    none.cs = 0;
     qm::launch_head_bwd(u->dyhat, u->d0, 16, u->hw, u->gd0, u->partial, u->hgw, u->s);
-    conv_bwd(u, 10, u->c0, u->d0, u->gd0, u->gc0);
+    conv_bwd(u, 10, u->c0, kNone, u->gd0, u->gc0);
     qm::launch_upsample_adj(slice(u->gc0, 0), u->gd1, 32, u->s);
     conv_bwd(u, 9, u->c1, u->d1, u->gd1, u->gc1);
     qm::launch_upsample_adj(slice(u->gc1, 0), u->gd2, 64, u->s);
@@ -157,26 +159,18 @@ void backward(qumond_unet *u)
     qm::launch_upsample_adj(slice(u->gc2, 0), u->gb3, 64, u->s);
     conv_bwd(u, 7, u->a3, u->b3, u->gb3, u->ga3);
     conv_bwd(u, 6, u->s2, u->a3, u->ga3, u->gs2);
-    qm::launch_add(u->gs2, slice(u->gc2, 64), 64, u->s);
-    conv_bwd(u, 5, u->a2, u->s2, u->gs2, u->ga2);
+    conv_bwd(u, 5, u->a2, u->s2, u->gs2, u->ga2, slice(u->gc2, 64));
     conv_bwd(u, 4, u->s1, u->a2, u->ga2, u->gs1);
-    qm::launch_add(u->gs1, slice(u->gc1, 64), 32, u->s);
-    conv_bwd(u, 3, u->a1, u->s1, u->gs1, u->ga1);
+    conv_bwd(u, 3, u->a1, u->s1, u->gs1, u->ga1, slice(u->gc1, 64));
     conv_bwd(u, 2, u->s0, u->a1, u->ga1, u->gs0);
-    qm::launch_add(u->gs0, slice(u->gc0, 32), 16, u->s);
-    conv_bwd(u, 1, u->a0, u->s0, u->gs0, u->ga0);
-    conv_bwd(u, 0, u->x0, u->a0, u->ga0, none);
+    conv_bwd(u, 1, u->a0, u->s0, u->gs0, u->ga0, slice(u->gc0, 32));
+    conv_bwd(u, 0, u->x0, u->a0, u->ga0, kNone);
 }
 
 void adam(qumond_unet *u, float lr)
 {
     ++u->step;
-    for (int l = 0; l < 11; ++l) {
-        Conv &c = u->L[l];
-        qm::launch_adam(c.w, c.mw, c.vw, c.gw, c.cout * c.kpad, lr, u->step, c.wb, u->s);
-        qm::launch_adam(c.b, c.mb, c.vb, c.gb, c.cout, lr, u->step, nullptr, u->s);
-    }
-    qm::launch_adam(u->hw, u->hm, u->hv, u->hgw, 17, lr, u->step, nullptr, u->s);
+    qm::launch_adam(u->adam, u->n_adam, u->n_param, lr, u->step, u->s);
 }
 
 bool good_n(int n) { return n >= 17 && n <= 513 && qm::log2_exact(n - 1) >= 4; }
@@ -231,7 +225,7 @@ qumond_status qumond_unet_create(int32_t n, uint64_t seed, void *hip_stream, qum
         c.wb = (__bf16 *)u->alloc(nw * 2);
         c.wd = (__bf16 *)u->alloc((size_t)c.cin * c.kpad_d * 2);
         c.b = (float *)u->alloc(c.cout * 4);
-        c.gb = (float *)u->alloc(c.cout * 4);
+        if (l < 10) c.gb = (float *)u->alloc(c.cout * 4);   // layer 10's lie behind the head's gradients
         c.mb = (float *)u->alloc(c.cout * 4);
         c.vb = (float *)u->alloc(c.cout * 4);
         if (u->err != hipSuccess) break;
@@ -249,7 +243,8 @@ qumond_status qumond_unet_create(int32_t n, uint64_t seed, void *hip_stream, qum
         qm::launch_to_bf16(c.w, c.wb, (int)nw, u->s);
     }
     u->hw = (float *)u->alloc(17 * 4);
-    u->hgw = (float *)u->alloc(17 * 4);
+    u->hgw = (float *)u->alloc((17 + 16) * 4);
+    u->L[10].gb = u->hgw + 17;
     u->hm = (float *)u->alloc(17 * 4);
     u->hv = (float *)u->alloc(17 * 4);
     if (u->err == hipSuccess) {
@@ -260,6 +255,20 @@ qumond_status qumond_unet_create(int32_t n, uint64_t seed, void *hip_stream, qum
         (void)hipMemcpy(u->hw, hh, sizeof hh, hipMemcpyHostToDevice);
         (void)hipMemset(u->hm, 0, 17 * 4);
         (void)hipMemset(u->hv, 0, 17 * 4);
+    }
+    {   // the parameter arrays, for Adam's one launch
+        std::vector<qm::AdamArray> t;
+        for (int l = 0; l < 11; ++l) {
+            const Conv &c = u->L[l];
+            t.push_back({c.w, c.mw, c.vw, c.gw, c.wb, c.cout * c.kpad});
+            t.push_back({c.b, c.mb, c.vb, c.gb, nullptr, c.cout});
+        }
+        t.push_back({u->hw, u->hm, u->hv, u->hgw, nullptr, 17});
+        for (const qm::AdamArray &a : t) u->n_param += a.count;
+        u->n_adam = (int)t.size();
+        u->adam = (qm::AdamArray *)u->alloc(t.size() * sizeof(qm::AdamArray));
+        if (u->err == hipSuccess)
+            (void)hipMemcpy(u->adam, t.data(), t.size() * sizeof(qm::AdamArray), hipMemcpyHostToDevice);
     }
     const int n0 = u->n[0], n1 = u->n[1], n2 = u->n[2], n3 = u->n[3];
     u->x0 = u->tensor(n0, 8);

@@ -22,6 +22,7 @@
 namespace qm {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
@@ -818,18 +819,50 @@ static int reduce_splits(int N)
     return ns < 1 ? 1 : (ns > kMaxSplit ? kMaxSplit : ns);
 }
 
-// bias gradient: partial[split, c] = sum over the split's voxels of dy[v, c].
-// Workgroup = split; thread t sums channel t % c over voxels t / c + q (256 / c)
-// (c divides 256), then the c sums are combined in a fixed order.
-__global__ void __launch_bounds__(256) bgrad_k(Tensor dy, int c, int per, float *__restrict__ partial)
+// The gradient before the ReLU of a layer, in place, and its bias gradient:
+// g[v, c] += add[v, c] (rounded once to BF16; add.p null: nothing), 0 where the
+// ReLU output y[v, c] is 0, partial[split, c] = sum over the split's voxels of g.
+// Workgroup = split; a thread takes two channels of voxels l + q (256 / c), l
+// its place among 256 / c voxels (c divides 256), so that a channel's sum is one
+// chain per l, combined in a fixed order at the end.  The chain and its few
+// splits leave little parallelism: UN steps of a chain are loaded at once.  One
+// pass for what were up to three, whose sums waited for every load: 16 channels
+// at 129^3 89 (add) + 84 (ReLU) + 126 (sums) -> 120 us.
+template <bool ADD>
+__global__ void __launch_bounds__(128) pre_grad_k(Tensor g, Tensor add, Tensor y, int c, int per, float *__restrict__ partial)
 {
+    constexpr int UN = 16;
     __shared__ float sh[256];
-    const int N = dy.n * dy.n * dy.n;
+    const int N = g.n * g.n * g.n;
     const int vb = blockIdx.x * per, ve = min(N, vb + per);
-    const int ch = threadIdx.x % c, lanes = 256 / c, l = threadIdx.x / c;
-    float s = 0.f;
-    for (int v = vb + l; v < ve; v += lanes) s += (float)dy.p[(size_t)v * dy.cs + ch];
-    sh[threadIdx.x] = s;
+    const int hc = c / 2, ch = 2 * ((int)threadIdx.x % hc), lanes = 256 / c, l = threadIdx.x / hc;
+    float s0 = 0.f, s1 = 0.f;
+    for (int v0 = vb + l; v0 < ve; v0 += UN * lanes) {
+        bf16x2 gv[UN], av[UN], yv[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const size_t v = (size_t)min(v0 + u * lanes, ve - 1);
+            gv[u] = *reinterpret_cast<const bf16x2 *>(g.p + v * g.cs + ch);
+            yv[u] = *reinterpret_cast<const bf16x2 *>(y.p + v * y.cs + ch);
+            if (ADD) av[u] = *reinterpret_cast<const bf16x2 *>(add.p + v * add.cs + ch);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            if (v0 + u * lanes >= ve) break;
+            bf16x2 r = gv[u];
+            if (ADD) {
+                r[0] = (__bf16)((float)r[0] + (float)av[u][0]);
+                r[1] = (__bf16)((float)r[1] + (float)av[u][1]);
+            }
+            if (!((float)yv[u][0] > 0.f)) r[0] = (__bf16)0.f;
+            if (!((float)yv[u][1] > 0.f)) r[1] = (__bf16)0.f;
+            *reinterpret_cast<bf16x2 *>(g.p + (size_t)(v0 + u * lanes) * g.cs + ch) = r;
+            s0 += (float)r[0];
+            s1 += (float)r[1];
+        }
+    }
+    sh[l * c + ch] = s0;
+    sh[l * c + ch + 1] = s1;
     __syncthreads();
     if ((int)threadIdx.x < c) {
         float t = 0.f;
@@ -838,48 +871,14 @@ __global__ void __launch_bounds__(256) bgrad_k(Tensor dy, int c, int per, float 
     }
 }
 
-void launch_bgrad(Tensor dy, int c, float *partial, float *db, hipStream_t s)
+void launch_pre_grad(Tensor g, Tensor add, Tensor y, int c, float *partial, float *db, hipStream_t s)
 {
-    const int N = dy.n * dy.n * dy.n;
+    const int N = g.n * g.n * g.n;
     const int nsplit = reduce_splits(N);
     const int per = (N + nsplit - 1) / nsplit;
-    hipLaunchKernelGGL(bgrad_k, dim3(nsplit), dim3(256), 0, s, dy, c, per, partial);
-    hipLaunchKernelGGL(split_reduce_k, dim3((c + 255) / 256), dim3(256), 0, s, partial, nsplit, c, c, c, db);
-}
-
-// ---------------------------------------------------------- elementwise
-
-// g[v, c] = 0 where the ReLU output y[v, c] is 0
-__global__ void relu_bwd_k(Tensor g, Tensor y, int c)
-{
-    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    const size_t N = (size_t)g.n * g.n * g.n;
-    if (t >= N * c) return;
-    const size_t v = t / c, ch = t - v * c;
-    if (!((float)y.p[v * y.cs + ch] > 0.f)) g.p[v * g.cs + ch] = (__bf16)0.f;
-}
-
-void launch_relu_bwd(Tensor g, Tensor y, int c, hipStream_t s)
-{
-    const size_t cnt = (size_t)g.n * g.n * g.n * c;
-    hipLaunchKernelGGL(relu_bwd_k, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, g, y, c);
-}
-
-// dst[v, c] += src[v, c] (rounded once to BF16)
-__global__ void add_k(Tensor dst, Tensor src, int c)
-{
-    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    const size_t N = (size_t)dst.n * dst.n * dst.n;
-    if (t >= N * c) return;
-    const size_t v = t / c, ch = t - v * c;
-    __bf16 *d = dst.p + v * dst.cs + ch;
-    *d = (__bf16)((float)*d + (float)src.p[v * src.cs + ch]);
-}
-
-void launch_add(Tensor dst, Tensor src, int c, hipStream_t s)
-{
-    const size_t cnt = (size_t)dst.n * dst.n * dst.n * c;
-    hipLaunchKernelGGL(add_k, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, dst, src, c);
+    if (add.p) hipLaunchKernelGGL(pre_grad_k<true>, dim3(nsplit), dim3(128), 0, s, g, add, y, c, per, partial);
+    else hipLaunchKernelGGL(pre_grad_k<false>, dim3(nsplit), dim3(128), 0, s, g, add, y, c, per, partial);
+    hipLaunchKernelGGL(split_reduce_k, dim3(1), dim3(256), 0, s, partial, nsplit, c, c, c, db);
 }
 
 // Trilinear 2x up-sampling of vertex-centred grids (n_fine = 2 n_coarse - 1);
@@ -985,59 +984,70 @@ void launch_head_fwd(Tensor x, int c, const float *w, const float *b, float *yh,
     hipLaunchKernelGGL(head_fwd_k, dim3((N + 255) / 256), dim3(256), 0, s, x, c, w, b, yh);
 }
 
-// dx[v, c] = dy[v] w[c] (c a multiple of 8; 16-byte stores)
-__global__ void head_bwd_x_k(const float *__restrict__ dyh, int c, const float *__restrict__ w, Tensor dx)
+// Backward of the head and of the ReLU below it in one pass over x (the ReLU's
+// output): dx[v, c] = dy[v] w[c] (rounded to BF16), 0 where x[v, c] is 0; partial
+// sums per split of dy[v] x[v, c] (c < C), of dy[v] (C) and of dx[v, c] (C + 1 ..
+// 2 C, the bias gradient of the layer below).  Chains and order as in
+// pre_grad_k.
+__global__ void __launch_bounds__(128)
+head_bwd_k(const float *__restrict__ dyh, Tensor x, int c, const float *__restrict__ w, Tensor dx, int per,
+           float *__restrict__ partial)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    const int N = dx.n * dx.n * dx.n;
-    if (v >= N) return;
-    const float d = dyh[v];
-    for (int c8 = 0; c8 < c; c8 += 8) {
-        bf16x8 o;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = (__bf16)(d * w[c8 + e]);
-        *reinterpret_cast<bf16x8 *>(dx.p + (size_t)v * dx.cs + c8) = o;
-    }
-}
-
-// partial[split, c] = sum dy[v] x[v, c] (c < C), partial[split, C] = sum dy[v];
-// workgroup = split, fixed-order combination as in bgrad_k (C divides 256).
-__global__ void __launch_bounds__(256)
-head_bwd_w_k(const float *__restrict__ dyh, Tensor x, int c, int per, float *__restrict__ partial)
-{
-    __shared__ float sh[256], sb[256];
+    constexpr int UN = 16;
+    __shared__ float sw[256], sb[256], sd[256];
     const int N = x.n * x.n * x.n;
     const int vb = blockIdx.x * per, ve = min(N, vb + per);
-    const int ch = threadIdx.x % c, lanes = 256 / c, l = threadIdx.x / c;
-    float s = 0.f, sbias = 0.f;
-    for (int v = vb + l; v < ve; v += lanes) {
-        const float d = dyh[v];
-        s += d * (float)x.p[(size_t)v * x.cs + ch];
-        sbias += d;
+    const int hc = c / 2, ch = 2 * ((int)threadIdx.x % hc), lanes = 256 / c, l = threadIdx.x / hc;
+    const float w0 = w[ch], w1 = w[ch + 1];
+    float s0 = 0.f, s1 = 0.f, b = 0.f, d0 = 0.f, d1 = 0.f;
+    for (int v0 = vb + l; v0 < ve; v0 += UN * lanes) {
+        float dv[UN];
+        bf16x2 xv[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const size_t v = (size_t)min(v0 + u * lanes, ve - 1);
+            dv[u] = dyh[v];
+            xv[u] = *reinterpret_cast<const bf16x2 *>(x.p + v * x.cs + ch);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            if (v0 + u * lanes >= ve) break;
+            const float d = dv[u], x0 = (float)xv[u][0], x1 = (float)xv[u][1];
+            bf16x2 r;
+            r[0] = x0 > 0.f ? (__bf16)(d * w0) : (__bf16)0.f;
+            r[1] = x1 > 0.f ? (__bf16)(d * w1) : (__bf16)0.f;
+            *reinterpret_cast<bf16x2 *>(dx.p + (size_t)(v0 + u * lanes) * dx.cs + ch) = r;
+            s0 += d * x0;
+            s1 += d * x1;
+            b += d;
+            d0 += (float)r[0];
+            d1 += (float)r[1];
+        }
     }
-    sh[threadIdx.x] = s;
-    sb[threadIdx.x] = sbias;
+    sw[l * c + ch] = s0;
+    sw[l * c + ch + 1] = s1;
+    sb[l * c + ch] = b;
+    sd[l * c + ch] = d0;
+    sd[l * c + ch + 1] = d1;
     __syncthreads();
-    if ((int)threadIdx.x < c) {
-        float t = 0.f;
-        for (int q = 0; q < lanes; ++q) t += sh[q * c + threadIdx.x];
-        partial[(size_t)blockIdx.x * (c + 1) + threadIdx.x] = t;
-    } else if ((int)threadIdx.x == c) {
-        float t = 0.f;
-        for (int q = 0; q < lanes; ++q) t += sb[q * c];   // channel-0 threads saw every voxel once
-        partial[(size_t)blockIdx.x * (c + 1) + c] = t;
+    const int t = threadIdx.x, row = 2 * c + 1;
+    if (t <= 2 * c) {
+        const float *src = t < c ? sw + t : (t == c ? sb : sd + (t - c - 1));   // every voxel once in channel 0's sums
+        float v = 0.f;
+        for (int q = 0; q < lanes; ++q) v += src[q * c];
+        partial[(size_t)blockIdx.x * row + t] = v;
     }
 }
 
+// dwb: c weights and the bias of the head, then the c bias gradients of the layer below
 void launch_head_bwd(const float *dyh, Tensor x, int c, const float *w, Tensor dx, float *partial, float *dwb,
                      hipStream_t s)
 {
     const int N = x.n * x.n * x.n;
-    hipLaunchKernelGGL(head_bwd_x_k, dim3((N + 255) / 256), dim3(256), 0, s, dyh, c, w, dx);
     const int nsplit = reduce_splits(N);
-    const int per = (N + nsplit - 1) / nsplit;
-    hipLaunchKernelGGL(head_bwd_w_k, dim3(nsplit), dim3(256), 0, s, dyh, x, c, per, partial);
-    hipLaunchKernelGGL(split_reduce_k, dim3(1), dim3(256), 0, s, partial, nsplit, c + 1, c + 1, c + 1, dwb);
+    const int per = (N + nsplit - 1) / nsplit, row = 2 * c + 1;
+    hipLaunchKernelGGL(head_bwd_k, dim3(nsplit), dim3(128), 0, s, dyh, x, c, w, dx, per, partial);
+    hipLaunchKernelGGL(split_reduce_k, dim3(1), dim3(256), 0, s, partial, nsplit, row, row, row, dwb);
 }
 
 // Mean squared error over interior nodes; dy = 2 (yhat - t) / N_int there, 0 on
@@ -1068,9 +1078,12 @@ mse_k(const float *__restrict__ yh, const float *__restrict__ tg, int n, float *
 
 __global__ void sum_k(const double *__restrict__ partial, int nb, double *__restrict__ out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+    __shared__ double sh[kLossBlocks];
+    for (int b = threadIdx.x; b < nb; b += 64) sh[b] = partial[b];
+    __syncthreads();
+    if (threadIdx.x == 0) {
         double s = 0.0;
-        for (int b = 0; b < nb; ++b) s += partial[b];
+        for (int b = 0; b < nb; ++b) s += sh[b];
         out[0] = s;
     }
 }
@@ -1081,27 +1094,34 @@ void launch_mse(const float *yh, const float *tg, int n, float *dy, double *part
     hipLaunchKernelGGL(sum_k, dim3(1), dim3(64), 0, s, partial, kLossBlocks, loss);
 }
 
-// Adam on FP32 master weights; the BF16 copy (if any) is refreshed.
-__global__ void adam_k(float *__restrict__ w, float *__restrict__ m, float *__restrict__ v, const float *__restrict__ g,
-                       int count, float lr, float b1, float b2, float eps, float c1, float c2, __bf16 *__restrict__ wb)
+// Adam on FP32 master weights, all arrays of the network in one launch; the
+// BF16 copy (if any) is refreshed.
+__global__ void adam_k(const AdamArray *__restrict__ arrays, int n, float lr, float b1, float b2, float eps, float c1,
+                       float c2)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= count) return;
-    const float gt = g[t];
-    const float mt = b1 * m[t] + (1.f - b1) * gt;
-    const float vt = b2 * v[t] + (1.f - b2) * gt * gt;
-    m[t] = mt;
-    v[t] = vt;
-    const float wt = w[t] - lr * (mt / c1) / (sqrtf(vt / c2) + eps);
-    w[t] = wt;
-    if (wb) wb[t] = (__bf16)wt;
+    int t = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int a = 0; a < n; ++a) {
+        const AdamArray A = arrays[a];
+        if (t < A.count) {
+            const float gt = A.g[t];
+            const float mt = b1 * A.m[t] + (1.f - b1) * gt;
+            const float vt = b2 * A.v[t] + (1.f - b2) * gt * gt;
+            A.m[t] = mt;
+            A.v[t] = vt;
+            const float wt = A.w[t] - lr * (mt / c1) / (sqrtf(vt / c2) + eps);
+            A.w[t] = wt;
+            if (A.wb) A.wb[t] = (__bf16)wt;
+            return;
+        }
+        t -= A.count;
+    }
 }
 
-void launch_adam(float *w, float *m, float *v, const float *g, int count, float lr, int step, __bf16 *wb, hipStream_t s)
+void launch_adam(const AdamArray *arrays, int n, int total, float lr, int step, hipStream_t s)
 {
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    hipLaunchKernelGGL(adam_k, dim3((count + 255) / 256), dim3(256), 0, s, w, m, v, g, count, lr, b1, b2, eps, c1, c2, wb);
+    hipLaunchKernelGGL(adam_k, dim3((total + 255) / 256), dim3(256), 0, s, arrays, n, lr, b1, b2, eps, c1, c2);
 }
 
 __global__ void to_bf16_k(const float *__restrict__ src, __bf16 *__restrict__ dst, int count)
