@@ -2103,302 +2103,6 @@ void launch_fill(T *p, size_t count, T v, hipStream_t s)
     hipLaunchKernelGGL(fill_k<T>, dim3((unsigned)blocks), dim3(256), 0, s, p, count, v);
 }
 
-// ------------------------------------------------------------- coarse tail
-//
-// Every level with at most 17 points per side lives in the LDS of a single
-// workgroup (u and f of 17^3, 9^3, 5^3, 3^3: 5794 values each), so a V-cycle
-// or a whole FMG over these levels is one launch.  Level l has 2^l + 1 points.
-
-constexpr int kTailTop = 4;              // 17^3
-constexpr int kTailThreads = 1024;
-__host__ __device__ constexpr int tail_off(int l)
-{
-    return l <= 1 ? 0 : tail_off(l - 1) + ((1 << (l - 1)) + 1) * ((1 << (l - 1)) + 1) * ((1 << (l - 1)) + 1);
-}
-constexpr int kTailSize = tail_off(kTailTop + 1);
-constexpr int kTailTopN = (1 << kTailTop) + 1;
-
-// Lanes of the 1024-thread workgroup cover a 16 x 16 x 4 brick of nodes (i, j
-// from the lane, k strided by 4); colour passes use 8 x 16 x 8 with two nodes of
-// one colour per row pair.  Every level is a compile-time template argument, so
-// all node indexing folds to constants.
-template <typename T>
-struct TailLDS {
-    T *U, *F, *R;
-    T L;
-    int npre, npost;
-    T *h2, *ih2;   // in LDS: h^2 and 1/h^2 per level, h = L / (n - 1)
-
-    __device__ void init_h() const   // by one thread, before the first barrier
-    {
-        for (int l = 1; l <= kTailTop; ++l) {
-            const T h = L / T((1 << l));
-            h2[l] = h * h;
-            ih2[l] = T(1) / (h * h);
-        }
-    }
-    template <int LV> __device__ T *u() const { return U + tail_off(LV); }
-    template <int LV> __device__ T *fr() const { return F + tail_off(LV); }
-
-    template <int LV>
-    __device__ void gs(int colour) const
-    {
-#pragma clang fp contract(off)
-        constexpr int n = (1 << LV) + 1, m = n - 2;
-        const T hh = h2[LV], sixth = T(1) / T(6);
-        T *uu = u<LV>();
-        const T *ff = fr<LV>();
-        const int tx = threadIdx.x & 7, ty = (threadIdx.x >> 3) & 15, tz = threadIdx.x >> 7;
-        const int j = 1 + ty;
-        if (j <= m) {
-#pragma unroll
-            for (int k = 1 + tz; k <= m; k += 8) {
-                const int i = 1 + 2 * tx + ((colour + 1 + j + k) & 1);
-                if (i > m) continue;
-                const int p = i + n * (j + n * k);
-                const T s = uu[p - 1] + uu[p + 1] + uu[p - n] + uu[p + n] + uu[p - n * n] + uu[p + n * n];
-                uu[p] = (s - hh * ff[p]) * sixth;
-            }
-        }
-        __syncthreads();
-    }
-    template <int LV>
-    __device__ void sweeps(int ns) const
-    {
-        for (int s = 0; s < ns; ++s) {
-            gs<LV>(0);
-            gs<LV>(1);
-        }
-    }
-    // exact solve of the single interior node of the 3^3 level, in FP64
-    __device__ void exact() const
-    {
-#pragma clang fp contract(off)
-        if (threadIdx.x == 0) {
-            T *uu = u<1>();
-            const T *ff = fr<1>();
-            const double h = double(L) / 2.0;
-            const int p = 13;
-            const double s = double(uu[p - 1]) + double(uu[p + 1]) + double(uu[p - 3]) + double(uu[p + 3]) +
-                             double(uu[p - 9]) + double(uu[p + 9]);
-            uu[p] = T((s - h * h * double(ff[p])) / 6.0);
-        }
-        __syncthreads();
-    }
-    // fc = FW(f - A u) on level LV-1 and uc = 0: the residual of level LV is staged in R
-    template <int LV>
-    __device__ void resid_restrict() const
-    {
-#pragma clang fp contract(off)
-        constexpr int n = (1 << LV) + 1, m = n - 2, nc = (1 << (LV - 1)) + 1;
-        const T ih = ih2[LV];
-        const T *uu = u<LV>();
-        const T *ff = fr<LV>();
-        const int li = threadIdx.x & 15, lj = (threadIdx.x >> 4) & 15, lk = threadIdx.x >> 8;
-        if (li < m && lj < m) {
-            const int i = 1 + li, j = 1 + lj;
-            for (int k = 1 + lk; k <= m; k += 4) {
-                const int p = i + n * (j + n * k);
-                R[p] = ff[p] - (uu[p - 1] + uu[p + 1] + uu[p - n] + uu[p + n] + uu[p - n * n] + uu[p + n * n] -
-                                T(6) * uu[p]) * ih;
-            }
-        }
-        __syncthreads();
-        T *fc = fr<LV - 1>();
-        T *uc = u<LV - 1>();
-        const T w[3] = {T(0.25), T(0.5), T(0.25)};
-        if (li < nc && lj < nc) {
-            for (int K = lk; K < nc; K += 4) {
-                const int C = li + nc * (lj + nc * K);
-                uc[C] = T(0);
-                if (li == 0 || lj == 0 || K == 0 || li == nc - 1 || lj == nc - 1 || K == nc - 1) {
-                    fc[C] = T(0);
-                    continue;
-                }
-                T acc = T(0);
-                for (int c = -1; c <= 1; ++c)
-                    for (int b = -1; b <= 1; ++b)
-                        for (int a = -1; a <= 1; ++a)
-                            acc += (w[a + 1] * w[b + 1] * w[c + 1]) * R[(2 * li + a) + n * ((2 * lj + b) + n * (2 * K + c))];
-                fc[C] = acc;
-            }
-        }
-        __syncthreads();
-    }
-    template <int LV>
-    __device__ void restrict_f() const   // f_{LV-1} = FW(f_LV)
-    {
-#pragma clang fp contract(off)
-        constexpr int n = (1 << LV) + 1, nc = (1 << (LV - 1)) + 1;
-        const T *ff = fr<LV>();
-        T *fc = fr<LV - 1>();
-        const T w[3] = {T(0.25), T(0.5), T(0.25)};
-        const int li = threadIdx.x & 15, lj = (threadIdx.x >> 4) & 15, lk = threadIdx.x >> 8;
-        if (li < nc && lj < nc) {
-            for (int K = lk; K < nc; K += 4) {
-                const int C = li + nc * (lj + nc * K);
-                if (li == 0 || lj == 0 || K == 0 || li == nc - 1 || lj == nc - 1 || K == nc - 1) {
-                    fc[C] = T(0);
-                    continue;
-                }
-                T acc = T(0);
-                for (int c = -1; c <= 1; ++c)
-                    for (int b = -1; b <= 1; ++b)
-                        for (int a = -1; a <= 1; ++a)
-                            acc += (w[a + 1] * w[b + 1] * w[c + 1]) * ff[(2 * li + a) + n * ((2 * lj + b) + n * (2 * K + c))];
-                fc[C] = acc;
-            }
-        }
-        __syncthreads();
-    }
-    template <int LC>
-    __device__ void prolong(bool add) const   // level LC -> LC+1 interior
-    {
-        constexpr int nc = (1 << LC) + 1, n = (1 << (LC + 1)) + 1, m = n - 2;
-        const T *uc = u<LC>();
-        T *uf = u<LC + 1>();
-        const int li = threadIdx.x & 15, lj = (threadIdx.x >> 4) & 15, lk = threadIdx.x >> 8;
-        if (li < m && lj < m) {
-            const int i = 1 + li, j = 1 + lj;
-            for (int k = 1 + lk; k <= m; k += 4) {
-                const T v = prolong_at(nc, uc, i, j, k);
-                const int p = i + n * (j + n * k);
-                uf[p] = add ? uf[p] + v : v;
-            }
-        }
-        __syncthreads();
-    }
-    template <int LV, int TOP>
-    __device__ void inject() const   // boundary of level LV from level TOP, interior 0
-    {
-        constexpr int n = (1 << LV) + 1, nt = (1 << TOP) + 1, st = (nt - 1) / (n - 1);
-        T *uu = u<LV>();
-        const T *ut = u<TOP>();
-        const int li = threadIdx.x & 15, lj = (threadIdx.x >> 4) & 15, lk = threadIdx.x >> 8;
-        if (li < n && lj < n) {
-            for (int k = lk; k < n; k += 4) {
-                const bool bnd = li == 0 || lj == 0 || k == 0 || li == n - 1 || lj == n - 1 || k == n - 1;
-                uu[li + n * (lj + n * k)] = bnd ? ut[(li * st) + nt * ((lj * st) + nt * (k * st))] : T(0);
-            }
-        }
-        __syncthreads();
-    }
-    template <int LV>
-    __device__ void down() const
-    {
-        if constexpr (LV >= 2) {
-            sweeps<LV>(npre);
-            resid_restrict<LV>();
-            down<LV - 1>();
-        }
-    }
-    template <int LV, int TOP>
-    __device__ void up() const
-    {
-        if constexpr (LV <= TOP) {
-            prolong<LV - 1>(true);
-            sweeps<LV>(npost);
-            up<LV + 1, TOP>();
-        }
-    }
-    template <int TOP>
-    __device__ void vcycle() const
-    {
-        down<TOP>();
-        exact();
-        up<2, TOP>();
-    }
-    template <int LV, int TOP>
-    __device__ void restrict_all() const   // f of TOP-1 .. 1 from TOP
-    {
-        if constexpr (LV >= 2) {
-            restrict_f<LV>();
-            restrict_all<LV - 1, TOP>();
-        }
-    }
-    template <int LV, int TOP>
-    __device__ void inject_all() const
-    {
-        if constexpr (LV < TOP) {
-            inject<LV, TOP>();
-            inject_all<LV + 1, TOP>();
-        }
-    }
-    template <int LV, int TOP>
-    __device__ void fmg_up(int ncycle) const
-    {
-        if constexpr (LV <= TOP) {
-            prolong<LV - 1>(false);
-            for (int c = 0; c < ncycle; ++c) vcycle<LV>();
-            fmg_up<LV + 1, TOP>(ncycle);
-        }
-    }
-    template <int TOP>
-    __device__ void run(int mode, int ncycle, int nrep) const
-    {
-        if (mode == 1) {
-            restrict_all<TOP, TOP>();
-            inject_all<1, TOP>();
-            exact();
-            fmg_up<2, TOP>(ncycle);
-        } else {
-            for (int r = 0; r < nrep; ++r) vcycle<TOP>();
-        }
-    }
-};
-
-template <typename T>
-__global__ void __launch_bounds__(kTailThreads)
-coarse_tail_k(int top, T L, const T *__restrict__ fg, T *__restrict__ ug, int npre, int npost, int ncycle, int mode,
-              int nrep)
-{
-    __shared__ T U[kTailSize];
-    __shared__ T F[kTailSize];
-    __shared__ T Rs[kTailTopN * kTailTopN * kTailTopN];
-    __shared__ T hs[2][kTailTop + 1];
-    TailLDS<T> t{U, F, Rs, L, npre, npost, hs[0], hs[1]};
-    if (threadIdx.x == 0) t.init_h();
-    const int n = (1 << top) + 1, cnt = n * n * n;
-    fg += (size_t)blockIdx.x * cnt;
-    ug += (size_t)blockIdx.x * cnt;
-    T *utop = U + tail_off(top), *ftop = F + tail_off(top);
-    const bool uzero = mode == 2;   // a correction V-cycle whose iterate is known to be zero: not read
-    // all global loads of a lane first, then its LDS stores (overlapped latency)
-    constexpr int NL = (kTailTopN * kTailTopN * kTailTopN + kTailThreads - 1) / kTailThreads;
-    T xu[NL], xf[NL];
-#pragma unroll
-    for (int r = 0; r < NL; ++r) {
-        const int p = min((int)threadIdx.x + r * kTailThreads, cnt - 1);
-        xu[r] = uzero ? T(0) : ug[p];
-        xf[r] = fg[p];
-    }
-#pragma unroll
-    for (int r = 0; r < NL; ++r) {
-        const int p = threadIdx.x + r * kTailThreads;
-        if (p < cnt) {
-            utop[p] = xu[r];
-            ftop[p] = xf[r];
-        }
-    }
-    __syncthreads();
-    const int md = mode == 1 ? 1 : 0;
-    switch (top) {
-    case 1: t.template run<1>(md, ncycle, nrep); break;
-    case 2: t.template run<2>(md, ncycle, nrep); break;
-    case 3: t.template run<3>(md, ncycle, nrep); break;
-    default: t.template run<4>(md, ncycle, nrep); break;
-    }
-    for (int p = threadIdx.x; p < cnt; p += blockDim.x) ug[p] = utop[p];
-}
-
-template <typename T>
-void launch_coarse_tail(int ltop, double L, const T *f, T *u, int npre, int npost, int ncycle, int mode, int nrep,
-                        hipStream_t s, int nb)
-{
-    hipLaunchKernelGGL(coarse_tail_k<T>, dim3(nb), dim3(kTailThreads), 0, s, ltop, T(L), f, u, npre, npost, ncycle,
-                       mode, nrep);
-}
-
 // ------------------------------------------------------------------ norms
 
 template <int NT>
@@ -2874,7 +2578,6 @@ void launch_guess_interior(int n, const void *g, int kind, double *u, hipStream_
     template void launch_inject_boundary<T>(int, const T *, int, T *, T *, hipStream_t, int);                  \
     template void launch_fill<T>(T *, size_t, T, hipStream_t);                                                 \
     template void launch_boundary_copy<T>(int, const T *, T *, hipStream_t);                                   \
-    template void launch_coarse_tail<T>(int, double, const T *, T *, int, int, int, int, int, hipStream_t, int);\
     template void launch_resid_norms<T>(int, double, const T *, const T *, double *, double *, hipStream_t, int,    \
                                         double *);
 QM_INST(double)
