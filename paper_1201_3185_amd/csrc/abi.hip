@@ -457,7 +457,8 @@ static qumond_status solve_box(qumond_ctx *ctx, const Chain &ch, bool mond, int 
     // The norms pass that follows a step (the relres() of the loop) also forms
     // the next step's right-hand side, scaled by the power of two from the
     // norms before the step's correction (any power of two gives the same
-    // corrected iterate), so only the first step forms it separately.
+    // corrected iterate); the norms pass after an FP32 FMG forms the first
+    // step's, and only the first step from a guess forms it separately.
     auto refine_step = [&]() {
         Mixed &X = *ch.mix;
         double *sc = X.sc + 2 * X.cur;
@@ -465,12 +466,14 @@ static qumond_status solve_box(qumond_ctx *ctx, const Chain &ch, bool mond, int 
             qm::launch_mixed_scale(ctx->n, ch.mg->norms, sc, ch.s);
             qm::launch_resid_to_f32(ctx->n, B.h, sc, f, u, X.r, ch.s);
         }
-        // zero correction iterate: the buffers are cleared on the first step of
-        // a solve; later steps' first sweeps read no iterate
+        // zero correction iterate: the buffers' faces are cleared before the first
+        // step of a solve, their interiors only where the first sweep reads them
         X.mg.bind(B.L, X.a[0], X.a[1], X.r);
-        if (!X.fresh || !X.mg.zero_start_ok()) {
+        if (!X.mg.zero_start_ok()) {
             qm::launch_fill<float>(X.a[0], ctx->N, 0.0f, ch.s);
             qm::launch_fill<float>(X.a[1], ctx->N, 0.0f, ch.s);
+        } else if (!X.fresh) {
+            qm::launch_zero_boundary(ctx->n, X.a[0], X.a[1], nullptr, ch.s);
         }
         X.mg.zero_start = X.mg.zero_start_ok();
         X.mg.finest_cycle();
@@ -533,11 +536,15 @@ static qumond_status solve_box(qumond_ctx *ctx, const Chain &ch, bool mond, int 
     if (mixed) {
         // FP32 FMG seeds the FP64 iterate ...
         Mixed &X = *ch.mix;
-        qm::launch_narrow(f, X.r, ctx->N, ch.s);
-        qm::launch_narrow_boundary(ctx->n, u, X.a[0], X.a[1], ch.s);
+        qm::launch_mixed_start(ctx->n, B.h, f, u, X.r, X.a[0], X.a[1], ch.mg->partial, X.sc + 2 * X.cur, ch.s);
         X.mg.bind(B.L, X.a[0], X.a[1], X.r);
         X.mg.fmg(c.ncycle_fmg);
         qm::launch_widen_interior(ctx->n, X.mg.result(), u, ch.s);
+        if (c.tol_rel > 0.0 && c.max_vcycles > 0) {   // the norms pass forms the first step's right-hand side
+            qm::launch_zero_boundary(ctx->n, X.a[0], X.a[1], X.r, ch.s);
+            ch.mg->set_r32(X.sc + 2 * X.cur, X.r);
+            X.fresh = true;
+        }
         if ((e = ch.mg->relres(rr)) != hipSuccess) return hip_fail(e, "solve: FP32 FMG");
         rr0 = rr;
         // ... then FP64 residual correction with FP32 V-cycles (zero boundary

@@ -148,34 +148,39 @@ void enqueue_solve(const qumond_batch *B, Class &C, qm::Multigrid<float> &mg, bo
     const double *f = (mond ? C.S : C.f) + (size_t)p0 * C.N;
     const size_t cnt = (size_t)nb * C.N;
     qm::launch_bc_outer_batch(C.n, c.box_side, mond ? 2 : 1, c.G, c.a0, C.prob + p0, u, nb, s, B->nu);
-    qm::launch_narrow(f, C.r, cnt, s);
-    qm::launch_narrow_boundary(C.n, u, C.a[0], C.a[1], s, nb);
+    // Scales in two slots of 2 nb doubles: step k corrects with the scale its
+    // right-hand side was formed with, and the norms pass before it forms that
+    // right-hand side: with the size of f and the boundary values for the first
+    // step, with the power of two from the norms before the previous correction
+    // for the later ones.
+    double *const scs[2] = {C.sc, C.sc + 2 * (size_t)C.P};
+    qm::launch_mixed_start(C.n, C.h, f, u, C.r, C.a[0], C.a[1], C.partial, scs[0], s, nb);
     mg.bind(c.box_side, C.a[0], C.a[1], C.r);
     mg.fmg(c.ncycle_fmg);
     qm::launch_widen_interior(C.n, mg.result(), u, s, nb);
-    qm::launch_resid_norms<double>(C.n, C.h, f, u, C.partial, hist_slot(B, C, mond, 0, p0), s, nb);
-    // Scales in two slots of 2 nb doubles: step k corrects with the scale its
-    // right-hand side was formed with, and its norms pass forms the next
-    // right-hand side with the power of two from the norms before its correction.
-    double *const scs[2] = {C.sc, C.sc + 2 * (size_t)C.P};
+    if (K > 0) {
+        // zero correction iterate; its interiors are cleared below where they are read
+        qm::launch_zero_boundary(C.n, C.a[0], C.a[1], C.r, s, nb);
+        qm::launch_resid_norms_r32(C.n, C.h, f, u, C.partial, hist_slot(B, C, mond, 0, p0), scs[0], C.r, s, nb);
+    } else {
+        qm::launch_resid_norms<double>(C.n, C.h, f, u, C.partial, hist_slot(B, C, mond, 0, p0), s, nb);
+    }
     for (int k = 1; k <= K; ++k) {
         double *cur = scs[(k - 1) & 1], *next = scs[k & 1];
-        if (k == 1) {
-            qm::launch_mixed_scale(C.n, hist_slot(B, C, mond, 0, p0), cur, s, nb);
-            qm::launch_resid_to_f32(C.n, C.h, cur, f, u, C.r, s, nb);
-        }
-        // zero correction iterate: the buffers (boundaries left by the FMG) are
-        // cleared once; later steps' first sweeps read no iterate
         mg.bind(c.box_side, C.a[0], C.a[1], C.r);
-        if (k == 1 || !mg.zero_start_ok()) {
+        if (!mg.zero_start_ok()) {
             qm::launch_fill<float>(C.a[0], cnt, 0.0f, s);
             qm::launch_fill<float>(C.a[1], cnt, 0.0f, s);
         }
         mg.zero_start = mg.zero_start_ok();
         mg.finest_cycle();
         qm::launch_correct(C.n, cur, mg.result(), u, s, nb);
-        qm::launch_mixed_scale(C.n, hist_slot(B, C, mond, k - 1, p0), next, s, nb);
-        qm::launch_resid_norms_r32(C.n, C.h, f, u, C.partial, hist_slot(B, C, mond, k, p0), next, C.r, s, nb);
+        if (k < K) {
+            qm::launch_mixed_scale(C.n, hist_slot(B, C, mond, k - 1, p0), next, s, nb);
+            qm::launch_resid_norms_r32(C.n, C.h, f, u, C.partial, hist_slot(B, C, mond, k, p0), next, C.r, s, nb);
+        } else {
+            qm::launch_resid_norms<double>(C.n, C.h, f, u, C.partial, hist_slot(B, C, mond, k, p0), s, nb);
+        }
     }
 }
 
@@ -238,9 +243,11 @@ hipError_t tail_steps(qumond_batch *B, Class &C, bool mond, int p, const double 
         qm::launch_mixed_scale(C.n, last, C.sc1, s, 1);
         qm::launch_resid_to_f32(C.n, C.h, C.sc1, f, u, C.r, s, 1);
         mg.bind(c.box_side, C.a[0], C.a[1], C.r);
-        if (steps == 0 || !mg.zero_start_ok()) {
+        if (!mg.zero_start_ok()) {
             qm::launch_fill<float>(C.a[0], C.N, 0.0f, s);
             qm::launch_fill<float>(C.a[1], C.N, 0.0f, s);
+        } else if (steps == 0) {
+            qm::launch_zero_boundary(C.n, C.a[0], C.a[1], nullptr, s);
         }
         mg.zero_start = mg.zero_start_ok();
         mg.finest_cycle();

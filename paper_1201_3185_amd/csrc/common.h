@@ -229,8 +229,13 @@ constexpr int kNormBlocks = 2048;
 
 // mixed precision (FP64 refinement around FP32 multigrid); sc holds s and 1/s
 // per problem, written by launch_mixed_scale from the residual norms.
-void launch_narrow(const double *src, float *dst, size_t count, hipStream_t s);
-void launch_narrow_boundary(int n, const double *src, float *d0, float *d1, hipStream_t s, int nb = 1);
+// launch_mixed_start: narrowed copies of nb right-hand sides f and of the faces of
+// u (into d0 and d1), and in sc the scale of the first step, the power of two at
+// or below the RMS of f and of the boundary values over h^2; partial: the norms'.
+void launch_mixed_start(int n, double h, const double *f, const double *u, float *r, float *d0, float *d1,
+                        double *partial, double *sc, hipStream_t s, int nb = 1);
+// zero values on the faces of two or three grids (d2 may be null)
+void launch_zero_boundary(int n, float *d0, float *d1, float *d2, hipStream_t s, int nb = 1);
 void launch_widen_interior(int n, const float *src, double *dst, hipStream_t s, int nb = 1);
 void launch_mixed_scale(int n, const double *norms, double *sc, hipStream_t s, int nb = 1);
 // The residual norms (as launch_resid_norms) and, in the same pass, the

@@ -2398,27 +2398,89 @@ void launch_resid_norms_r32(int n, double h, const double *f, const double *u, d
 // power of two is exact, and every FP32 multigrid operation commutes with it,
 // so the corrected iterate does not depend on which power of two scales a
 // step (values far from the FP32 subnormal range): a step may take its scale
-// from the norms before the previous correction, which lets the norms pass
-// of one step write the next step's scaled residual.  s and 1/s are computed
+// from the norms before the previous correction, the first one from the size
+// of the right-hand side, which lets the norms pass before a step write that
+// step's scaled residual.  s and 1/s are computed
 // on the device from the residual norms, so no host round trip sits between
 // the steps.
 
-__global__ void narrow_k(const double *__restrict__ src, float *__restrict__ dst, size_t count)
+// Start of a mixed solve, one pass: the right-hand side and the Dirichlet values
+// narrowed for the FP32 multigrid (problem blockIdx.y), with per-block sums of
+// the squares of f and of the boundary values over h^2, in a fixed order.
+// Bound by HBM (12 bytes a node).  With the first step's own pass over f and u and
+// two fills gone, a mixed solve of two potentials at 513^3 fell from 32.2 to 30.1 ms
+// and a batch of 7 problems of 129^3 and 9 of 257^3 from 40.4 to 38.2.
+__global__ void __launch_bounds__(256)
+mixed_start_k(int n, double ih2, const double *__restrict__ f, const double *__restrict__ u, float *__restrict__ r,
+              float *__restrict__ d0, float *__restrict__ d1, double *__restrict__ partial)
 {
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < count; t += (size_t)gridDim.x * blockDim.x)
-        dst[t] = (float)src[t];
+    __shared__ double sh[256];
+    const size_t N = (size_t)n * n * n, off = blockIdx.y * N;
+    f += off;
+    u += off;
+    r += off;
+    d0 += off;
+    d1 += off;
+    const size_t t0 = blockIdx.x * (size_t)256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
+    double q = 0.0;
+    for (size_t t = t0; t < N; t += stride) {
+        const double v = f[t];
+        r[t] = (float)v;
+        q += v * v;
+    }
+    for (size_t t = t0; t < (size_t)6 * n * n; t += stride) {
+        int i, j, k;
+        face_node(n, (int)t, i, j, k);
+        const size_t p = id3(n, i, j, k);
+        const double v = u[p], w = v * ih2;
+        d0[p] = (float)v;
+        d1[p] = (float)v;
+        q += w * w;
+    }
+    sh[threadIdx.x] = q;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) partial[blockIdx.y * gridDim.x + blockIdx.x] = sh[0];
 }
 
-__global__ void narrow_boundary_k(int n, const double *__restrict__ src, float *__restrict__ d0, float *__restrict__ d1)
+// ... and the power of two at or below their RMS as the scale of the first
+// refinement step, so that the norms pass after the FP32 FMG forms that step's
+// right-hand side too: a pass of its own over f and u (20 bytes a node) less.
+__global__ void __launch_bounds__(256)
+start_scale_k(int n, const double *__restrict__ partial, int nb, double *__restrict__ sc)
+{
+    __shared__ double sh[256];
+    partial += (size_t)blockIdx.x * nb;
+    double q = 0.0;
+    for (int t = threadIdx.x; t < nb; t += 256) q += partial[t];
+    sh[threadIdx.x] = q;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const double rms = sqrt(sh[0] / ((double)n * n * n));
+        const int e = (rms > 0.0 && isfinite(rms)) ? ilogb(rms) : 0;
+        sc[2 * blockIdx.x] = ldexp(1.0, e);
+        sc[2 * blockIdx.x + 1] = ldexp(1.0, -e);
+    }
+}
+
+// zero values on the faces of two or three grids (d2 may be null)
+__global__ void zero_boundary_k(int n, float *__restrict__ d0, float *__restrict__ d1, float *__restrict__ d2)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 6 * n * n) return;
     int i, j, k;
     face_node(n, t, i, j, k);
     const size_t p = id3(n, i, j, k) + blockIdx.y * (size_t)n * n * n;
-    const float v = (float)src[p];
-    d0[p] = v;
-    if (d1) d1[p] = v;
+    d0[p] = 0.0f;
+    d1[p] = 0.0f;
+    if (d2) d2[p] = 0.0f;
 }
 
 // u64 interior = (double) u32
@@ -2477,17 +2539,20 @@ __global__ void correct_k(int n, const double *__restrict__ sc, const float *__r
     u[p] += sc[2 * pb] * (double)e[p];
 }
 
-void launch_narrow(const double *src, float *dst, size_t count, hipStream_t s)
+void launch_mixed_start(int n, double h, const double *f, const double *u, float *r, float *d0, float *d1,
+                        double *partial, double *sc, hipStream_t s, int nb)
 {
-    size_t blocks = (count + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(narrow_k, dim3((unsigned)blocks), dim3(256), 0, s, src, dst, count);
+    size_t blocks = ((size_t)n * n * n + 1023) / 1024;
+    if (blocks > 3 * (size_t)kNormBlocks) blocks = 3 * kNormBlocks;   // the room of partial, per problem
+    hipLaunchKernelGGL(mixed_start_k, dim3((unsigned)blocks, nb), dim3(256), 0, s, n, 1.0 / (h * h), f, u, r, d0, d1,
+                       partial);
+    hipLaunchKernelGGL(start_scale_k, dim3(nb), dim3(256), 0, s, n, partial, (int)blocks, sc);
 }
 
-void launch_narrow_boundary(int n, const double *src, float *d0, float *d1, hipStream_t s, int nb)
+void launch_zero_boundary(int n, float *d0, float *d1, float *d2, hipStream_t s, int nb)
 {
     const int cnt = 6 * n * n;
-    hipLaunchKernelGGL(narrow_boundary_k, dim3((cnt + 255) / 256, nb), dim3(256), 0, s, n, src, d0, d1);
+    hipLaunchKernelGGL(zero_boundary_k, dim3((cnt + 255) / 256, nb), dim3(256), 0, s, n, d0, d1, d2);
 }
 
 void launch_widen_interior(int n, const float *src, double *dst, hipStream_t s, int nb)
