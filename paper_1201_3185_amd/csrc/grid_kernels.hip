@@ -1608,239 +1608,11 @@ residual_restrict_tile_k(int nf, T ih2, const T *__restrict__ f, const T *__rest
     fc[C] = acc;
 }
 
-// Residual and restriction marching in z: a workgroup owns CX x CY coarse
-// columns and a chunk of kc interior coarse planes.  For coarse plane K it
-// loads u planes 2K+1 and 2K+2 into a ring of four LDS planes, forms the fine
-// residuals of planes 2K and 2K+1 once each into a ring of three (plane 2K-1
-// is kept from the step before), then restricts planes 2K-1..2K+1 to plane K.
-// Every fine residual is formed once, with the expression and summation order
-// of residual_restrict_k, so the two kernels give identical results.
-// O1: tiles start at coarse column 1 rather than 0, so that 2^m interior-plus-
-// one columns split into whole tiles (a 257^3 coarse grid into 8 x 32 tiles
-// of 32 x 8, one workgroup per CU marching the whole column as the smoother
-// does, neighbours on one XCD sharing their halos in L2); the owner of a
-// column next to the low faces (I = 1 or J = 1) also zeroes the boundary
-// column beyond it.  DEPTH 2, 3 or 4 fetches each step's planes that many
-// steps ahead, into as many register sets used by the steps in turn.
-template <typename T, int CX, int CY, int NT = 256, bool O1 = false, int DEPTH = 1>
-__global__ void __launch_bounds__(NT)
-residual_restrict_zmarch_k(int nf, T ih2, const T *__restrict__ f, const T *__restrict__ u, T *__restrict__ fc,
-                           T *__restrict__ uc0, T *__restrict__ uc1, int tx, int ty, int tzc, int kc, int zu)
-{
-#pragma clang fp contract(off)
-    constexpr int RX = 2 * CX + 1, RY = 2 * CY + 1, RP = RX * RY;   // fine residual region of a plane
-    constexpr int UX = RX + 2, UY = RY + 2, UP = UX * UY;           // u region (one-node ring)
-    constexpr int NU = (UP + NT - 1) / NT, NR = (RP + NT - 1) / NT;
-    static_assert(CX * CY <= NT, "one coarse node per thread");
-    __shared__ T Us[4][UP];
-    __shared__ T Rs[3][RP];
-    const int nc = (nf + 1) / 2;
-    int bid = (int)xcd_tile(blockIdx.x, gridDim.x);
-    const int bx = bid % tx;
-    bid /= tx;
-    const int by = bid % ty;
-    bid /= ty;
-    const int bz = bid % tzc;
-    const int pb = bid / tzc;
-    const size_t Nf = (size_t)nf * nf * nf, Nc = (size_t)nc * nc * nc;
-    const size_t sy = (size_t)nf, sz = (size_t)nf * nf;
-    f += pb * Nf;
-    u += pb * Nf;
-    fc += pb * Nc;
-    uc0 += pb * Nc;
-    if (uc1) uc1 += pb * Nc;
-    const int tid = threadIdx.x;
-    const int I0 = (O1 ? 1 : 0) + bx * CX, J0 = (O1 ? 1 : 0) + by * CY;
-    const int fi0 = 2 * I0 - 1, fj0 = 2 * J0 - 1;   // origin of the fine residual region
-    // this thread's share of a u plane and of a residual plane
-    int uoff[NU], foff[NR], rq[NR];
-#pragma unroll
-    for (int r = 0; r < NU; ++r) {
-        const int t = tid + r * NT;
-        const int a = t % UX, b = t / UX;
-        const int i = fi0 - 1 + a, j = fj0 - 1 + b;
-        uoff[r] = (t < UP && i >= 0 && i < nf && j >= 0 && j < nf) ? i + nf * j : -1;
-    }
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const int t = tid + r * NT;
-        const int a = t % RX, b = t / RX;
-        const int i = fi0 + a, j = fj0 + b;
-        foff[r] = (t < RP && i >= 1 && i <= nf - 2 && j >= 1 && j <= nf - 2) ? i + nf * j : -1;
-        rq[r] = (a + 1) + UX * (b + 1);
-    }
-    // this thread's coarse node
-    const int ci = tid % CX, cj = tid / CX;
-    const int I = I0 + ci, J = J0 + cj;
-    const bool c_thread = tid < CX * CY && I < nc && J < nc;
-    const bool c_inner = c_thread && I >= 1 && I <= nc - 2 && J >= 1 && J <= nc - 2;
-    const bool ex = O1 && c_thread && I == 1, ey = O1 && c_thread && J == 1;   // also own column 0 / row 0
-    const int Kb = 1 + bz * kc, Ke = min(Kb + kc - 1, nc - 2);
-
-    auto zero_at = [&](int Ix, int Jx, int K) {
-        const size_t C = id3(nc, Ix, Jx, K);
-        uc0[C] = T(0);
-        if (uc1) uc1[C] = T(0);
-        fc[C] = T(0);
-    };
-    auto zero_extra = [&](int K) {   // the boundary columns beyond this thread's (O1 tiles only)
-        if (ex) zero_at(0, J, K);
-        if (ey) zero_at(I, 0, K);
-        if (ex && ey) zero_at(0, 0, K);
-    };
-    auto zero_node = [&](int K) {
-        zero_at(I, J, K);
-        zero_extra(K);
-    };
-    if (c_thread && bz == 0) zero_node(0);
-    if (c_thread && bz == tzc - 1) zero_node(nc - 1);
-
-    auto load_u = [&](int p) {
-        T *U = Us[p & 3];
-        const T *src = u + (size_t)p * sz;
-#pragma unroll
-        for (int r = 0; r < NU; ++r) {
-            const int t = tid + r * NT;
-            if (t < UP) U[t] = uoff[r] >= 0 ? src[uoff[r]] : T(0);
-        }
-    };
-    auto load_f = [&](int p, T *fv) {
-        const T *src = f + (size_t)p * sz;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) fv[r] = foff[r] >= 0 ? src[foff[r]] : T(0);
-    };
-    auto resid = [&](int p, const T *fv) {
-        const T *U = Us[p & 3];
-        const T *Um = Us[(p - 1) & 3];
-        const T *Up = Us[(p + 1) & 3];
-        T *Rp = Rs[p % 3];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int t = tid + r * NT;
-            if (t >= RP) continue;
-            if (foff[r] < 0) {
-                Rp[t] = T(0);
-                continue;
-            }
-            const int q = rq[r];
-            const T lap = (U[q - 1] + U[q + 1] + U[q - UX] + U[q + UX] + Um[q] + Up[q] - T(6) * U[q]) * ih2;
-            Rp[t] = fv[r] - lap;
-        }
-    };
-    auto restrict_plane = [&](int K) {
-        if (!c_thread) return;
-        if (!c_inner) {
-            zero_node(K);
-            return;
-        }
-        zero_extra(K);
-        const T w[3] = {T(0.25), T(0.5), T(0.25)};
-        T acc = T(0);
-        for (int c = -1; c <= 1; ++c) {
-            const T *Rp = Rs[(2 * K + c) % 3];
-            for (int b = -1; b <= 1; ++b)
-                for (int a = -1; a <= 1; ++a)
-                    acc += (w[a + 1] * w[b + 1] * w[c + 1]) * Rp[(2 * ci + 1 + a) + RX * (2 * cj + 1 + b)];
-        }
-        const size_t C = id3(nc, I, J, K);
-        if (zu) uc0[C] = T(0);
-        fc[C] = acc;
-    };
-
-    // u planes 2K+1, 2K+2 and f planes 2K, 2K+1 of step K travel in registers
-    // one step ahead: their loads are in flight while step K-1 computes
-    T ua[NU], ub[NU], fa[NR], fb[NR];
-    auto fetch_u = [&](int p, T *uv) {
-        const T *src = u + (size_t)p * sz;
-#pragma unroll
-        for (int r = 0; r < NU; ++r) uv[r] = uoff[r] >= 0 ? src[uoff[r]] : T(0);
-    };
-    auto store_u = [&](int p, const T *uv) {
-        T *U = Us[p & 3];
-#pragma unroll
-        for (int r = 0; r < NU; ++r) {
-            const int t = tid + r * NT;
-            if (t < UP) U[t] = uv[r];
-        }
-    };
-    // warm-up: u planes 2Kb-2..2Kb and the residual of plane 2Kb-1
-    load_u(2 * Kb - 2);
-    load_u(2 * Kb - 1);
-    load_u(2 * Kb);
-    load_f(2 * Kb - 1, fa);
-    __syncthreads();
-    resid(2 * Kb - 1, fa);
-    fetch_u(2 * Kb + 1, ua);
-    fetch_u(2 * Kb + 2, ub);
-    load_f(2 * Kb, fa);
-    load_f(2 * Kb + 1, fb);
-    __syncthreads();
-    if constexpr (DEPTH == 1) {
-        for (int K = Kb; K <= Ke; ++K) {
-            store_u(2 * K + 1, ua);   // slots of planes 2K-3 and 2K-2, last read before the previous barrier
-            store_u(2 * K + 2, ub);
-            T fc0[NR], fc1[NR];
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                fc0[r] = fa[r];
-                fc1[r] = fb[r];
-            }
-            if (K + 1 <= Ke) {   // the next step's planes, in flight during this one
-                fetch_u(2 * K + 3, ua);
-                fetch_u(2 * K + 4, ub);
-                load_f(2 * K + 2, fa);
-                load_f(2 * K + 3, fb);
-            }
-            __syncthreads();
-            resid(2 * K, fc0);
-            resid(2 * K + 1, fc1);
-            __syncthreads();
-            restrict_plane(K);
-        }
-    } else {
-        // step K's planes sit in register set (K - Kb) mod DEPTH, fetched DEPTH steps ahead
-        T ua2[NU], ub2[NU], fa2[NR], fb2[NR], ua3[NU], ub3[NU], fa3[NR], fb3[NR], ua4[NU], ub4[NU], fa4[NR], fb4[NR];
-        auto fetch_step = [&](int K, T *xa, T *xb, T *ya, T *yb) {
-            fetch_u(2 * K + 1, xa);
-            fetch_u(2 * K + 2, xb);
-            load_f(2 * K, ya);
-            load_f(2 * K + 1, yb);
-        };
-        if (Kb + 1 <= Ke) fetch_step(Kb + 1, ua2, ub2, fa2, fb2);
-        if (DEPTH >= 3 && Kb + 2 <= Ke) fetch_step(Kb + 2, ua3, ub3, fa3, fb3);
-        if (DEPTH >= 4 && Kb + 3 <= Ke) fetch_step(Kb + 3, ua4, ub4, fa4, fb4);
-        auto step = [&](int K, T *xa, T *xb, T *ya, T *yb) {
-            store_u(2 * K + 1, xa);
-            store_u(2 * K + 2, xb);
-            T fc0[NR], fc1[NR];
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                fc0[r] = ya[r];
-                fc1[r] = yb[r];
-            }
-            if (K + DEPTH <= Ke) fetch_step(K + DEPTH, xa, xb, ya, yb);   // into the set just emptied
-            __syncthreads();
-            resid(2 * K, fc0);
-            resid(2 * K + 1, fc1);
-            __syncthreads();
-            restrict_plane(K);
-        };
-        for (int K = Kb; K <= Ke; K += DEPTH) {
-            step(K, ua, ub, fa, fb);
-            if (K + 1 <= Ke) step(K + 1, ua2, ub2, fa2, fb2);
-            if (DEPTH >= 3 && K + 2 <= Ke) step(K + 2, ua3, ub3, fa3, fb3);
-            if (DEPTH >= 4 && K + 3 <= Ke) step(K + 3, ua4, ub4, fa4, fb4);
-        }
-    }
-}
-
 // Which residual-restriction kernel a fine level of n points uses (0: per-node
-// gather, 1: 8x8x4 LDS tile, 2/3/4: z-march over chunks of 4/8/16 coarse planes,
-// 5: 4x4x4, 6: 4x4x2 LDS tiles, 7/8: whole-column z-march of 32x8 / 64x4
-// columns with 512 threads loading two steps ahead, 9: 32x8 columns over
-// 64-plane chunks, 10/11: 32x8 whole columns loading three / four steps
-// ahead), per
-// precision; set by the autotuner, gather by default.
+// gather, 1: 8x8x4 LDS tile, 2/3/4: z-march of 16x8 columns over chunks of 4/8/16
+// coarse planes, 5: 4x4x4, 6: 4x4x2 LDS tiles, 7: z-march of whole 32x8 columns,
+// 10/11/9/8: of 32x8 columns over chunks of 16/32/64/128 planes), per precision;
+// set by the autotuner, gather by default.
 static int g_rr_variant[2][11] = {{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}};
 
 template <typename T>
@@ -1864,47 +1636,9 @@ void launch_residual_restrict_variant(int nf, double h, const T *f, const T *u, 
         hipLaunchKernelGGL(residual_restrict_k<T>, g, blk, 0, s, nf, T(1.0 / (h * h)), f, u, fc, uc0, uc1, zb, zu);
         return;
     }
-    if (variant >= 2 && variant <= 4) {   // z-march with chunks of 4, 8 or 16 coarse planes
-        constexpr int CX = 16, CY = 8;
-        const int kc = variant == 2 ? 4 : (variant == 3 ? 8 : 16);
-        const int tx = (nc + CX - 1) / CX, ty = (nc + CY - 1) / CY, tzc = (nc - 2 + kc - 1) / kc;
-        const dim3 g((unsigned)((size_t)tx * ty * tzc * nb));
-        hipLaunchKernelGGL((residual_restrict_zmarch_k<T, CX, CY>), g, dim3(256), 0, s, nf, T(1.0 / (h * h)), f, u, fc,
-                           uc0, uc1, tx, ty, tzc, kc, zu);
-        return;
-    }
-    if (variant >= 7 && variant <= 11) {   // tiles from coarse column 1 (see residual_restrict_zmarch_k)
-        const T ih2 = T(1.0 / (h * h));
-        if (variant == 8) {   // 64 x 4 columns, whole column, two steps ahead, 512 threads
-            constexpr int CX = 64, CY = 4;
-            const int tx = (nc - 1 + CX - 1) / CX, ty = (nc - 1 + CY - 1) / CY;
-            const dim3 g((unsigned)((size_t)tx * ty * nb));
-            hipLaunchKernelGGL((residual_restrict_zmarch_k<T, CX, CY, 512, true, 2>), g, dim3(512), 0, s, nf, ih2, f,
-                               u, fc, uc0, uc1, tx, ty, 1, nc - 2, zu);
-            return;
-        }
-        constexpr int CX = 32, CY = 8;
-        const int tx = (nc - 1 + CX - 1) / CX, ty = (nc - 1 + CY - 1) / CY;
-        if (variant == 7) {   // 32 x 8 columns, whole column, two steps ahead, 512 threads
-            const dim3 g((unsigned)((size_t)tx * ty * nb));
-            hipLaunchKernelGGL((residual_restrict_zmarch_k<T, CX, CY, 512, true, 2>), g, dim3(512), 0, s, nf, ih2, f,
-                               u, fc, uc0, uc1, tx, ty, 1, nc - 2, zu);
-            return;
-        }
-        if (variant == 10 || variant == 11) {   // 32 x 8 columns, whole column, three / four steps ahead
-            const dim3 g((unsigned)((size_t)tx * ty * nb));
-            if (variant == 10)
-                hipLaunchKernelGGL((residual_restrict_zmarch_k<T, CX, CY, 512, true, 3>), g, dim3(512), 0, s, nf, ih2,
-                                   f, u, fc, uc0, uc1, tx, ty, 1, nc - 2, zu);
-            else
-                hipLaunchKernelGGL((residual_restrict_zmarch_k<T, CX, CY, 512, true, 4>), g, dim3(512), 0, s, nf, ih2,
-                                   f, u, fc, uc0, uc1, tx, ty, 1, nc - 2, zu);
-            return;
-        }
-        const int kc = 64, tzc = (nc - 2 + kc - 1) / kc;   // 32 x 8 columns, 64-plane chunks, 256 threads
-        const dim3 g((unsigned)((size_t)tx * ty * tzc * nb));
-        hipLaunchKernelGGL((residual_restrict_zmarch_k<T, CX, CY, 256, true, 1>), g, dim3(256), 0, s, nf, ih2, f, u,
-                           fc, uc0, uc1, tx, ty, tzc, kc, zu);
+    if ((variant >= 2 && variant <= 4) || variant >= 7) {   // z-march over 16 x 8 or 32 x 8 coarse columns
+        constexpr int chunk[kRrVariants] = {0, 0, 4, 8, 16, 0, 0, 0, 128, 64, 16, 32};
+        launch_rr_march<T>(nf, h, f, u, fc, uc0, uc1, variant >= 7, chunk[variant], s, nb, zu);
         return;
     }
     if (variant == 5) {   // 4 x 4 x 4 coarse tiles
