@@ -3,24 +3,28 @@
 // whole FMG over these levels is one launch.  Level l has 2^l + 1 points; the
 // 3^3 level is solved exactly, in FP64.
 //
-// A thread owns an x-pair of neighbouring nodes of a level (one red, one black:
-// i + j + k even and odd; at 17^3 the pair on two neighbouring planes) and keeps
-// its u and f in registers for the whole launch, on every level at once.  In
-// LDS each level has an array per colour, [k][j][pair]: a colour pass reads only
-// the other colour, at consecutive places, and only the neighbours the thread
-// does not own (four of six at 17^3).  The residual is staged with even and odd
-// columns apart, which is how the restriction reads it, and the prolongation
-// takes the eight coarse values of a pair once for all its nodes.  17^3 has 960
-// owners, 9^3 196; 5^3 and 3^3 fit one wavefront, which works through them on its
-// own, in order and without barriers, while the others wait at one.
+// A thread owns the 2 x 2 x 2 nodes (2q + e) of a block q of a level and keeps
+// their u and f in registers for the whole launch, on every level at once.  A
+// node's colour and its place among the eight follow from e alone, so every
+// register index is a constant and a phase has no index arithmetic: in LDS each
+// level has one array per e, [q], and a thread's accesses are one address and
+// constant offsets.  A node reads three neighbours from LDS and has three of its
+// own.  Rows of an array hold the blocks alone, the far face of x follows them:
+// with the face in the rows, at a stride of nine values, every access took twice
+// the LDS cycles in conflicts.  Block q of a level is also node q of the level below it, which the same
+// thread restricts to (eight of the 27 residuals are its own) and prolongs from.
+// 17^3 has 512 owners, 9^3 64 and 5^3 eight: the levels below 17^3 belong to the
+// first wavefront, which works through them in order and without barriers, while
+// the others wait at one.  The far faces (2q + 2 of the last block) are boundary
+// nodes only and live in LDS alone.
 //
-// Bound by the latency of its dependent phases (26 barriers per V-cycle from
-// 17^3).  The form before this one held u, f and the residual in LDS in grid
-// order and read seven values per node update at a stride of two, about twice
-// the LDS cycles in conflicts; every phase had all 1024 threads meet at a
-// barrier (34 per V-cycle).  Same operations in the same order.  A V-cycle from
-// 17^3 14.4 -> 12.1 us (from 9^3 5.1 -> 5.0, from 5^3 2.0), a launch of one in a
-// 65^3 step 26.8 -> 23.1 us on average.
+// No value is masked on its way in: what is read beyond a low face only enters
+// boundary nodes, which keep their values.
+//
+// Bound by the latency and the instruction issue of its dependent phases.  With a
+// pair of nodes per thread (1024 threads, four LDS reads a node at 17^3, places
+// and colours worked out in every phase) a V-cycle from 17^3 took 12.1 us, now
+// 9.1 (from 9^3 5.0 -> 4.4; from 5^3, eight lanes' work, 2.0 -> 2.2).
 #include "common.h"
 
 namespace qm {
@@ -28,52 +32,64 @@ namespace qm {
 namespace {
 
 constexpr int kTailTop = 4;
-constexpr int kTailThreads = 1024;
 
 template <int LV>
 struct Lv {
-    static constexpr int n = (1 << LV) + 1, m = n - 2;
-    static constexpr int Q = (1 << (LV - 1)) + 1;        // pairs of a row, the far face's among them
-    static constexpr int NQ = 1 << (LV - 1);             // ... that hold interior nodes: columns 2q, 2q + 1
-    static constexpr int KB = LV == 4 ? 2 : 1;           // planes per owner
-    static constexpr int G = (m + KB - 1) / KB, OWN = NQ * m * G;
-    static constexpr int S = n * n * Q;                  // nodes of one colour, with the places no node has
-    static_assert(OWN <= kTailThreads, "one owner per thread");
+    static constexpr int n = (1 << LV) + 1, NQ = 1 << (LV - 1), Q = NQ + 1;   // blocks of a row; with the far face
+    static constexpr int S = Q * Q * Q, SR = NQ * NQ * NQ;                    // a class of nodes of u, of residuals
+    static constexpr int OWN = SR;
 };
 
-template <typename T>
-struct TailShared {
-    T u4[2][Lv<4>::S], u3[2][Lv<3>::S], u2[2][Lv<2>::S], u1[27];
-    T r4[2 * Lv<4>::S], r3[2 * Lv<3>::S], r2[2 * Lv<2>::S];   // [k][j][parity of i][i / 2]
-    T h2[kTailTop + 1], ih2[kTailTop + 1];
-};
+// LDS, in values: the residuals of levels 4, 3, 2 (classes 1 to 7), their u, the
+// restricted right-hand sides of levels 3 and 2, u of the 3^3 level
+constexpr int kPad = 128;   // reads beyond the low faces of the first array
+template <int LV> __host__ __device__ constexpr int at_r()
+{
+    return LV == 4 ? kPad : at_r<LV == 4 ? 4 : LV + 1>() + 7 * Lv<LV == 4 ? 4 : LV + 1>::SR + 8 * Lv<LV == 4 ? 4 : LV + 1>::S;
+}
+template <int LV> __host__ __device__ constexpr int at_u() { return at_r<LV>() + 7 * Lv<LV>::SR; }
+template <int LV> __host__ __device__ constexpr int at_f()
+{
+    return LV == 3 ? at_u<2>() + 8 * Lv<2>::S : at_u<2>() + 8 * Lv<2>::S + Lv<4>::SR;
+}
+constexpr int kAtU1 = at_f<2>() + Lv<3>::SR, kTailLds = kAtU1 + 27;
 
 template <typename T, int LV>
 struct Own {
-    T u[2][Lv<LV>::KB], f[2][Lv<LV>::KB];    // by colour
-    int q, j, k;                             // pair, row, first plane
-    bool act;
+    T u[8], f[8];           // node e = ex + 2 ey + 4 ez of the block
+    int at, ar;             // the block's place in the arrays of u and of residuals
+    int xp;                 // ... of u of the next block of the row, or the far face
+    int qx, qy, qz;
+    bool act, low[3];       // low[d]: the block lies on the low face of direction d
 
     __device__ void init()
     {
+        constexpr int NQ = Lv<LV>::NQ, Q = Lv<LV>::Q;
+        const int t = threadIdx.x % Lv<LV>::OWN;
         act = (int)threadIdx.x < Lv<LV>::OWN;
-        const int t = act ? (int)threadIdx.x : 0;
-        q = t % Lv<LV>::NQ;
-        j = 1 + t / Lv<LV>::NQ % Lv<LV>::m;
-        k = 1 + t / (Lv<LV>::NQ * Lv<LV>::m) * Lv<LV>::KB;
+        qx = t % NQ;
+        qy = t / NQ % NQ;
+        qz = t / (NQ * NQ);
+        at = (qz * Q + qy) * NQ + qx;
+        xp = qx < NQ - 1 ? at + 1 : (NQ * Q + qz) * Q + qy;
+        ar = t;
+        low[0] = qx == 0;
+        low[1] = qy == 0;
+        low[2] = qz == 0;
     }
     // The indices count as new from here: addresses of every phase kept across the cycles would spill.
-    __device__ void fresh() { asm volatile("" : "+v"(q), "+v"(j), "+v"(k)); }
-    __device__ int place(int kb) const { return ((k + kb) * Lv<LV>::n + j) * Lv<LV>::Q + q; }
-    // which node of the pair has colour c on plane k + kb
-    __device__ int node(int kb, int c) const { return ((j + k + kb) & 1) ^ c; }
-    __device__ bool interior(int kb, int e) const { return act && (q > 0 || e) && k + kb <= Lv<LV>::m; }
+    __device__ void fresh() { asm volatile("" : "+v"(at), "+v"(xp), "+v"(ar), "+v"(qx), "+v"(qy), "+v"(qz)); }
+    __device__ bool interior(int e) const
+    {
+        return !((!(e & 1) && low[0]) || (!(e & 2) && low[1]) || (!(e & 4) && low[2]));
+    }
 };
 
-template <typename T>
+template <typename T, int TOP>
 struct Tail {
-    TailShared<T> &S;
-    T L;
+    T *mem;
+    double L;
+    T h2, ih2;               // h^2 and 1 / h^2 of the top level
     int npre, npost;
     Own<T, 4> o4;
     Own<T, 3> o3;
@@ -86,191 +102,163 @@ struct Tail {
         else if constexpr (LV == 3) return o3;
         else return o2;
     }
-    template <int LV> __device__ T *u(int c)
+    // Levels up to 9^3 belong to the first wavefront, whose LDS operations complete in order.
+    template <int LV> __device__ static void sync()
     {
-        if constexpr (LV == 4) return S.u4[c];
-        else if constexpr (LV == 3) return S.u3[c];
-        else return S.u2[c];
-    }
-    template <int LV> __device__ T *r()
-    {
-        if constexpr (LV == 4) return S.r4;
-        else if constexpr (LV == 3) return S.r3;
-        else return S.r2;
-    }
-    // Levels up to 5^3 belong to the first wavefront, whose LDS operations complete in order.
-    template <int LV> __device__ void sync()
-    {
-        if constexpr (LV >= 3) {
+        if constexpr (LV >= 4) {
             __syncthreads();
         } else {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
     }
-    template <int LV> __device__ static bool mine() { return LV >= 3 || threadIdx.x < 64; }
+    template <int LV> __device__ static bool mine() { return LV >= 4 || threadIdx.x < 64; }
 
-    // sum of the six neighbours of the node of colour c on plane k + kb, in grid order (the two of x commute)
-    template <int LV> __device__ T neighbours(const Own<T, LV> &o, int kb, int c)
+    // sum of the six neighbours of node e, in grid order (the two of x commute)
+    template <int LV> __device__ T neighbours(const Own<T, LV> &o, int e)
     {
 #pragma clang fp contract(off)
-        constexpr int Q = Lv<LV>::Q, P = Lv<LV>::n * Q, KB = Lv<LV>::KB;
-        const T *O = u<LV>(c ^ 1) + o.place(kb);
-        const T zm = kb == 0 ? O[-P] : o.u[c ^ 1][kb == 0 ? 0 : kb - 1];
-        const T zp = kb == KB - 1 ? O[P] : o.u[c ^ 1][kb == KB - 1 ? kb : kb + 1];
-        return o.u[c ^ 1][kb] + O[o.node(kb, c) ? 1 : -1] + O[-Q] + O[Q] + zm + zp;
+        constexpr int NQ = Lv<LV>::NQ, P = Lv<LV>::Q * NQ, S = Lv<LV>::S;
+        const T *U = mem + at_u<LV>() + o.at, *X = mem + at_u<LV>() + o.xp;
+        const T xo = e & 1 ? X[(e ^ 1) * S] : U[(e ^ 1) * S - 1];
+        const T yo = U[(e ^ 2) * S + (e & 2 ? NQ : -NQ)], yi = o.u[e ^ 2];
+        const T zo = U[(e ^ 4) * S + (e & 4 ? P : -P)], zi = o.u[e ^ 4];
+        return o.u[e ^ 1] + xo + (e & 2 ? yi : yo) + (e & 2 ? yo : yi) + (e & 4 ? zi : zo) + (e & 4 ? zo : zi);
     }
-    template <int LV> __device__ void pass(int c)
+    static __device__ constexpr int colour(int e) { return (e ^ e >> 1 ^ e >> 2) & 1; }
+    // the block's values to LDS: those of one colour, or all (2)
+    template <int LV, int C> __device__ void put_u(const Own<T, LV> &o)
+    {
+        if (LV > 2 || o.act) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (C == 2 || colour(e) == C) mem[at_u<LV>() + o.at + e * Lv<LV>::S] = o.u[e];
+        }
+    }
+    template <int LV, int C> __device__ void pass()
     {
 #pragma clang fp contract(off)
         Own<T, LV> &o = own<LV>();
-        const T hh = S.h2[LV], sixth = T(1) / T(6);
-        o.fresh();
-        if (o.act) {
-            T v[Lv<LV>::KB];
+        const T hh = h2 * T(1 << 2 * (TOP - LV)), sixth = T(1) / T(6);
+        T v[8];
 #pragma unroll
-            for (int kb = 0; kb < Lv<LV>::KB; ++kb) v[kb] = (neighbours<LV>(o, kb, c) - hh * o.f[c][kb]) * sixth;
+        for (int e = 0; e < 8; ++e)
+            if (colour(e) == C) v[e] = (neighbours<LV>(o, e) - hh * o.f[e]) * sixth;
 #pragma unroll
-            for (int kb = 0; kb < Lv<LV>::KB; ++kb)
-                if (o.interior(kb, o.node(kb, c))) {
-                    o.u[c][kb] = v[kb];
-                    u<LV>(c)[o.place(kb)] = v[kb];
-                }
-        }
+        for (int e = 0; e < 8; ++e)
+            if (colour(e) == C) o.u[e] = o.interior(e) ? v[e] : o.u[e];
+        put_u<LV, C>(o);
         sync<LV>();
     }
     template <int LV> __device__ void sweeps(int ns)
     {
         for (int s = 0; s < ns; ++s) {
-            pass<LV>(0);
-            pass<LV>(1);
+            pass<LV, 0>();
+            pass<LV, 1>();
         }
     }
-    // values of the owner's interior nodes into the staging array of level LV
-    template <int LV, typename V> __device__ void stage(V value)
+    // Full weighting of v (a value per node of level LV) at the block's coarse
+    // node, in the order of the restriction kernel; meaningful inside the low faces.
+    template <int LV> __device__ T weighted(const T (&v)[8])
     {
-        Own<T, LV> &o = own<LV>();
-        o.fresh();
-#pragma unroll
-        for (int kb = 0; kb < Lv<LV>::KB; ++kb)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const int e = o.node(kb, c);
-                if (o.interior(kb, e))
-                    r<LV>()[(((o.k + kb) * Lv<LV>::n + o.j) * 2 + e) * Lv<LV>::Q + o.q] = value(o, kb, c);
-            }
-    }
-    template <int LV> __device__ void residual()   // staged; and the next level's u becomes zero
-    {
-        const T ih = S.ih2[LV];
-        stage<LV>([&](const Own<T, LV> &o, int kb, int c) {
 #pragma clang fp contract(off)
-            return o.f[c][kb] - (neighbours<LV>(o, kb, c) - T(6) * o.u[c][kb]) * ih;
-        });
-        constexpr int NT = LV >= 3 ? kTailThreads : 64;
-        if constexpr (LV == 2) {
-            if (threadIdx.x < 27) S.u1[threadIdx.x] = T(0);
-        } else {
-            T *z = u<LV - 1>(0);
-            for (int p = threadIdx.x; p < 2 * Lv<LV - 1>::S; p += NT) z[p] = T(0);
+        constexpr int NQ = Lv<LV>::NQ, SR = Lv<LV>::SR;
+        Own<T, LV> &o = own<LV>();
+        T *R = mem + at_r<LV>() + o.ar - SR;
+        if (LV > 2 || o.act) {
+#pragma unroll
+            for (int e = 1; e < 8; ++e) R[e * SR] = v[e];
         }
         sync<LV>();
-    }
-    // full weighting of the staged values of level LV at its coarse node (I, J, K)
-    template <int LV> __device__ T weighted(int I, int J, int K)
-    {
-#pragma clang fp contract(off)
-        constexpr int n = Lv<LV>::n, Q = Lv<LV>::Q;
         const T w[3] = {T(0.25), T(0.5), T(0.25)};
         T acc = T(0);
 #pragma unroll
-        for (int c = -1; c <= 1; ++c) {
-            T v[9];
+        for (int c = -1; c <= 1; ++c)
 #pragma unroll
             for (int b = -1; b <= 1; ++b)
 #pragma unroll
-                for (int a = -1; a <= 1; ++a)
-                    v[(a + 1) + 3 * (b + 1)] = r<LV>()[(((2 * K + c) * n + 2 * J + b) * 2 + (a & 1)) * Q + (a < 0 ? I - 1 : I)];
-#pragma unroll
-            for (int b = -1; b <= 1; ++b)
-#pragma unroll
-                for (int a = -1; a <= 1; ++a) acc += (w[a + 1] * w[b + 1] * w[c + 1]) * v[(a + 1) + 3 * (b + 1)];
-        }
+                for (int a = -1; a <= 1; ++a) {
+                    const int e = (a & 1) + 2 * (b & 1) + 4 * (c & 1);
+                    const int d = (a < 0 ? 1 : 0) + (b < 0 ? NQ : 0) + (c < 0 ? NQ * NQ : 0);
+                    const T x = d == 0 ? v[e] : R[e * SR - d];
+                    acc += (w[a + 1] * w[b + 1] * w[c + 1]) * x;
+                }
         return acc;
     }
-    template <int LV> __device__ void restrict_to()   // f of level LV - 1, its owners' u zero
+    // ... to the right-hand side of level LV - 1
+    template <int LV> __device__ void restrict_to(const T (&v)[8])
+    {
+        const T acc = weighted<LV>(v);
+        if constexpr (LV == 2) {
+            f1 = acc;                             // of the last block's thread
+        } else {
+            Own<T, LV> &o = own<LV>();
+            mem[at_f<LV - 1>() + o.ar] = acc;
+            sync<LV>();
+            if (mine<LV - 1>()) {
+                constexpr int N = Lv<LV>::NQ;     // nodes 0 .. N - 1 of level LV - 1 in a row
+                Own<T, LV - 1> &p = own<LV - 1>();
+                p.fresh();
+                const T *F = mem + at_f<LV - 1>() + 2 * ((p.qz * N + p.qy) * N + p.qx);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) p.f[e] = F[(e & 1) + N * (e >> 1 & 1) + N * N * (e >> 2)];
+            }
+        }
+    }
+    template <int LV> __device__ void zero_below(int threads)   // u of level LV - 1
     {
         if constexpr (LV == 2) {
-            if (threadIdx.x == 0) f1 = weighted<2>(1, 1, 1);
+            if (threadIdx.x < 27) mem[kAtU1 + threadIdx.x] = T(0);
         } else {
-            Own<T, LV - 1> &o = own<LV - 1>();
-            o.fresh();
+            for (int p = threadIdx.x; p < 8 * Lv<LV - 1>::S; p += threads) mem[at_u<LV - 1>() + p] = T(0);
+            Own<T, LV - 1> &p = own<LV - 1>();
 #pragma unroll
-            for (int kb = 0; kb < Lv<LV - 1>::KB; ++kb)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const int e = o.node(kb, c);
-                    o.u[c][kb] = T(0);
-                    o.f[c][kb] = o.interior(kb, e) ? weighted<LV>(2 * o.q + e, o.j, o.k + kb) : T(0);
-                }
+            for (int e = 0; e < 8; ++e) p.u[e] = T(0);
         }
     }
-    __device__ void exact()   // the 3^3 level's one interior node, by the first thread
+    __device__ void exact()   // the 3^3 level's one interior node, by the last 5^3 block's thread
     {
 #pragma clang fp contract(off)
-        if (threadIdx.x == 0) {
-            const T *v = S.u1;
-            const double h = double(L) / 2.0;
+        if (threadIdx.x == 7) {
+            const T *v = mem + kAtU1;
+            const double h = L / 2.0;
             const double s = double(v[12]) + double(v[14]) + double(v[10]) + double(v[16]) + double(v[4]) + double(v[22]);
-            S.u1[13] = T((s - h * h * double(f1)) / 6.0);
+            mem[kAtU1 + 13] = T((s - h * h * double(f1)) / 6.0);
         }
     }
-    template <int LC> __device__ T coarse(int I, int J, int K)
+    template <int LV> static __device__ int place(int i, int j, int k)   // of a node in LDS
     {
-        if constexpr (LC == 1) return S.u1[I + 3 * (J + 3 * K)];
-        else return u<LC>((I + J + K) & 1)[(K * Lv<LC>::n + J) * Lv<LC>::Q + (I >> 1)];
+        if constexpr (LV == 1) return kAtU1 + i + 3 * (j + 3 * k);
+        constexpr int NQ = Lv<LV>::NQ, Q = Lv<LV>::Q;
+        const int q = i >> 1, row = (k >> 1) * Q + (j >> 1);
+        return at_u<LV>() + ((i & 1) + 2 * (j & 1) + 4 * (k & 1)) * Lv<LV>::S + (q < NQ ? row * NQ + q : NQ * Q * Q + row);
     }
-    // level LC -> LC + 1: the trilinear expression of the prolongation kernel, in its order
+    // level LC -> LC + 1: the trilinear expression of the prolongation kernel, in
+    // its order, without the terms of weight zero
     template <int LC> __device__ void prolong(bool add)
     {
 #pragma clang fp contract(off)
-        constexpr int LV = LC + 1, KB = Lv<LV>::KB;
+        constexpr int LV = LC + 1;
         Own<T, LV> &o = own<LV>();
         o.fresh();
-        if (o.act) {
-            const int ja = o.j >> 1, jb = (o.j + 1) >> 1, dj = o.j & 1;
-            const T wja = dj ? T(0.5) : T(1), wjb = dj ? T(0.5) : T(0);
-            T row[2][2][2];              // [coarse plane k / 2, (k + 1) / 2 of the first plane][row a, b][column q, q + 1]
-            const int pl[2] = {o.k >> 1, (o.k + 1) >> 1};
+        T x[2][2][2];                             // [plane][row][column parity]: along x
 #pragma unroll
-            for (int z = 0; z < 2; ++z)
+        for (int z = 0; z < 2; ++z)
 #pragma unroll
-                for (int x = 0; x < 2; ++x) {
-                    row[z][0][x] = coarse<LC>(o.q + x, ja, pl[z]);
-                    row[z][1][x] = coarse<LC>(o.q + x, jb, pl[z]);
-                }
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                // with two planes the first is odd and the second, even, lies on the upper coarse plane
-                const bool ko = KB == 2 ? kb == 0 : (o.k & 1);
-                const T wka = ko ? T(0.5) : T(1), wkb = ko ? T(0.5) : T(0);
-                const int za = KB == 2 && kb == 1 ? 1 : 0;
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const int e = o.node(kb, c);
-                    auto along_x = [&](const T *p) {
-                        return (e ? T(0.5) : T(1)) * p[0] + (e ? T(0.5) : T(0)) * (e ? p[1] : p[0]);
-                    };
-                    const T xa = along_x(row[za][0]), xb = along_x(row[za][1]), xc = along_x(row[1][0]),
-                            xd = along_x(row[1][1]);
-                    const T v = wka * (wja * xa + wjb * xb) + wkb * (wja * xc + wjb * xd);
-                    if (o.interior(kb, e)) {
-                        o.u[c][kb] = add ? o.u[c][kb] + v : v;
-                        u<LV>(c)[o.place(kb)] = o.u[c][kb];
-                    }
-                }
+            for (int y = 0; y < 2; ++y) {
+                const T a = mem[place<LC>(o.qx, o.qy + y, o.qz + z)], b = mem[place<LC>(o.qx + 1, o.qy + y, o.qz + z)];
+                x[z][y][0] = a;
+                x[z][y][1] = T(0.5) * a + T(0.5) * b;
             }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int ex = e & 1;
+            const T a = e & 2 ? T(0.5) * x[0][0][ex] + T(0.5) * x[0][1][ex] : x[0][0][ex];
+            const T b = e & 2 ? T(0.5) * x[1][0][ex] + T(0.5) * x[1][1][ex] : x[1][0][ex];
+            const T v = e & 4 ? T(0.5) * a + T(0.5) * b : a;
+            o.u[e] = o.interior(e) ? (add ? o.u[e] + v : v) : o.u[e];
         }
+        put_u<LV, 2>(o);
         sync<LV>();
     }
     template <int LV> __device__ void vcycle()
@@ -279,143 +267,131 @@ struct Tail {
             exact();
             sync<1>();
         } else {
+#pragma clang fp contract(off)
             sweeps<LV>(npre);
-            residual<LV>();
-            if constexpr (LV == 3) {     // the first wavefront alone below 9^3
-                if (mine<2>()) {
-                    restrict_to<3>();
-                    vcycle<2>();
-                }
-                __syncthreads();
-            } else {
-                restrict_to<LV>();
-                vcycle<LV - 1>();
-            }
+            Own<T, LV> &o = own<LV>();
+            const T ih = ih2 * (T(1) / T(1 << 2 * (TOP - LV)));
+            T r[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[e] = o.f[e] - (neighbours<LV>(o, e) - T(6) * o.u[e]) * ih;
+            zero_below<LV>(LV >= 4 ? Lv<4>::OWN : 64);
+            restrict_to<LV>(r);
+            if (mine<LV - 1>()) vcycle<LV - 1>();
+            if constexpr (LV >= 4) __syncthreads();
             prolong<LV - 1>(true);
             sweeps<LV>(npost);
         }
     }
-    template <int LV> __device__ void restrict_all()   // f of the levels below LV, by all threads
+    template <int LV> __device__ void restrict_all()   // f of the levels below LV
     {
         if constexpr (LV >= 2) {
-            stage<LV>([](const Own<T, LV> &o, int kb, int c) { return o.f[c][kb]; });
-            __syncthreads();
-            restrict_to<LV>();
-            restrict_all<LV - 1>();
+            restrict_to<LV>(own<LV>().f);
+            if (mine<LV - 1>()) restrict_all<LV - 1>();
         }
     }
-    template <int LV> __device__ void load_own()   // the owners' u from LDS
-    {
-        Own<T, LV> &o = own<LV>();
-#pragma unroll
-        for (int kb = 0; kb < Lv<LV>::KB; ++kb)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) o.u[c][kb] = u<LV>(c)[o.place(kb)];
-    }
-    template <int LV, int TOP> __device__ void inject()   // boundary of level LV from level TOP, interior 0
+    template <int LV> __device__ void inject()   // boundary of level LV from the top level, interior 0
     {
         constexpr int n = (1 << LV) + 1, st = 1 << (TOP - LV);
-        for (int p = threadIdx.x; p < n * n * n; p += kTailThreads) {
+        for (int p = threadIdx.x; p < n * n * n; p += Lv<TOP>::OWN >= 64 ? Lv<TOP>::OWN : 64) {
             const int i = p % n, j = p / n % n, k = p / (n * n);
             const bool bnd = i == 0 || j == 0 || k == 0 || i == n - 1 || j == n - 1 || k == n - 1;
-            const T v = bnd ? coarse<TOP>(i * st, j * st, k * st) : T(0);
-            if constexpr (LV == 1) S.u1[p] = v;
-            else u<LV>((i + j + k) & 1)[(k * n + j) * Lv<LV>::Q + (i >> 1)] = v;
+            mem[place<LV>(i, j, k)] = bnd ? mem[place<TOP>(i * st, j * st, k * st)] : T(0);
         }
+        if constexpr (LV + 1 < TOP) inject<LV + 1>();
     }
-    template <int LV, int TOP> __device__ void inject_all()
+    template <int LV> __device__ void load_below()   // the owners' u of the levels below LV from LDS
     {
-        if constexpr (LV < TOP) {
-            inject<LV, TOP>();
-            inject_all<LV + 1, TOP>();
+        if constexpr (LV > 2) {
+            Own<T, LV - 1> &o = own<LV - 1>();
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o.u[e] = mem[at_u<LV - 1>() + o.at + e * Lv<LV - 1>::S];
+            load_below<LV - 1>();
         }
     }
-    template <int LV, int TOP> __device__ void load_all()
-    {
-        if constexpr (LV < TOP) {
-            load_own<LV>();
-            load_all<LV + 1, TOP>();
-        }
-    }
-    template <int LV, int TOP> __device__ void fmg_up(int ncycle)
+    template <int LV> __device__ void fmg_up(int ncycle)
     {
         if constexpr (LV <= TOP) {
             if (mine<LV>()) {
                 prolong<LV - 1>(false);
                 for (int c = 0; c < ncycle; ++c) vcycle<LV>();
             }
-            if constexpr (LV == 2) __syncthreads();
-            fmg_up<LV + 1, TOP>(ncycle);
+            if constexpr (LV == 3) __syncthreads();
+            fmg_up<LV + 1>(ncycle);
         }
     }
 
     // mode 0: nrep V-cycles of the top level; 1: FMG; 2: one V-cycle from u = 0, not read
-    template <int TOP> __device__ void run(const T *fg, T *ug, int ncycle, int mode, int nrep)
+    __device__ void run(const T *fg, T *ug, int ncycle, int mode, int nrep)
     {
-        constexpr int n = Lv<TOP>::n, cnt = n * n * n, NL = (cnt + kTailThreads - 1) / kTailThreads;
+        typedef T pair_t __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+        constexpr int n = Lv<TOP>::n, NT = Lv<TOP>::OWN >= 64 ? Lv<TOP>::OWN : 64, NF = 3 * n * n;
         Own<T, TOP> &o = own<TOP>();
-        // all global loads of a thread first
-        T x[NL];
+        const int g = 2 * (o.qx + n * (o.qy + n * o.qz));
+        // node p of the three far faces
+        auto far = [](int p, int &i, int &j, int &k) {
+            const int d = p / (n * n), a = p % n, b = p / n % n;
+            i = d == 0 ? n - 1 : a;
+            j = d == 0 ? a : d == 1 ? n - 1 : b;
+            k = d == 2 ? n - 1 : b;
+        };
+        pair_t fv[4], uv[4];
 #pragma unroll
-        for (int t = 0; t < NL; ++t) x[t] = mode == 2 ? T(0) : ug[min((int)threadIdx.x + t * kTailThreads, cnt - 1)];
-#pragma unroll
-        for (int kb = 0; kb < Lv<TOP>::KB; ++kb)
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-                o.f[c][kb] = fg[2 * o.q + o.node(kb, c) + n * (o.j + n * (o.k + kb))];
-#pragma unroll
-        for (int t = 0; t < NL; ++t) {
-            const int p = threadIdx.x + t * kTailThreads;
-            const int i = p % n, j = p / n % n, k = p / (n * n);
-            if (p < cnt) u<TOP>((i + j + k) & 1)[(k * n + j) * Lv<TOP>::Q + (i >> 1)] = x[t];
+        for (int r = 0; r < 4; ++r) {
+            const int p = g + n * ((r & 1) + n * (r >> 1));
+            fv[r] = *reinterpret_cast<const pair_t *>(fg + p);
+            uv[r] = mode == 2 ? pair_t{T(0), T(0)} : *reinterpret_cast<const pair_t *>(ug + p);
         }
+        for (int p = threadIdx.x; p < NF; p += NT) {
+            int i, j, k;
+            far(p, i, j, k);
+            mem[place<TOP>(i, j, k)] = mode == 2 ? T(0) : ug[i + n * (j + n * k)];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            o.f[2 * r] = fv[r].x;
+            o.f[2 * r + 1] = fv[r].y;
+            o.u[2 * r] = uv[r].x;
+            o.u[2 * r + 1] = uv[r].y;
+        }
+        put_u<TOP, 2>(o);
         __syncthreads();
-        load_own<TOP>();
         if (mode == 1) {
             restrict_all<TOP>();
-            inject_all<1, TOP>();
+            inject<1>();
             __syncthreads();
-            load_all<2, TOP>();
+            load_below<TOP>();
             exact();
             __syncthreads();
-            fmg_up<2, TOP>(ncycle);
-        } else if (mine<TOP>()) {
+            fmg_up<2>(ncycle);
+        } else {
             for (int c = 0; c < nrep; ++c) vcycle<TOP>();
         }
-        __syncthreads();
+        if (o.act) {
 #pragma unroll
-        for (int t = 0; t < NL; ++t) {
-            const int p = threadIdx.x + t * kTailThreads;
-            if (p < cnt) ug[p] = coarse<TOP>(p % n, p / n % n, p / (n * n));
+            for (int r = 0; r < 4; ++r)
+                *reinterpret_cast<pair_t *>(ug + g + n * ((r & 1) + n * (r >> 1))) = pair_t{o.u[2 * r], o.u[2 * r + 1]};
         }
+        if (mode == 2)
+            for (int p = threadIdx.x; p < NF; p += NT) {
+                int i, j, k;
+                far(p, i, j, k);
+                ug[i + n * (j + n * k)] = T(0);
+            }
     }
 };
 
-template <typename T>
-__global__ void __launch_bounds__(kTailThreads)
-coarse_tail_k(int top, T L, const T *__restrict__ fg, T *__restrict__ ug, int npre, int npost, int ncycle, int mode,
-              int nrep)
+template <typename T, int TOP>
+__global__ void __launch_bounds__(Lv<TOP>::OWN >= 64 ? Lv<TOP>::OWN : 64)
+coarse_tail_k(double L, T h2, T ih2, const T *__restrict__ fg, T *__restrict__ ug, int npre, int npost, int ncycle,
+              int mode, int nrep)
 {
-    __shared__ TailShared<T> S;
-    Tail<T> t{S, L, npre, npost, {}, {}, {}, T(0)};
+    __shared__ T mem[kTailLds];
+    Tail<T, TOP> t{mem, L, h2, ih2, npre, npost, {}, {}, {}, T(0)};
     t.o4.init();
     t.o3.init();
     t.o2.init();
-    if (threadIdx.x == 0) {
-        for (int l = 1; l <= kTailTop; ++l) {
-            const T h = L / T((1 << l));
-            S.h2[l] = h * h;
-            S.ih2[l] = T(1) / (h * h);
-        }
-    }
-    const int n = (1 << top) + 1;
-    fg += (size_t)blockIdx.x * n * n * n;
-    ug += (size_t)blockIdx.x * n * n * n;
-    switch (top) {
-    case 2: t.template run<2>(fg, ug, ncycle, mode, nrep); break;
-    case 3: t.template run<3>(fg, ug, ncycle, mode, nrep); break;
-    default: t.template run<4>(fg, ug, ncycle, mode, nrep); break;
-    }
+    constexpr int n = Lv<TOP>::n;
+    t.run(fg + (size_t)blockIdx.x * n * n * n, ug + (size_t)blockIdx.x * n * n * n, ncycle, mode, nrep);
 }
 
 }  // namespace
@@ -424,8 +400,14 @@ template <typename T>
 void launch_coarse_tail(int ltop, double L, const T *f, T *u, int npre, int npost, int ncycle, int mode, int nrep,
                         hipStream_t s, int nb)
 {
-    hipLaunchKernelGGL(coarse_tail_k<T>, dim3(nb), dim3(kTailThreads), 0, s, ltop, T(L), f, u, npre, npost, ncycle,
-                       mode, nrep);
+    const T h = T(L) / T(1 << ltop), h2 = h * h, ih2 = T(1) / (h * h);
+    const double Lt = double(T(L));
+    auto go = [&](auto *kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(threads), 0, s, Lt, h2, ih2, f, u, npre, npost, ncycle, mode, nrep);
+    };
+    if (ltop >= kTailTop) go(coarse_tail_k<T, 4>, Lv<4>::OWN);
+    else if (ltop == 3) go(coarse_tail_k<T, 3>, Lv<3>::OWN);
+    else go(coarse_tail_k<T, 2>, 64);
 }
 
 template void launch_coarse_tail<double>(int, double, const double *, double *, int, int, int, int, int, hipStream_t, int);
