@@ -1916,26 +1916,32 @@ resid_norms_partial_k(int n, double ih2, const T *__restrict__ f, const T *__res
     }
 }
 
-// The same partial sums from a z-march: a workgroup owns a 64 x 4 column tile
-// of interior nodes and a chunk of z planes, holds three planes of u (tile
-// plus a one-node ring) in LDS and loads each plane once, with the next plane
-// and the next f values in flight while a plane is summed, so u and f are
-// read from HBM about once (the row form reads the +-z neighbour rows again,
-// from other workgroups at other times).  Each lane sums its own column; the
-// order depends only on n and the launch shape, which the launcher fixes from
-// n, so the sums are reproducible bit for bit.  Same residual expression, same
-// FP32 residual with R32.
-constexpr int kNzTX = 64, kNzTY = 4;
+// The same partial sums from a z-march: a workgroup owns a 64 x TY column tile
+// of interior nodes and a chunk of z planes, so u and f are read from HBM about
+// once (the row form reads the +-z neighbour rows again, from other workgroups
+// at other times).  A thread owns one column: its z neighbours stay in
+// registers, the x and y ones come from an LDS plane of the tile and its ring,
+// which is written a step before (two planes, one barrier a step).  A plane of u
+// is requested three steps before use, one of f two; the loads come after all
+// uses of the registers they fill, and nothing is masked on its way in: what is
+// clamped into the grid enters no interior node's residual.  Each lane sums its
+// own column; the order depends only on n and the launch shape, which the
+// launcher fixes from n, so the sums are reproducible bit for bit.  Same
+// residual expression, same FP32 residual with R32.  Bound by HBM: 513^3 FP64 445 us
+// with one plane in flight and two barriers a plane, now 407 (5.3 TB/s; with R32
+// 648 -> 625); 129^3 15.2 -> 11.9, 65^3 8.5 -> 5.9.
+constexpr int kNzTX = 64;
 
-template <typename T, bool R32>
-__global__ void __launch_bounds__(kNzTX *kNzTY)
+template <typename T, bool R32, int TY>
+__global__ void __launch_bounds__(kNzTX *TY)
 resid_norms_zmarch_k(int n, double ih2, const T *__restrict__ f, const T *__restrict__ u,
                      double *__restrict__ partial, const double *__restrict__ sc, float *__restrict__ r32, int kchunk,
                      int gx, int gy)
 {
-    constexpr int TX = kNzTX, TY = kNzTY, PX = TX + 2, PY = TY + 2, PL = PX * PY, NT = TX * TY;
-    constexpr int NL = (PL + NT - 1) / NT;
-    __shared__ double pl[3][PL];
+    constexpr int TX = kNzTX, PX = TX + 2, PL = PX * (TY + 2), NT = TX * TY;
+    constexpr int DEPTH = 4;
+    constexpr int NH = 2 * (TX + TY);      // ring nodes, without the corners
+    __shared__ T pl[2][PL + NT];           // the threads without a ring node write theirs behind the plane
     __shared__ double sh[3 * NT];
     const size_t nn = (size_t)n * n;
     f += blockIdx.y * nn * n;
@@ -1947,111 +1953,122 @@ resid_norms_zmarch_k(int n, double ih2, const T *__restrict__ f, const T *__rest
         inv_s = sc[2 * blockIdx.y + 1];
     }
     const int tid = threadIdx.x;
-    const int b = blockIdx.x, bx = b % gx, by = (b / gx) % gy, bz = b / (gx * gy);
+    const int b = (int)xcd_tile(blockIdx.x, gridDim.x), bx = b % gx, by = (b / gx) % gy, bz = b / (gx * gy);
     const int i0 = 1 + bx * TX, j0 = 1 + by * TY;
     const int kb = 1 + bz * kchunk, ke = min(kb + kchunk - 1, n - 2);
-    int goff[NL];
-#pragma unroll
-    for (int r = 0; r < NL; ++r) {
-        const int t = tid + r * NT;
-        const int i = i0 - 1 + t % PX, j = j0 - 1 + t / PX;
-        goff[r] = (t < PL && i < n && j < n) ? i + n * j : -1;
-    }
-    double v[NL];
-    auto fetch = [&](int k) {
-        const T *src = u + (size_t)k * nn;
-#pragma unroll
-        for (int r = 0; r < NL; ++r) v[r] = goff[r] >= 0 ? (double)src[goff[r]] : 0.0;
-    };
-    auto commit = [&](int k) {
-        double *D = pl[k % 3];
-#pragma unroll
-        for (int r = 0; r < NL; ++r) {
-            const int t = tid + r * NT;
-            if (t < PL) D[t] = v[r];
-        }
-    };
     const int a = tid % TX, bq = tid / TX;
     const int i = i0 + a, j = j0 + bq;
     const bool own = i <= n - 2 && j <= n - 2 && kb <= ke;
     const int c = (bq + 1) * PX + (a + 1);
-    const size_t col = (size_t)i + (size_t)n * j;
     const bool ij_edge = i == 1 || j == 1 || i == n - 2 || j == n - 2;
+    // this thread's ring node (x, y of the tile from -1), two rows and two columns
+    const int side = tid - 2 * TX;
+    const int ha = side < 0 ? a : (side < TY ? -1 : TX), hb = side < 0 ? (tid < TX ? -1 : TY) : side & (TY - 1);
+    const int hc = tid < NH ? (hb + 1) * PX + (ha + 1) : PL + tid;
+    auto place = [&](int x, int y) { return (unsigned)(min(x, n - 1) + n * min(y, n - 1)) * (unsigned)sizeof(T); };
+    const unsigned off = place(i, j), hoff = tid < NH ? place(i0 + ha, j0 + hb) : off;
+    const unsigned soff = own ? (unsigned)(i + n * j) * (unsigned)sizeof(float) : ~0u;
+    auto at = [](const T *g, unsigned o) {
+        return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(g) + o);
+    };
     double sr = 0.0, sf = 0.0, sb = 0.0;
     if (kb <= ke) {
-        {   // planes kb-1, kb, kb+1: all loads in flight before the first store
-            double w[3][NL];
+        struct set {
+            T u, h, f;   // own and ring node of plane k + 2, f of plane k
+        };
+        const T *pu = u + (size_t)(kb - 1) * nn, *pf = f + (size_t)kb * nn;
+        T wm = at(pu, off), w0 = at(pu + nn, off), wp = at(pu + 2 * nn, off);
+        const T h0 = at(pu + nn, hoff);
+        T hp = at(pu + 2 * nn, hoff);
+        auto load = [&](int k) {   // u of plane k, f of plane k - 2, clamped into the grid
+            const T *g = u + (size_t)min(k, n - 1) * nn;
+            return set{at(g, off), at(g, hoff), at(f + (size_t)min(k - 2, n - 1) * nn, off)};
+        };
+        // The store of r32: every lane issues it (the idle ones out of the buffer's
+        // range, which drops them), also once before the loop, so that the waits
+        // for the loads count it, where they would wait for a store in a branch.
+        auto put = [&](int k, float v, unsigned o) {
+            const __amdgpu_buffer_rsrc_t plane =
+                __builtin_amdgcn_make_buffer_rsrc(r32 + (size_t)k * nn, 0, (int)(nn * sizeof(float)), 0x00027000);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), plane, o, 0, 0);
+        };
+        set X[DEPTH];
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const T *src = u + (size_t)(kb - 1 + q) * nn;
-#pragma unroll
-                for (int r = 0; r < NL; ++r) w[q][r] = goff[r] >= 0 ? (double)src[goff[r]] : 0.0;
-            }
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                double *D = pl[(kb - 1 + q) % 3];
-#pragma unroll
-                for (int r = 0; r < NL; ++r) {
-                    const int t = tid + r * NT;
-                    if (t < PL) D[t] = w[q][r];
-                }
-            }
+        for (int d = 0; d < DEPTH; ++d) {
+            if (R32 && d > 0) put(kb, 0.0f, ~0u);
+            X[d] = load(kb + 2 + d);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (kb + 2 <= ke + 1) fetch(kb + 2);
-        double fv = own ? (double)f[(size_t)kb * nn + col] : 0.0;
+        pl[0][c] = w0;
+        pl[0][hc] = h0;
         __syncthreads();
-        for (int k = kb; k <= ke; ++k) {
-            const double fn = (own && k + 1 <= ke) ? (double)f[(size_t)(k + 1) * nn + col] : 0.0;
+        auto step = [&](int k, const int q, set &X) {
+            const T *Z = pl[q] + c;
+            const double um = (double)Z[-1], up = (double)Z[1], vm = (double)Z[-PX], vp = (double)Z[PX];
+            pl[1 - q][c] = wp;
+            pl[1 - q][hc] = hp;
+            const double zm = (double)wm, z0 = (double)w0, zp = (double)wp;
+            const double fv = (double)X.f;
+            const double lap = (um + up + vm + vp + zm + zp - 6.0 * z0) * ih2;
+            const double res = fv - lap;
+            if (R32) put(k, (float)(res * inv_s), soff);
             if (own) {
-                const double *M = pl[(k - 1) % 3], *Z = pl[k % 3], *Q = pl[(k + 1) % 3];
-                const double um = Z[c - 1], up = Z[c + 1], vm = Z[c - PX], vp = Z[c + PX], wm = M[c], wp = Q[c];
-                const double lap = (um + up + vm + vp + wm + wp - 6.0 * Z[c]) * ih2;
-                const double res = fv - lap;
-                if (R32) r32[(size_t)k * nn + col] = (float)(res * inv_s);
                 sr += res * res;
                 sf += fv * fv;
                 if (ij_edge || k == 1 || k == n - 2) {
                     const double bv = ((i == 1 ? um : 0.0) + (i == n - 2 ? up : 0.0) + (j == 1 ? vm : 0.0) +
-                                       (j == n - 2 ? vp : 0.0) + (k == 1 ? wm : 0.0) + (k == n - 2 ? wp : 0.0)) * ih2;
+                                       (j == n - 2 ? vp : 0.0) + (k == 1 ? zm : 0.0) + (k == n - 2 ? zp : 0.0)) * ih2;
                     sb += bv * bv;
                 }
             }
-            fv = fn;
+            wm = w0;
+            w0 = wp;
+            wp = X.u;
+            hp = X.h;
+            asm volatile("" : "+v"(wp), "+v"(hp));   // held apart from the registers loaded next
+            __builtin_amdgcn_sched_barrier(0);
+            X = load(k + 2 + DEPTH);
             __syncthreads();
-            if (k + 2 <= ke + 1) {   // plane k+2 replaces plane k-1, whose readers are past the barrier
-                commit(k + 2);
-                if (k + 3 <= ke + 1) fetch(k + 3);
-            }
-            __syncthreads();
-        }
+        };
+        int k = kb;
+        for (; k + DEPTH - 1 <= ke; k += DEPTH)
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) step(k + d, d & 1, X[d]);
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d)
+            if (k + d <= ke) step(k + d, d & 1, X[d]);
     }
     block_sum3<NT>(sh, sr, sf, sb);
     if (threadIdx.x == 0) {
-        partial[3 * blockIdx.x] = sr;
-        partial[3 * blockIdx.x + 1] = sf;
-        partial[3 * blockIdx.x + 2] = sb;
+        partial[3 * b] = sr;
+        partial[3 * b + 1] = sf;
+        partial[3 * b + 2] = sb;
     }
 }
 
-// Launch shape of the z-march norms for n: tiles of 64 x 4 columns and the
-// z-chunk that keeps the block count at most kNormBlocks (and the chunks at
-// least 8 planes); 0 blocks when the tiles alone exceed kNormBlocks (the row
-// form serves then).
+// Launch shape of the z-march norms for n: tiles of 64 x ty columns and the
+// z-chunk that keeps the block count at most kNormBlocks, or half of it with ty =
+// 8 (and the chunks at least 8 planes); 0 blocks when the tiles alone exceed
+// kNormBlocks (the row form serves then).  ty = 8 reads 1.3 values of u per node
+// instead of 1.5 and wins where HBM bounds (513^3: 407 against 420 us, with R32 625
+// against 661); with ty = 4 smaller grids have more workgroups (129^3 11.9 against
+// 12.6 us, 65^3 5.9 against 6.9).
 struct NormsShape {
-    int gx, gy, kchunk, nzc, blocks;
+    int ty, gx, gy, kchunk, nzc, blocks;
 };
 static NormsShape norms_shape(int n)
 {
     NormsShape sh;
     const int m = n - 2;
+    sh.ty = n >= 257 ? 8 : 4;
     sh.gx = (m + kNzTX - 1) / kNzTX;
-    sh.gy = (m + kNzTY - 1) / kNzTY;
+    sh.gy = (m + sh.ty - 1) / sh.ty;
     const int tiles = sh.gx * sh.gy;
     if (tiles > kNormBlocks) {
         sh.kchunk = sh.nzc = sh.blocks = 0;
         return sh;
     }
-    const int q = kNormBlocks / tiles;
+    const int q = std::max(1, kNormBlocks * 4 / sh.ty / tiles);
     sh.kchunk = std::max(8, (m + q - 1) / q);
     sh.nzc = (m + sh.kchunk - 1) / sh.kchunk;
     sh.blocks = tiles * sh.nzc;
@@ -2087,14 +2104,25 @@ __global__ void __launch_bounds__(256) norms_final_k(const double *__restrict__ 
     }
 }
 
+template <typename T, bool R32>
+static void norms_zmarch(const NormsShape &zs, int n, double h, const T *f, const T *u, double *partial, const double *sc,
+                         float *r32, hipStream_t s, int nb)
+{
+    auto go = [&](auto *kernel) {
+        hipLaunchKernelGGL(kernel, dim3(zs.blocks, nb), dim3(kNzTX * zs.ty), 0, s, n, 1.0 / (h * h), f, u, partial, sc,
+                           r32, zs.kchunk, zs.gx, zs.gy);
+    };
+    if (zs.ty == 8) go(resid_norms_zmarch_k<T, R32, 8>);
+    else go(resid_norms_zmarch_k<T, R32, 4>);
+}
+
 template <typename T>
 void launch_resid_norms(int n, double h, const T *f, const T *u, double *partial, double *out, hipStream_t s, int nb,
                         double *hout)
 {
     const NormsShape zs = norms_shape(n);
     if (zs.blocks > 0) {
-        hipLaunchKernelGGL((resid_norms_zmarch_k<T, false>), dim3(zs.blocks, nb), dim3(kNzTX * kNzTY), 0, s, n,
-                           1.0 / (h * h), f, u, partial, nullptr, nullptr, zs.kchunk, zs.gx, zs.gy);
+        norms_zmarch<T, false>(zs, n, h, f, u, partial, nullptr, nullptr, s, nb);
         hipLaunchKernelGGL(norms_final_k, dim3(nb), dim3(256), 0, s, partial, zs.blocks, out, hout);
         return;
     }
@@ -2111,8 +2139,7 @@ void launch_resid_norms_r32(int n, double h, const double *f, const double *u, d
 {
     const NormsShape zs = norms_shape(n);
     if (zs.blocks > 0) {
-        hipLaunchKernelGGL((resid_norms_zmarch_k<double, true>), dim3(zs.blocks, nb), dim3(kNzTX * kNzTY), 0, s, n,
-                           1.0 / (h * h), f, u, partial, sc, r32, zs.kchunk, zs.gx, zs.gy);
+        norms_zmarch<double, true>(zs, n, h, f, u, partial, sc, r32, s, nb);
         hipLaunchKernelGGL(norms_final_k, dim3(nb), dim3(256), 0, s, partial, zs.blocks, out, hout);
         return;
     }
