@@ -27,14 +27,18 @@
 // march starts at step K0 - 3 and ends with step K1 + 2, and what the stages
 // write further out is read by no value that is kept.
 //
-// Bound: 513^3 by HBM (two sweeps move 24 B per node once: 592 us FP64 = 5.5
+// Bound: 513^3 by HBM (two sweeps move 24 B per node once: 595 us FP64 = 5.4
 // TB/s), smaller grids by the step's issue and latency (about 0.7 us on 64x16
-// columns).  The form before this one skewed the stages two planes apart and
-// read all six neighbours from ten LDS planes of both colours, at a stride of
-// two values: 1.4 us per step, 726 us at 513^3.  FP64 pairs, before -> now (with
-// the correction): 513^3 726 -> 592 (862 -> 697) us; 257^3, there two single
-// sweeps, 203 -> 92 (235 -> 111) us in 64-plane chunks; 129^3 45 -> 24 (59 -> 31)
-// us in 8-plane chunks; 65^3, there 8^3 bricks, 18 -> 15 (26 -> 19) us.  64x16
+// columns), FP32 by both.  The form before this one skewed the stages two planes
+// apart and read all six neighbours from ten LDS planes of both colours, at a
+// stride of two values: 1.4 us per step, 726 us at 513^3.  Loads that are not
+// masked, LDS writes without a branch and, away from the column's ends, steps
+// without range checks came after: FP32 513^3 425 -> 406 us, 257^3 51 -> 45 (with
+// the correction 77 -> 68), FP64 257^3 90 -> 88 (110 -> 107).  Requesting planes
+// four steps ahead gained nothing.  FP64 pairs, before -> now (with
+// the correction): 513^3 726 -> 595 (862 -> 697) us; 257^3, there two single
+// sweeps, 203 -> 88 (235 -> 107) us in 64-plane chunks; 129^3 45 -> 19 (59 -> 26)
+// us in 8-plane chunks; 65^3, there 8^3 bricks, 18 -> 11 (26 -> 14) us.  64x16
 // columns waste least on the ring (1.7 nodes per node of the tile; 1.9 at 32x16,
 // 2.5 at 32x8) and win from 129^3 up; the small ones fill the chip at 65^3.
 #include "common.h"
@@ -59,7 +63,7 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
     constexpr int RG = 4;                                  // ring of the region a workgroup owns
     constexpr int HP = TX / 2 + RG, PY = TY + 2 * RG, NP = HP * PY;   // its x-pairs and rows
     static_assert(TX % 2 == 0 && TY % 2 == 0 && NP <= NT, "one pair of nodes per thread");
-    constexpr int PAD = HP + 1, ROW = NP + 2 * PAD;        // reads of the outermost pairs stay inside
+    constexpr int PAD = HP + 1, ROW = NT + 2 * PAD;        // reads of the outermost threads stay inside
     // coarse rows of the region (tile origins are odd): TY / 2 + 5; a coarse
     // plane is staged interpolated along x on the region's fine columns, the
     // even and the odd of a pair apart
@@ -97,24 +101,26 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
                     ok |= 1u << (2 * w + e);
             }
     }
-    const int me = PAD + min(tid, NP - 1);     // LDS place of the pair
-    // u of the pair on a plane: one 16-byte load from a base clamped into the
-    // grid's row (node il + e sits at element e + sh of the load), taken as it
-    // is and masked where it is used, two steps later, so nothing waits for the
-    // load in between; a lane with nothing to load reads the tile's corner pair
-    // (lanes of all workgroups meeting on one cache line would queue on it).
-    const bool row = tid < NP && jp >= 0 && jp < n;
-    const int ic = min(max(il, 0), n - 2), sh = il - ic;
-    const bool in0 = row && il >= 0 && il <= n - 1, in1 = row && il + 1 >= 0 && il + 1 <= n - 1;
+    const int me = PAD + tid;                  // LDS place of the pair
+    // u of the pair on a plane: one 16-byte load, its place clamped into the plane
+    // (the node before a row's first is the row before's last; a row outside the
+    // grid and threads beyond the region read the tile's corner pair, since lanes
+    // of all workgroups meeting on one cache line would queue on it).  Nothing is
+    // masked: what is no node of the grid, or lies on one of its edges, enters no
+    // update that is kept.
     const int idle = i0 + n * j0;
-    const int uoff = row ? ic + n * jp : idle;
-    auto fetch = [&](int k, pair_t &v) {
-        if (!ZERO) v = *reinterpret_cast<const pair_t *>(uin + (size_t)k * nn + uoff);
+    auto bytes = [](int p) { return (unsigned)p * (unsigned)sizeof(T); };
+    const unsigned uoff = bytes(tid < NP && jp >= 0 && jp < n ? min(max(il + n * jp, 0), n * n - 2) : idle);
+    auto at = [](const T *g, unsigned off) {
+        return *reinterpret_cast<const pair_t *>(reinterpret_cast<const char *>(g) + off);
+    };
+    auto fetch = [&](const T *g, pair_t &v) {
+        if (!ZERO) v = at(g, uoff);
     };
     // f of the pair (in range: both columns lie in the grid when either is
     // interior on the widest ring)
-    const int foff = (ok >> 6) != 0 ? il + n * jp : idle;
-    auto f_pair = [&](int k) { return *reinterpret_cast<const pair_t *>(f + (size_t)k * nn + foff); };
+    const unsigned foff = bytes((ok >> 6) != 0 ? il + n * jp : idle);
+    auto f_pair = [&](const T *g) { return at(g, foff); };
 
     // The correction's coarse data: per staged entry r of this thread (pair t %
     // HP, parity and coarse row from t / HP), the two coarse nodes its
@@ -137,12 +143,12 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
     T cv0[NXL], cv1[NXL];
     auto fetch_c = [&](int c) {   // the coarse nodes of plane c (clamped into the grid) into cv0, cv1
         if constexpr (PROLONG) {
-            const T *C = uc + (size_t)min(c, nc - 1) * nc * nc;
+            const char *C = reinterpret_cast<const char *>(uc + (size_t)min(c, nc - 1) * nc * nc);
 #pragma unroll
             for (int r = 0; r < NXL; ++r) {
-                const int o = xo[r] >= 0 ? xo[r] : cidle;
-                cv0[r] = C[o];
-                cv1[r] = C[xodd[r] && xo[r] >= 0 ? o + 1 : o];
+                const unsigned o = bytes(xo[r] >= 0 ? xo[r] : cidle);
+                cv0[r] = *reinterpret_cast<const T *>(C + o);
+                cv1[r] = *reinterpret_cast<const T *>(C + (xodd[r] && xo[r] >= 0 ? o + (unsigned)sizeof(T) : o));
             }
         }
     };
@@ -176,12 +182,11 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
     // the correction only the black one takes it: a red node's own value is
     // replaced by the first sweep's red update before any update reads it, and
     // red nodes of the outer ring are not read at all.
-    auto enter = [&](int k, const pair_t &v, int er, T &r, T &b) {
-        const T x0 = (!ZERO && in0) ? (sh == 0 ? v.x : v.y) : T(0);
-        const T x1 = (!ZERO && in1) ? (sh == 0 ? v.y : v.x) : T(0);
+    auto enter = [&](int k, const pair_t &v, int er, bool inside, T &r, T &b) {
+        const T x0 = ZERO ? T(0) : v.x, x1 = ZERO ? T(0) : v.y;
         r = er ? x1 : x0;
         b = er ? x0 : x1;
-        if (PROLONG && k >= 1 && k <= n - 2 && (er ? cin0 : cin1)) b += corr(er ^ 1, k);
+        if (PROLONG && (inside || (k >= 1 && k <= n - 2)) && (er ? cin0 : cin1)) b += corr(er ^ 1, k);
     };
 
     // Own values by plane.  Before step s: bz[0], bz[1] = black of planes s - 1, s
@@ -197,8 +202,8 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
     int er = (il + jp + s0) & 1;         // the red node of the pair on plane s0
     {
         pair_t w0 = {T(0), T(0)}, w1 = {T(0), T(0)};
-        fetch(s0 - 1, w0);
-        fetch(s0, w1);
+        fetch(uin + (size_t)(s0 - 1) * nn, w0);
+        fetch(uin + (size_t)s0 * nn, w1);
         if constexpr (PROLONG) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -207,24 +212,33 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
             }
             __syncthreads();
         }
-        enter(s0 - 1, w0, er ^ 1, r1a, bzm);
-        enter(s0, w1, er, ra, bzc);
+        enter(s0 - 1, w0, er ^ 1, false, r1a, bzm);
+        enter(s0, w1, er, false, ra, bzc);
         r1b = T(0);
     }
     fetch_c((s0 - 1) / 2 + 3);
     pair_t vA = {T(0), T(0)}, vB = {T(0), T(0)};
-    fetch(min(s0 + 1, umax), vA);
-    fetch(min(s0 + 2, umax), vB);
-    pair_t pA = f_pair(min(s0, fmax)), pB = f_pair(min(s0 + 1, fmax));
-    if (tid < NP) half[0][s0 & 1][me] = bzc;
+    // in the order of the loop's requests, which its waits count; pu and pf: the
+    // next planes of u and f, clamped into the march's (what the last steps fetch
+    // beyond them is never used)
+    auto plane = [&](const T *g, int k) { return g + (size_t)k * nn; };
+    fetch(plane(uin, min(s0 + 1, umax)), vA);
+    pair_t pA = f_pair(plane(f, min(s0, fmax)));
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(plane(uin, min(s0 + 2, umax)), vB);
+    pair_t pB = f_pair(plane(f, min(s0 + 1, fmax)));
+    __builtin_amdgcn_sched_barrier(0);
+    const T *pu = plane(uin, min(s0 + 3, umax)), *pf = plane(f, min(s0 + 2, fmax));
+    half[0][s0 & 1][me] = bzc;
     __syncthreads();
 
     const int smax = K1 + 2;   // the last black update of the second sweep is plane K1 - 1
-    T *const dst = uout + (size_t)n * jp + il;
+    T *const dst0 = uout + (ptrdiff_t)n * jp + il;
     // even: s is even (the loop's second step of a pair); with the correction,
     // an even step s stores coarse plane (s + 4) / 2, first read by fine plane
     // s + 3, which enters in step s + 2, and requests plane (s + 6) / 2
-    auto step = [&](int s, pair_t &vX, pair_t &pX, bool even) {
+    // inside: all four updates' planes are interior and plane s - 3 is one of the chunk's
+    auto step = [&](int s, pair_t &vX, pair_t &pX, const bool even, const bool inside) {
         const int p = even ? 0 : 1;      // parity of plane s, s - 2
         const int xn = me + (er ? 1 : -1);
         // the three lateral neighbours of the four updates
@@ -235,38 +249,38 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
         const unsigned m = ok >> er;
         // plane s + 1 enters
         T rn, bn;
-        enter(s + 1, vX, er ^ 1, rn, bn);
+        enter(s + 1, vX, er ^ 1, inside, rn, bn);
         const T hr0 = h2 * (er ? pX.y : pX.x), hb0 = h2 * (er ? pX.x : pX.y);
         if (PROLONG && even) {   // into the slot of coarse plane s / 2 - 1, last read in step s - 2
             store_c((s + 4) / 2);
             fetch_c((s + 6) / 2);
         }
-        // the next requests, their planes clamped into the march's (what the last
-        // steps fetch beyond them is never used)
-        fetch(min(s + 3, umax), vX);
-        pX = f_pair(min(s + 2, fmax));
+        fetch(pu, vX);
+        pX = f_pair(pf);
+        pu += s + 3 < umax ? nn : 0;
+        pf += s + 2 < fmax ? nn : 0;
         // sums in the order of the single sweep (x, y, z neighbours; the two of x commute)
-        const T r1n = (s <= n - 2 && (m & 64)) ? (bzc + ax + ad + au + bzm + bn - hr0) * sixth : ra;
-        const T b1n = (s - 1 >= 1 && s - 1 <= n - 2 && (m & 16)) ? (r1a + bx1 + bd + bu + r1b + r1n - hb1) * sixth : bzm;
-        const T r2n = (s - 2 >= 1 && s - 2 <= n - 2 && (m & 4)) ? (b1a + cx + cd + cu + b1b + b1n - hr2) * sixth : r1b;
+        const T r1n = ((inside || s <= n - 2) && (m & 64)) ? (bzc + ax + ad + au + bzm + bn - hr0) * sixth : ra;
+        const T b1n = ((inside || (s - 1 >= 1 && s - 1 <= n - 2)) && (m & 16))
+                          ? (r1a + bx1 + bd + bu + r1b + r1n - hb1) * sixth : bzm;
+        const T r2n = ((inside || (s - 2 >= 1 && s - 2 <= n - 2)) && (m & 4))
+                          ? (b1a + cx + cd + cu + b1b + b1n - hr2) * sixth : r1b;
         const T b2n = (r2a + dx + dd + du + r2b + r2n - hb3) * sixth;
-        if (tid < NP) {
-            half[0][p ^ 1][me] = bn;
-            half[1][p][me] = r1n;
-            half[2][p ^ 1][me] = b1n;
-            half[3][p][me] = r2n;
-        }
+        half[0][p ^ 1][me] = bn;
+        half[1][p][me] = r1n;
+        half[2][p ^ 1][me] = b1n;
+        half[3][p][me] = r2n;
         // plane s - 3 is final: its black node is node er of the pair
         const int k = s - 3;
-        if (k >= K0 && k < K1 && (ok & 3)) {
-            T *d = dst + (size_t)k * nn;
+        if ((inside || (k >= K0 && k < K1)) && (ok & 3)) {
+            T *dst = dst0 + (size_t)k * nn;
             if ((ok & 3) == 3) {
                 pair_t o;
                 o.x = er ? r2a : b2n;
                 o.y = er ? b2n : r2a;
-                *reinterpret_cast<pair_t *>(d) = o;
+                *reinterpret_cast<pair_t *>(dst) = o;
             } else {                     // one node of the pair is on the far face
-                d[ok & 2 ? 1 : 0] = (er != 0) == ((ok & 2) != 0) ? b2n : r2a;
+                dst[ok & 2 ? 1 : 0] = (er != 0) == ((ok & 2) != 0) ? b2n : r2a;
             }
         }
         bzm = bzc;
@@ -286,12 +300,26 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
         er ^= 1;
         __syncthreads();
     };
+    // whole pairs of steps: no branch inside a loop; those with every plane inside
+    // check none (not with the correction: a second copy of its step spills, 813
+    // against 718 us at 513^3 in FP64)
+    const int sa = PROLONG ? smax : max(K0 + 3, s0 + 2), sb = min(n - 3, smax - 1);
     int s = s0;
-    for (; s + 1 <= smax; s += 2) {   // whole pairs of steps: no branch inside the loop
-        step(s, vA, pA, false);
-        step(s + 1, vB, pB, true);
+    for (; s < sa && s + 1 <= smax; s += 2) {
+        step(s, vA, pA, false, false);
+        step(s + 1, vB, pB, true, false);
     }
-    if (s <= smax) step(s, vA, pA, false);
+    if constexpr (!PROLONG) {
+        for (; s <= sb; s += 2) {
+            step(s, vA, pA, false, true);
+            step(s + 1, vB, pB, true, true);
+        }
+        for (; s + 1 <= smax; s += 2) {
+            step(s, vA, pA, false, false);
+            step(s + 1, vB, pB, true, false);
+        }
+    }
+    if (s <= smax) step(s, vA, pA, false, false);
 }
 
 }  // namespace
