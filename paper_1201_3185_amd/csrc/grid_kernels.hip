@@ -1861,73 +1861,19 @@ __device__ __forceinline__ void block_sum3(double *sh, double &a, double &b, dou
 
 // Per-block partial sums over interior nodes of (f - A_h u)^2, f^2 and the
 // squared boundary-value contribution (sum of boundary neighbours / h^2),
-// which scales the stopping test of a source-free box.  A workgroup is 4 rows
-// of 64 lanes: each lane row walks x along one interior (j, k) row (coalesced),
-// the workgroups stride over the rows; the summation order depends only on n
-// and the block count, so the norms are reproducible bit for bit.  With R32
-// the pass also writes the residual times 1/s (sc[2p + 1]) rounded to FP32 at
-// every interior node, the right-hand side of the next refinement step of a
-// mixed solve (the value resid_to_f32_k forms, saving that pass).
-template <typename T, bool R32>
-__global__ void __launch_bounds__(256)
-resid_norms_partial_k(int n, double ih2, const T *__restrict__ f, const T *__restrict__ u, double *__restrict__ partial,
-                      const double *__restrict__ sc, float *__restrict__ r32)
-{
-    __shared__ double sh[768];
-    const int m = n - 2;
-    const unsigned rows = (unsigned)m * (unsigned)m;
-    const size_t sy = (size_t)n, sz = (size_t)n * n;
-    f += blockIdx.y * sz * n;
-    u += blockIdx.y * sz * n;
-    partial += blockIdx.y * 3 * (size_t)gridDim.x;
-    double inv_s = 0.0;
-    if (R32) {
-        r32 += blockIdx.y * sz * n;
-        inv_s = sc[2 * blockIdx.y + 1];
-    }
-    const int lane = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    double sr = 0.0, sf = 0.0, sb = 0.0;
-    for (unsigned r = blockIdx.x * 4u + (unsigned)ty; r < rows; r += gridDim.x * 4u) {
-        const unsigned kq = r / (unsigned)m;              // one division per row
-        const int j = 1 + (int)(r - kq * (unsigned)m), k = 1 + (int)kq;
-        const bool jk_edge = j == 1 || k == 1 || j == n - 2 || k == n - 2;
-        const size_t row = id3(n, 0, j, k);
-        for (int i = 1 + lane; i <= n - 2; i += 64) {
-            const size_t p = row + (size_t)i;
-            const double um = u[p - 1], up = u[p + 1], vm = u[p - sy], vp = u[p + sy], wm = u[p - sz], wp = u[p + sz];
-            const double lap = (um + up + vm + vp + wm + wp - 6.0 * (double)u[p]) * ih2;
-            const double fv = (double)f[p];
-            const double res = fv - lap;
-            if (R32) r32[p] = (float)(res * inv_s);
-            sr += res * res;
-            sf += fv * fv;
-            if (jk_edge || i == 1 || i == n - 2) {
-                const double b = ((i == 1 ? um : 0.0) + (i == n - 2 ? up : 0.0) + (j == 1 ? vm : 0.0) +
-                                  (j == n - 2 ? vp : 0.0) + (k == 1 ? wm : 0.0) + (k == n - 2 ? wp : 0.0)) * ih2;
-                sb += b * b;
-            }
-        }
-    }
-    block_sum3<256>(sh, sr, sf, sb);
-    if (threadIdx.x == 0) {
-        partial[3 * blockIdx.x] = sr;
-        partial[3 * blockIdx.x + 1] = sf;
-        partial[3 * blockIdx.x + 2] = sb;
-    }
-}
-
-// The same partial sums from a z-march: a workgroup owns a 64 x TY column tile
-// of interior nodes and a chunk of z planes, so u and f are read from HBM about
-// once (the row form reads the +-z neighbour rows again, from other workgroups
-// at other times).  A thread owns one column: its z neighbours stay in
+// which scales the stopping test of a source-free box, from a z-march: a
+// workgroup owns a 64 x TY column tile of interior nodes and a chunk of z planes,
+// so u and f are read from HBM about once.  With R32 the pass also writes the
+// residual times 1/s (sc[2p + 1]) rounded to FP32 at every interior node, the
+// right-hand side of the next refinement step of a mixed solve (the value
+// resid_to_f32_k forms, saving that pass).  A thread owns one column: its z neighbours stay in
 // registers, the x and y ones come from an LDS plane of the tile and its ring,
 // which is written a step before (two planes, one barrier a step).  A plane of u
 // is requested three steps before use, one of f two; the loads come after all
 // uses of the registers they fill, and nothing is masked on its way in: what is
 // clamped into the grid enters no interior node's residual.  Each lane sums its
 // own column; the order depends only on n and the launch shape, which the
-// launcher fixes from n, so the sums are reproducible bit for bit.  Same
-// residual expression, same FP32 residual with R32.  Bound by HBM: 513^3 FP64 445 us
+// launcher fixes from n, so the sums are reproducible bit for bit.  Bound by HBM: 513^3 FP64 445 us
 // with one plane in flight and two barriers a plane, now 407 (5.3 TB/s; with R32
 // 648 -> 625); 129^3 15.2 -> 11.9, 65^3 8.5 -> 5.9.
 constexpr int kNzTX = 64;
@@ -2048,8 +1994,8 @@ resid_norms_zmarch_k(int n, double ih2, const T *__restrict__ f, const T *__rest
 
 // Launch shape of the z-march norms for n: tiles of 64 x ty columns and the
 // z-chunk that keeps the block count at most kNormBlocks, or half of it with ty =
-// 8 (and the chunks at least 8 planes); 0 blocks when the tiles alone exceed
-// kNormBlocks (the row form serves then).  ty = 8 reads 1.3 values of u per node
+// 8 (and the chunks at least 8 planes); the tiles of the largest grid, 1025^3, are
+// kNormBlocks.  ty = 8 reads 1.3 values of u per node
 // instead of 1.5 and wins where HBM bounds (513^3: 407 against 420 us, with R32 625
 // against 661); with ty = 4 smaller grids have more workgroups (129^3 11.9 against
 // 12.6 us, 65^3 5.9 against 6.9).
@@ -2064,10 +2010,6 @@ static NormsShape norms_shape(int n)
     sh.gx = (m + kNzTX - 1) / kNzTX;
     sh.gy = (m + sh.ty - 1) / sh.ty;
     const int tiles = sh.gx * sh.gy;
-    if (tiles > kNormBlocks) {
-        sh.kchunk = sh.nzc = sh.blocks = 0;
-        return sh;
-    }
     const int q = std::max(1, kNormBlocks * 4 / sh.ty / tiles);
     sh.kchunk = std::max(8, (m + q - 1) / q);
     sh.nzc = (m + sh.kchunk - 1) / sh.kchunk;
@@ -2121,33 +2063,16 @@ void launch_resid_norms(int n, double h, const T *f, const T *u, double *partial
                         double *hout)
 {
     const NormsShape zs = norms_shape(n);
-    if (zs.blocks > 0) {
-        norms_zmarch<T, false>(zs, n, h, f, u, partial, nullptr, nullptr, s, nb);
-        hipLaunchKernelGGL(norms_final_k, dim3(nb), dim3(256), 0, s, partial, zs.blocks, out, hout);
-        return;
-    }
-    // about 8 four-row groups per workgroup, at most kNormBlocks workgroups per problem
-    const long long rows = (long long)(n - 2) * (n - 2);
-    const int blocks = (int)std::min<long long>(kNormBlocks, std::max<long long>(1, (rows + 31) / 32));
-    hipLaunchKernelGGL((resid_norms_partial_k<T, false>), dim3(blocks, nb), dim3(256), 0, s, n, 1.0 / (h * h), f, u,
-                       partial, nullptr, nullptr);
-    hipLaunchKernelGGL(norms_final_k, dim3(nb), dim3(256), 0, s, partial, blocks, out, hout);
+    norms_zmarch<T, false>(zs, n, h, f, u, partial, nullptr, nullptr, s, nb);
+    hipLaunchKernelGGL(norms_final_k, dim3(nb), dim3(256), 0, s, partial, zs.blocks, out, hout);
 }
 
 void launch_resid_norms_r32(int n, double h, const double *f, const double *u, double *partial, double *out,
                             const double *sc, float *r32, hipStream_t s, int nb, double *hout)
 {
     const NormsShape zs = norms_shape(n);
-    if (zs.blocks > 0) {
-        norms_zmarch<double, true>(zs, n, h, f, u, partial, sc, r32, s, nb);
-        hipLaunchKernelGGL(norms_final_k, dim3(nb), dim3(256), 0, s, partial, zs.blocks, out, hout);
-        return;
-    }
-    const long long rows = (long long)(n - 2) * (n - 2);
-    const int blocks = (int)std::min<long long>(kNormBlocks, std::max<long long>(1, (rows + 31) / 32));
-    hipLaunchKernelGGL((resid_norms_partial_k<double, true>), dim3(blocks, nb), dim3(256), 0, s, n, 1.0 / (h * h), f,
-                       u, partial, sc, r32);
-    hipLaunchKernelGGL(norms_final_k, dim3(nb), dim3(256), 0, s, partial, blocks, out, hout);
+    norms_zmarch<double, true>(zs, n, h, f, u, partial, sc, r32, s, nb);
+    hipLaunchKernelGGL(norms_final_k, dim3(nb), dim3(256), 0, s, partial, zs.blocks, out, hout);
 }
 
 // ------------------------------------------------- mixed-precision helpers

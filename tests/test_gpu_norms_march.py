@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("source", [True, False])
-@pytest.mark.parametrize("n", [5, 9, 33, 65, 129, 257, 513])
+@pytest.mark.parametrize("n", [5, 9, 33, 65, 129, 257, 513, 1025])
 def test_relative_residual(n, source):
     """The relative residual that a solve without cycles reports (over f, or over
     the boundary terms of a source-free box), against torch in FP64: sums of n^3
