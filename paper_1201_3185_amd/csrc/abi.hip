@@ -392,11 +392,14 @@ qumond_status qumond_deposit(qumond_ctx *ctx, const double *x, const double *y, 
         a.box[b].inv_h = (double)(ctx->n - 1) / B.L;
         a.box[b].h = B.h;
         a.q[b] = (unsigned long long *)B.q;
-        qm::launch_fill<long long>(B.q, ctx->N, 0LL, ctx->s);
     }
-    qm::launch_fill<unsigned long long>(ctx->d_count, 1, 0ULL, ctx->s);
-    if (sort_workspace(ctx, np)) qm::launch_deposit_sorted(a, x, y, z, m, np, ctx->d_count, ctx->sort_ws, ctx->s);
-    else qm::launch_deposit(a, x, y, z, m, np, ctx->d_count, ctx->s);
+    if (sort_workspace(ctx, np)) {
+        qm::launch_deposit_sorted(a, x, y, z, m, np, ctx->d_count, ctx->sort_ws, ctx->s);
+    } else {
+        for (int b = 0; b < a.nbox; ++b) qm::launch_fill<long long>(ctx->box[b].q, ctx->N, 0LL, ctx->s);
+        qm::launch_fill<unsigned long long>(ctx->d_count, 1, 0ULL, ctx->s);
+        qm::launch_deposit(a, x, y, z, m, np, ctx->d_count, ctx->s);
+    }
     const double four_pi_G = 4.0 * M_PI * ctx->cfg.G;
     for (int b = 0; b < a.nbox; ++b)
         qm::launch_rhs_from_q(ctx->n, ctx->box[b].h, four_pi_G, shift, ctx->box[b].q, ctx->box[b].f, ctx->s);

@@ -268,8 +268,10 @@ void launch_bc_from_coarse(int n, const double *uc, double *u0, double *u1, hipS
 size_t deposit_scratch_bytes(int nbox);
 void launch_deposit(const DepositArgs &a, const double *x, const double *y, const double *z, const double *m,
                     int64_t np, unsigned long long *inside_count, hipStream_t s);
-// The same integers by way of a sort of the particles by cell tile; deposit_sorts
-// says where it is the faster, ws holds deposit_sort_bytes(n, nbox, np) bytes.
+// The same integers by way of a sort of the particles by cell tile, or by the
+// window where a sample of them says that it is the faster; a.q and inside_count
+// are cleared here.  deposit_sorts says where this can pay, ws holds
+// deposit_sort_bytes(n, nbox, np) bytes.
 bool deposit_sorts(int n, int nbox, int64_t np);
 size_t deposit_sort_bytes(int n, int nbox, int64_t np);
 void launch_deposit_sorted(const DepositArgs &a, const double *x, const double *y, const double *z, const double *m,

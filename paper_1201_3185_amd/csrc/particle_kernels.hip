@@ -43,13 +43,13 @@ __device__ __forceinline__ bool cic_cell(const BoxGeom &g, int n, double px, dou
     return true;
 }
 
-__global__ void __launch_bounds__(kDepositThreads)
-deposit_window_k(DepositArgs A, const double *__restrict__ x, const double *__restrict__ y,
-                 const double *__restrict__ z, const double *__restrict__ m, int64_t np, int64_t per_block,
-                 unsigned long long *__restrict__ inside_count)
+// A workgroup's share; W: kWin words of LDS.
+__device__ __forceinline__ void window_share(const DepositArgs &A, const double *__restrict__ x,
+                                             const double *__restrict__ y, const double *__restrict__ z,
+                                             const double *__restrict__ m, int64_t np, int64_t per_block,
+                                             unsigned long long *__restrict__ inside_count, unsigned long long *W)
 {
 #pragma clang fp contract(off)
-    __shared__ unsigned long long W[kWin];
     __shared__ unsigned int cnt_sh;
     const int64_t p0 = (int64_t)blockIdx.x * per_block;
     const int64_t p1 = min(np, p0 + per_block);
@@ -89,29 +89,47 @@ deposit_window_k(DepositArgs A, const double *__restrict__ x, const double *__re
     if (threadIdx.x == 0 && cnt_sh) atomicAdd(inside_count, (unsigned long long)cnt_sh);
 }
 
-__global__ void __launch_bounds__(256)
-deposit_reduce_k(DepositArgs A, int nblocks)
+__global__ void __launch_bounds__(kDepositThreads)
+deposit_window_k(DepositArgs A, const double *__restrict__ x, const double *__restrict__ y,
+                 const double *__restrict__ z, const double *__restrict__ m, int64_t np, int64_t per_block,
+                 unsigned long long *__restrict__ inside_count)
 {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    const int b = blockIdx.y;
-    if (e >= kWin) return;
-    const int li = e % kWinX, lj = (e / kWinX) % kWinY, lk = e / (kWinX * kWinY);
-    const int i = A.w0[b][0] + li, j = A.w0[b][1] + lj, k = A.w0[b][2] + lk;
-    if (i >= A.n || j >= A.n || k >= A.n) return;
+    __shared__ unsigned long long W[kWin];
+    window_share(A, x, y, z, m, np, per_block, inside_count, W);
+}
+
+// Node e of box b's window over the slabs g0 .. g1 - 1.
+__device__ __forceinline__ unsigned long long window_sum(const DepositArgs &A, int g0, int g1, int e, int b)
+{
     // four independent integer sums keep four slab loads in flight (any order gives the same sum)
     unsigned long long s0 = 0ULL, s1 = 0ULL, s2 = 0ULL, s3 = 0ULL;
     const size_t st = (size_t)A.nbox * kWin;
     const unsigned long long *src = A.scratch + (size_t)b * kWin + e;
-    int g = 0;
-    for (; g + 4 <= nblocks; g += 4) {
+    int g = g0;
+    for (; g + 4 <= g1; g += 4) {
         s0 += src[(size_t)g * st];
         s1 += src[(size_t)(g + 1) * st];
         s2 += src[(size_t)(g + 2) * st];
         s3 += src[(size_t)(g + 3) * st];
     }
-    for (; g < nblocks; ++g) s0 += src[(size_t)g * st];
-    const unsigned long long s = (s0 + s1) + (s2 + s3);
+    for (; g < g1; ++g) s0 += src[(size_t)g * st];
+    return (s0 + s1) + (s2 + s3);
+}
+
+// ... added to the grid
+__device__ __forceinline__ void window_add(const DepositArgs &A, int e, int b, unsigned long long s)
+{
+    const int li = e % kWinX, lj = (e / kWinX) % kWinY, lk = e / (kWinX * kWinY);
+    const int i = A.w0[b][0] + li, j = A.w0[b][1] + lj, k = A.w0[b][2] + lk;
+    if (i >= A.n || j >= A.n || k >= A.n) return;
     if (s) A.q[b][id3(A.n, i, j, k)] += s;
+}
+
+__global__ void __launch_bounds__(256)
+deposit_reduce_k(DepositArgs A, int nblocks)
+{
+    const int e = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+    if (e < kWin) window_add(A, e, b, window_sum(A, 0, nblocks, e, b));
 }
 
 size_t deposit_scratch_bytes(int nbox) { return (size_t)kDepositMaxBlocks * nbox * kWin * sizeof(unsigned long long); }
@@ -141,9 +159,12 @@ void launch_deposit(const DepositArgs &a, const double *x, const double *y, cons
 // atomics, once per kSegment particles or more.  The weights, their rounding
 // and the integer sums are those of the window form, so the grids are the same
 // integers whatever the order.
-//   1. tile_count_k: LDS histogram over the tiles per workgroup, kept per
-//      workgroup and added to the totals;
-//   2. tile_scan_k: start of every tile, list of segments;
+//   0. deposit_start_k clears the grids and draws a sample of the particles, from
+//      which it says whether the sorted form or the window form takes them;
+//   1. deposit_first_k: LDS histogram over the tiles per workgroup, kept per
+//      workgroup and added to the totals (or the window form's shares);
+//   2. deposit_second_k: start of every tile, list of segments (or the sums of the
+//      window form's slabs);
 //   3. tile_scatter_k: particles as 32-byte records in tile order;
 //   4. tile_deposit_k: segments from a queue.
 // It is bound by its passes over the particles (24 + 32 + 32 + 32 B each) and by
@@ -153,7 +174,7 @@ void launch_deposit(const DepositArgs &a, const double *x, const double *y, cons
 // 257^3 boxes 1698 -> 422 us, 1e6 in four 129^3 boxes 351 -> 144 us.
 
 constexpr int kTileXY = 32, kTileZ = 8;
-constexpr int kSortBlocks = 256;
+constexpr int kSortBlocks = kDepositMaxBlocks;   // the window form in these launches fills as many slabs
 constexpr int kSegment = 4096;
 constexpr int kWinAll = 11904;       // nodes of one tile's blocks on all boxes, at most
 constexpr int kWinOne = 33 * 33 * 9;
@@ -198,13 +219,104 @@ __device__ __forceinline__ int tile_of(const DepositArgs &A, const TileGrid &T, 
     return bin;
 }
 
-template <int MAXBIN>
-__global__ void __launch_bounds__(1024)
-tile_count_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const double *__restrict__ y,
-             const double *__restrict__ z, int np, int per_block, unsigned *__restrict__ hist, unsigned *__restrict__ total,
-             unsigned long long *__restrict__ inside_count)
+// Which form is the faster one, from kSample particles, one of each of as many
+// equal runs of the list.  Either form gives the same integers, so the choice is
+// one of time alone.  What the forms cost, fitted to deposits of disks, spheres,
+// uniform and compact sets of 2.5e5 to 1e7 particles on 129^3 to 513^3 (1 to 11
+// boxes), in ps:
+//   window  12 per particle and box, 340 per particle and box whose corners lie
+//           outside the window (eight global atomics);
+//   sorted  18.5 per particle, 10 per particle and box, 32000 per tile with
+//           particles (its LDS window is cleared and scanned however few).
+// So a set inside the window stays there (1e7 particles of a disk four cells
+// wide, 129^3: 164 us against 339), as does one that is thin on the tiles
+// (250 000 filling a 513^3 box: 842 against 1069).
+constexpr int kStartThreads = 256, kSample = 2 * kStartThreads;
+constexpr int kMaxTiles = 32768;
+
+__device__ __forceinline__ void choose_form(const DepositArgs &A, const TileGrid &T, const double *__restrict__ x,
+                                            const double *__restrict__ y, const double *__restrict__ z, int np,
+                                            int *__restrict__ sorted)
 {
-    __shared__ unsigned H[MAXBIN];
+    __shared__ unsigned seen[kMaxTiles / 32];   // a bit per tile
+    __shared__ unsigned beyond, tiles;
+    for (int e = threadIdx.x; e < kMaxTiles / 32; e += kStartThreads) seen[e] = 0;
+    if (threadIdx.x == 0) beyond = tiles = 0;
+    __syncthreads();
+    unsigned out = 0;
+#pragma unroll
+    for (int r = 0; r < kSample / kStartThreads; ++r) {
+        const unsigned i = threadIdx.x + kStartThreads * r;
+        // a place of its own in every run: lists have periods
+        const double at = ((double)i + (double)(i * 2654435769u) * 0x1p-32) * ((double)np / kSample);
+        const int p = min((int)at, np - 1);
+        const double px = x[p], py = y[p], pz = z[p];
+        bool in0;
+        const int bin = tile_of(A, T, px, py, pz, in0);
+        if (bin >= 0) atomicOr(&seen[bin >> 5], 1u << (bin & 31));
+        for (int b = 0; b < A.nbox; ++b) {
+            int ic[3];
+            double w[3][2];
+            if (!cic_cell(A.box[b], A.n, px, py, pz, ic, w)) continue;
+            const int lx = ic[0] - A.w0[b][0], ly = ic[1] - A.w0[b][1], lz = ic[2] - A.w0[b][2];
+            out += !(lx >= 0 && lx < kWinX - 1 && ly >= 0 && ly < kWinY - 1 && lz >= 0 && lz < kWinZ - 1);
+        }
+    }
+    if (out) atomicAdd(&beyond, out);
+    __syncthreads();
+    unsigned hit = 0;
+    for (int e = threadIdx.x; e < kMaxTiles / 32; e += kStartThreads) hit += __popc(seen[e]);
+    if (hit) atomicAdd(&tiles, hit);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    // t tiles hit evenly show t (1 - exp(-kSample / t)) of them: t from 64 values between the tiles seen and all
+    const float d = (float)max(tiles, 1u);
+    const float t = d * exp2f(log2f((float)T.nbin / d) * ((float)threadIdx.x / 63.0f));
+    const unsigned long long below = __ballot(t * (1.0f - expf(-(float)kSample / t)) < d);
+    if (threadIdx.x != min(__popcll(below), 63)) return;
+    const float n = (float)np, nb = (float)A.nbox;
+    const float window = 12.0f * nb * n + 340.0f * ((float)beyond / kSample) * n;
+    const float sort = (18.5f + 10.0f * nb) * n + 32000.0f * t;
+    *sorted = window > sort;
+}
+
+// Clears the totals, the count of particles (clear) and, where a sample is drawn
+// (sorted), beside it the grids.
+__global__ void __launch_bounds__(kStartThreads)
+deposit_start_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const double *__restrict__ y,
+                const double *__restrict__ z, int np, int clear, unsigned *__restrict__ total,
+                unsigned long long *__restrict__ inside_count, int *__restrict__ sorted)
+{
+    if (blockIdx.x == 0) {
+        if (sorted) choose_form(A, T, x, y, z, np, sorted);
+        return;
+    }
+    const size_t t = (blockIdx.x - 1) * (size_t)kStartThreads + threadIdx.x, st = (gridDim.x - 1) * (size_t)kStartThreads;
+    for (size_t e = t; e < (size_t)T.nbin; e += st) total[e] = 0;
+    if (!clear) return;
+    if (t == 0) *inside_count = 0ULL;
+    if (!sorted) return;
+    // 16 bytes at a time on the small grids (deposit in one 257^3 box 145 -> 142 us, in
+    // two 513^3 boxes 1456 -> 1540)
+    const size_t N = (size_t)A.n * A.n * A.n;
+    for (int b = 0; b < A.nbox; ++b) {
+        if (A.n <= 257) {
+            for (size_t e = 2 * t; e < N; e += 2 * st) {
+                if (e + 1 < N) *reinterpret_cast<ulonglong2 *>(A.q[b] + e) = ulonglong2{0ULL, 0ULL};
+                else A.q[b][e] = 0ULL;
+            }
+        } else {
+            for (size_t e = t; e < N; e += st) A.q[b][e] = 0ULL;
+        }
+    }
+}
+
+template <int MAXBIN>
+__device__ __forceinline__ void tile_count(const DepositArgs &A, const TileGrid &T, const double *__restrict__ x,
+                                           const double *__restrict__ y, const double *__restrict__ z, int np,
+                                           int per_block, unsigned *__restrict__ hist, unsigned *__restrict__ total,
+                                           unsigned long long *__restrict__ inside_count, unsigned *H)
+{
     __shared__ unsigned cnt_sh;
     for (int e = threadIdx.x; e < T.nbin; e += 1024) H[e] = 0;
     if (threadIdx.x == 0) cnt_sh = 0;
@@ -228,13 +340,27 @@ tile_count_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const doub
     if (threadIdx.x == 0 && cnt_sh) atomicAdd(inside_count, (unsigned long long)cnt_sh);
 }
 
+template <int MAXBIN>
+__global__ void __launch_bounds__(1024)
+deposit_first_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const double *__restrict__ y,
+                const double *__restrict__ z, const double *__restrict__ m, int np, int per_block,
+                unsigned *__restrict__ hist, unsigned *__restrict__ total, unsigned long long *__restrict__ inside_count,
+                const int *__restrict__ sorted)
+{
+    static_assert(MAXBIN <= 2 * kWin, "the histogram lies in the window's LDS");
+    __shared__ unsigned long long W[kWin];
+    if (!sorted || *sorted)
+        tile_count<MAXBIN>(A, T, x, y, z, np, per_block, hist, total, inside_count, reinterpret_cast<unsigned *>(W));
+    else
+        window_share(A, x, y, z, m, np, per_block, inside_count, W);
+}
+
 // One workgroup: start[bin] = particles before the bin, next[bin] the same (the
 // scatter's cursor); seg[] = {bin, first, end} of every segment of at most
 // seg_len particles; queue[0] = number of segments, queue[1] = 0.
 template <int MAXBIN>
-__global__ void __launch_bounds__(1024)
-tile_scan_k(int nbin, int seg_len, const unsigned *__restrict__ total, unsigned *__restrict__ next, int4 *__restrict__ seg,
-            unsigned *__restrict__ queue)
+__device__ __forceinline__ void tile_scan(int nbin, int seg_len, const unsigned *__restrict__ total,
+                                          unsigned *__restrict__ next, int4 *__restrict__ seg, unsigned *__restrict__ queue)
 {
     constexpr int PER = MAXBIN / 1024;               // bins per thread, in order
     __shared__ unsigned B[MAXBIN + 1024];            // one word of padding per thread's bins
@@ -276,11 +402,33 @@ tile_scan_k(int nbin, int seg_len, const unsigned *__restrict__ total, unsigned 
 
 template <int MAXBIN>
 __global__ void __launch_bounds__(1024)
+deposit_second_k(DepositArgs A, int nbin, int seg_len, const unsigned *__restrict__ total, unsigned *__restrict__ next,
+                 int4 *__restrict__ seg, unsigned *__restrict__ queue, const int *__restrict__ sorted)
+{
+    if (!sorted || *sorted) {
+        if (blockIdx.x == 0 && blockIdx.y == 0) tile_scan<MAXBIN>(nbin, seg_len, total, next, seg, queue);
+        return;
+    }
+    // 256 nodes a workgroup, each over four quarters of the slabs
+    __shared__ unsigned long long part[1024];
+    static_assert(kWin % 256 == 0 && kSortBlocks % 4 == 0, "whole workgroups and quarters");
+    constexpr int Q = kSortBlocks / 4;
+    const int e = blockIdx.x * 256 + (threadIdx.x & 255), b = blockIdx.y, q = threadIdx.x >> 8;
+    part[threadIdx.x] = window_sum(A, q * Q, (q + 1) * Q, e, b);
+    __syncthreads();
+    if (q == 0)
+        window_add(A, e, b, (part[threadIdx.x] + part[threadIdx.x + 256]) + (part[threadIdx.x + 512] + part[threadIdx.x + 768]));
+}
+
+template <int MAXBIN>
+__global__ void __launch_bounds__(1024)
 tile_scatter_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const double *__restrict__ y,
                const double *__restrict__ z, const double *__restrict__ m, int np, int per_block,
-               const unsigned *__restrict__ hist, unsigned *__restrict__ next, double4 *__restrict__ rec)
+               const unsigned *__restrict__ hist, unsigned *__restrict__ next, double4 *__restrict__ rec,
+               const int *__restrict__ sorted)
 {
     __shared__ unsigned H[MAXBIN];
+    if (sorted && !*sorted) return;
     const unsigned *row = hist + (size_t)blockIdx.x * T.nbin;
     for (int e = threadIdx.x; e < T.nbin; e += 1024) {   // this workgroup's place in every tile it has particles of
         const unsigned h = row[e];
@@ -303,12 +451,13 @@ tile_scatter_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const do
 template <int WIN>
 __global__ void __launch_bounds__(1024)
 tile_deposit_k(DepositArgs A, TileGrid T, const double4 *__restrict__ rec, const int4 *__restrict__ seg,
-               unsigned *__restrict__ queue)
+               unsigned *__restrict__ queue, const int *__restrict__ sorted)
 {
 #pragma clang fp contract(off)
     __shared__ unsigned long long W[WIN];
     __shared__ int4 sg;
     __shared__ int more;
+    if (sorted && !*sorted) return;
     const unsigned nseg = queue[0];
     for (;;) {
         if (threadIdx.x == 0) {
@@ -399,16 +548,20 @@ tile_deposit_k(DepositArgs A, TileGrid T, const double4 *__restrict__ rec, const
     }
 }
 
-// The window form stays where its window holds most of the disk or the passes
-// of the sort cost more than the atomics they save: at 65^3 and below (1e7
-// particles: 163 us against 357, six nested boxes 823 against 912) and for few
-// particles (129^3, 1e5: 48 against 59, 3e5: 68 against 63 us; 257^3, 1e5: 104
-// against 102), and where the tiles outgrow an LDS histogram (1025^3, or 513^3
-// in more than two boxes).
+// Where the sorted form can be the faster one.  The window form alone stays at
+// 65^3 and below, whose window holds most of a disk (1e7 particles: 163 us against
+// 357, six nested boxes 823 against 912), for few particles (129^3, 1e5: 48
+// against 59, 3e5: 68 against 63 us; 257^3, 1e5: 104 against 102), and where the
+// tiles outgrow an LDS histogram (1025^3, or 513^3 in more than two boxes).
 bool deposit_sorts(int n, int nbox, int64_t np)
 {
-    return n >= 129 && np >= 250000 && tile_grid(n, nbox).nbin <= 32768;
+    return n >= 129 && np >= 250000 && tile_grid(n, nbox).nbin <= kMaxTiles;
 }
+
+// Where a sample decides between the forms.  It costs 4 us and the launches that
+// end at once, more than it can save below 1e6 particles on at most 257^3 (250 000
+// of the sets above: the sorted form takes at most 7 % longer there).
+static int deposit_samples(int n, int np) { return n > 257 || np >= 1000000; }
 
 constexpr int64_t kSortSlice = 1 << 26;   // particles sorted at a time
 
@@ -419,12 +572,12 @@ size_t deposit_sort_bytes(int n, int nbox, int64_t np)
     const TileGrid t = tile_grid(n, nbox);
     const int64_t m = np < kSortSlice ? np : kSortSlice;
     return round256((size_t)m * sizeof(double4)) + round256((size_t)kSortBlocks * t.nbin * 4) + 2 * round256((size_t)t.nbin * 4) +
-           round256(((size_t)m / kSegment + t.nbin + 1) * sizeof(int4)) + 256;
+           round256(((size_t)m / kSegment + t.nbin + 1) * sizeof(int4)) + 512;
 }
 
 template <int MAXBIN>
 static void deposit_sorted(const DepositArgs &a, const TileGrid &t, const double *x, const double *y, const double *z,
-                           const double *m, int np, unsigned long long *inside_count, void *ws, hipStream_t s)
+                           const double *m, int np, bool clear, unsigned long long *inside_count, void *ws, hipStream_t s)
 {
     char *w = (char *)ws;
     double4 *rec = (double4 *)w;
@@ -438,20 +591,29 @@ static void deposit_sorted(const DepositArgs &a, const TileGrid &t, const double
     int4 *seg = (int4 *)w;
     w += round256(((size_t)np / kSegment + t.nbin + 1) * sizeof(int4));
     unsigned *queue = (unsigned *)w;
+    w += 256;
+    int *sorted = deposit_samples(a.n, np) ? (int *)w : nullptr;   // null: the sorted form
     const int per_block = (np + kSortBlocks - 1) / kSortBlocks;
     // long enough that touched nodes are flushed rarely, short enough for some 1000 segments
     int seg_len = np / 1024;
     seg_len = (seg_len < kSegment ? kSegment : seg_len + kSegment - 1) / kSegment * kSegment;
-    launch_fill<unsigned long long>((unsigned long long *)total, ((size_t)t.nbin + 1) / 2, 0ULL, s);   // room for 256 bytes' multiple
-    hipLaunchKernelGGL((tile_count_k<MAXBIN>), dim3(kSortBlocks), dim3(1024), 0, s, a, t, x, y, z, np, per_block, hist,
-                       total, inside_count);
-    hipLaunchKernelGGL((tile_scan_k<MAXBIN>), dim3(1), dim3(1024), 0, s, t.nbin, seg_len, total, next, seg, queue);
+    // the grids are cleared beside the sample, or, where none is drawn, by fills of their own
+    const size_t N = (size_t)a.n * a.n * a.n;
+    if (clear && !sorted)
+        for (int b = 0; b < a.nbox; ++b) launch_fill<unsigned long long>(a.q[b], N, 0ULL, s);
+    const size_t fill = ((clear && sorted ? N : (size_t)t.nbin) + kStartThreads - 1) / kStartThreads;
+    hipLaunchKernelGGL(deposit_start_k, dim3(1 + (unsigned)(fill < 16384 ? fill : 16384)), dim3(kStartThreads), 0, s, a, t,
+                       x, y, z, np, clear ? 1 : 0, total, inside_count, sorted);
+    hipLaunchKernelGGL((deposit_first_k<MAXBIN>), dim3(kSortBlocks), dim3(1024), 0, s, a, t, x, y, z, m, np, per_block,
+                       hist, total, inside_count, sorted);
+    hipLaunchKernelGGL((deposit_second_k<MAXBIN>), sorted ? dim3(kWin / 256, a.nbox) : dim3(1), dim3(1024), 0, s, a, t.nbin,
+                       seg_len, total, next, seg, queue, sorted);
     hipLaunchKernelGGL((tile_scatter_k<MAXBIN>), dim3(kSortBlocks), dim3(1024), 0, s, a, t, x, y, z, m, np, per_block,
-                       hist, next, rec);
+                       hist, next, rec, sorted);
     if (a.nbox == 1)
-        hipLaunchKernelGGL((tile_deposit_k<kWinOne>), dim3(512), dim3(1024), 0, s, a, t, rec, seg, queue);
+        hipLaunchKernelGGL((tile_deposit_k<kWinOne>), dim3(512), dim3(1024), 0, s, a, t, rec, seg, queue, sorted);
     else
-        hipLaunchKernelGGL((tile_deposit_k<kWinAll>), dim3(256), dim3(1024), 0, s, a, t, rec, seg, queue);
+        hipLaunchKernelGGL((tile_deposit_k<kWinAll>), dim3(256), dim3(1024), 0, s, a, t, rec, seg, queue, sorted);
 }
 
 void launch_deposit_sorted(const DepositArgs &a, const double *x, const double *y, const double *z, const double *m,
@@ -460,8 +622,8 @@ void launch_deposit_sorted(const DepositArgs &a, const double *x, const double *
     const TileGrid t = tile_grid(a.n, a.nbox);
     for (int64_t p = 0; p < np; p += kSortSlice) {
         const int c = (int)(np - p < kSortSlice ? np - p : kSortSlice);
-        if (t.nbin <= 8192) deposit_sorted<8192>(a, t, x + p, y + p, z + p, m + p, c, inside_count, ws, s);
-        else deposit_sorted<32768>(a, t, x + p, y + p, z + p, m + p, c, inside_count, ws, s);
+        if (t.nbin <= 8192) deposit_sorted<8192>(a, t, x + p, y + p, z + p, m + p, c, p == 0, inside_count, ws, s);
+        else deposit_sorted<kMaxTiles>(a, t, x + p, y + p, z + p, m + p, c, p == 0, inside_count, ws, s);
     }
 }
 
