@@ -26,7 +26,9 @@
  *
  * Memory.  Every array pointer is a DEVICE pointer (for example a torch
  * tensor's data_ptr()) owned by the caller, unless marked "host".  The
- * library owns every grid it allocates inside a context.  All work is
+ * library owns every grid it allocates inside a context (by qumond_create, but
+ * for the second chain that qumond_solve adds on its first call and the
+ * workspace of large deposits; qumond_device_bytes counts all).  All work is
  * enqueued on the HIP stream given to qumond_create; calls that return data
  * to the host (the solves, for their stopping test, and n_outside) synchronise
  * that stream, every other call is asynchronous.
@@ -152,7 +154,14 @@ qumond_status qumond_destroy(qumond_ctx *ctx);
  * unless fixed_shift is set.  Then rhs = 4 pi G q 2^-s / h^3.  total_mass is
  * the mass of all particles (also those outside every box): it sets the
  * monopole boundary value.  n_outside (host, optional; synchronises) receives
- * the number of particles outside the outermost box.  np = 0 is valid. */
+ * the number of particles outside the outermost box.  np = 0 is valid.
+ * From 250000 particles up, on 129^3 to 513^3, the context takes a workspace of
+ * 32 bytes for each of the next power of two of particles (at least 2^18, at
+ * most 2^26, more being deposited in slices) and up to 34 MB.  A larger count
+ * adds a larger workspace, so that all of them together hold less than 4.7 GB;
+ * they are given back by qumond_destroy.  Without it (no memory left beside what
+ * qumond_solve needs, or the stream is being captured) the same integers come
+ * from a form that can take several times as long. */
 qumond_status qumond_deposit(qumond_ctx *ctx, const double *x, const double *y, const double *z,
                              const double *m, int64_t np, double total_mass, int64_t *n_outside);
 

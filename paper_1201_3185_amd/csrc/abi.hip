@@ -74,8 +74,8 @@ struct qumond_ctx {
     unsigned long long *d_count = nullptr;
     unsigned long long *h_count = nullptr;  // pinned
     unsigned long long *dep_scratch = nullptr;
-    void *sort_ws = nullptr;             // workspace of the sorted deposit, grown to the largest particle count seen
-    size_t sort_bytes = 0;
+    void *sort_ws = nullptr;             // workspace of the sorted deposit, for sort_cap particles
+    int64_t sort_cap = 0;
     // second solve chain (QUMOND potential) for qumond_solve, created on first use
     bool chain2 = false;
     hipStream_t s2 = nullptr;
@@ -210,7 +210,6 @@ qumond_status qumond_destroy(qumond_ctx *ctx)
     ctx->mix.mg.release();
     ctx->mix2.mg.release();
     for (void *p : ctx->owned) (void)hipFree(p);
-    if (ctx->sort_ws) (void)hipFree(ctx->sort_ws);
     if (ctx->h_count) (void)hipHostFree(ctx->h_count);
     delete ctx;
     return QUMOND_OK;
@@ -324,41 +323,43 @@ int64_t qumond_device_bytes(const qumond_ctx *ctx)
                : 0;
 }
 
-// Whether this deposit takes the sorted form: it is the faster one, its
-// workspace is there or can be had (without it the window form runs as it always
-// did), and the stream is not being captured (a captured graph would keep the
-// address of a workspace that a later, larger deposit replaces).
+// Whether this deposit may take the sorted form: it can be the faster one, its
+// workspace is there or can be had, and the stream is not being captured (a
+// captured deposit records the window form, which needs no workspace).
 static bool sort_workspace(qumond_ctx *ctx, int64_t np)
 {
     if (!qm::deposit_sorts(ctx->n, ctx->cfg.nbox, np)) return false;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->s, &cap) != hipSuccess) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->s, &st) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    if (cap != hipStreamCaptureStatusNone) return false;
-    const size_t need = qm::deposit_sort_bytes(ctx->n, ctx->cfg.nbox, np);
-    if (need <= ctx->sort_bytes) return true;
+    if (st != hipStreamCaptureStatusNone) return false;
+    const int64_t cap = qm::deposit_sort_capacity(np);
+    if (cap <= ctx->sort_cap) return true;
     // the allocation belongs to no capture: it must not end one that another stream has begun
     struct Relaxed {
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
         ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
     } relaxed;
-    if (ctx->sort_ws) {
-        if (hipStreamSynchronize(ctx->s) != hipSuccess) return false;   // the last deposit may still use it
-        (void)hipFree(ctx->sort_ws);
-        ctx->bytes -= (int64_t)ctx->sort_bytes;
-        ctx->sort_ws = nullptr;
-        ctx->sort_bytes = 0;
+    // A smaller workspace stays until the context goes: the last deposit may
+    // still use it, and this call waits for nothing.  What the second chain of
+    // qumond_solve will allocate stays free.
+    size_t later = 0;
+    if (!ctx->chain2) {
+        later = ctx->mg.bytes + ctx->N * sizeof(double);
+        if (ctx->cfg.precision == QUMOND_MIXED) later += ctx->mix.mg.bytes + 3 * ctx->N * sizeof(float) + 4 * sizeof(double);
     }
-    if (hipMalloc(&ctx->sort_ws, need) != hipSuccess) {
+    const size_t need = qm::deposit_sort_bytes(ctx->n, ctx->cfg.nbox, cap);
+    size_t avail = 0, whole = 0;
+    void *ws = nullptr;
+    if (hipMemGetInfo(&avail, &whole) != hipSuccess || avail < need + later || ctx->alloc(&ws, need) != hipSuccess) {
         (void)hipGetLastError();
-        ctx->sort_ws = nullptr;
         return false;
     }
-    ctx->sort_bytes = need;
-    ctx->bytes += (int64_t)need;
+    ctx->sort_ws = ws;
+    ctx->sort_cap = cap;
     return true;
 }
 

@@ -271,9 +271,10 @@ void launch_deposit(const DepositArgs &a, const double *x, const double *y, cons
 // The same integers by way of a sort of the particles by cell tile, or by the
 // window where a sample of them says that it is the faster; a.q and inside_count
 // are cleared here.  deposit_sorts says where this can pay, ws holds
-// deposit_sort_bytes(n, nbox, np) bytes.
+// deposit_sort_bytes(n, nbox, deposit_sort_capacity(np)) bytes.
 bool deposit_sorts(int n, int nbox, int64_t np);
-size_t deposit_sort_bytes(int n, int nbox, int64_t np);
+int64_t deposit_sort_capacity(int64_t np);
+size_t deposit_sort_bytes(int n, int nbox, int64_t m);
 void launch_deposit_sorted(const DepositArgs &a, const double *x, const double *y, const double *z, const double *m,
                            int64_t np, unsigned long long *inside_count, void *ws, hipStream_t s);
 void launch_rhs_from_q(int n, double h, double four_pi_G, int shift, const long long *q, double *f, hipStream_t s);

@@ -567,10 +567,17 @@ constexpr int64_t kSortSlice = 1 << 26;   // particles sorted at a time
 
 static size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
-size_t deposit_sort_bytes(int n, int nbox, int64_t np)
+// A power of two, so that counts that creep up from call to call share a workspace.
+int64_t deposit_sort_capacity(int64_t np)
+{
+    int64_t m = 1 << 18;
+    while (m < np && m < kSortSlice) m *= 2;
+    return m;
+}
+
+size_t deposit_sort_bytes(int n, int nbox, int64_t m)
 {
     const TileGrid t = tile_grid(n, nbox);
-    const int64_t m = np < kSortSlice ? np : kSortSlice;
     return round256((size_t)m * sizeof(double4)) + round256((size_t)kSortBlocks * t.nbin * 4) + 2 * round256((size_t)t.nbin * 4) +
            round256(((size_t)m / kSegment + t.nbin + 1) * sizeof(int4)) + 512;
 }
