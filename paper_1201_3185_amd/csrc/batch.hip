@@ -370,6 +370,10 @@ hipError_t tune_class(qumond_batch *B, Class &C, int reps)
             float *fc = C.mg.lv[l - 1].f, *c0 = C.mg.lv[l - 1].u[0], *c1 = C.mg.lv[l - 1].u[1];
             {
                 for (int v = 0; v < qm::kRrVariants; ++v) {
+                    if (qm::is_rr_alias(v)) {
+                        rr_us[v] = rr_us[7];
+                        continue;
+                    }
                     qm::launch_residual_restrict_variant<float>(n, h, f, u0, fc, c0, c1, v, s, C.P);
                     std::vector<float> t;
                     for (int r = 0; r < reps; ++r) {

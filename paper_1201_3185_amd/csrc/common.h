@@ -132,7 +132,9 @@ struct SmootherShape {
 constexpr int kSmootherVariants = 16;
 constexpr int kRrVariants = 12;   // residual restriction: gather, 8x8x4 LDS tile, z-march of 16x8 columns over
                                   // 4/8/16-plane chunks, 4x4x4 and 4x4x2 LDS tiles, z-march of 32x8 columns:
-                                  // whole, over 128-, 64-, 16- and 32-plane chunks
+                                  // 7 in chunks that fill the chip, 9 over 64-plane chunks
+// 8, 10 and 11 are 7: tables saved when they were whole columns keep their speed
+inline bool is_rr_alias(int v) { return v == 8 || v == 10 || v == 11; }
 // bricks hold their whole block in LDS and take no z-chunk
 inline bool is_brick_variant(int v, bool fused) { return fused ? (v >= 2 && v <= 4) : (v == 5 || v == 9 || v == 10); }
 constexpr int kFusedVariants = 11;  // two sweeps: 0: 32x8, 1: 64x4 z-march, 2: 8^3, 3: 4^3, 4: 6^3 bricks,
@@ -192,7 +194,7 @@ template <typename T> void launch_residual_restrict_variant(int nf, double h, co
                                                            bool zero_u = true);
 template <typename T> int &rr_variant(int nf);
 // The z-march (rr_march.hip) over 16 x 8 or (wide) 32 x 8 coarse columns in chunks
-// of kc coarse planes (0: whole columns).
+// of kc coarse planes (0: as short as the chip needs; from 513^3 up no shorter).
 template <typename T> void launch_rr_march(int nf, double h, const T *f, const T *u, T *fc, T *uc0, T *uc1, int wide,
                                            int kc, hipStream_t s, int nb, int zu);
 template <typename T> void launch_restrict(int nf, const T *src, T *dst, hipStream_t s, int nb = 1);

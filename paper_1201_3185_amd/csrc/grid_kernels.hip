@@ -1610,9 +1610,9 @@ residual_restrict_tile_k(int nf, T ih2, const T *__restrict__ f, const T *__rest
 
 // Which residual-restriction kernel a fine level of n points uses (0: per-node
 // gather, 1: 8x8x4 LDS tile, 2/3/4: z-march of 16x8 columns over chunks of 4/8/16
-// coarse planes, 5: 4x4x4, 6: 4x4x2 LDS tiles, 7: z-march of whole 32x8 columns,
-// 10/11/9/8: of 32x8 columns over chunks of 16/32/64/128 planes), per precision;
-// set by the autotuner, gather by default.
+// coarse planes, 5: 4x4x4, 6: 4x4x2 LDS tiles, 7: z-march of 32x8 columns in chunks
+// that fill the chip, 9: over 64 planes; 8, 10, 11: as 7), per precision; set by the
+// autotuner, gather by default.
 static int g_rr_variant[2][11] = {{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}};
 
 template <typename T>
@@ -1637,7 +1637,7 @@ void launch_residual_restrict_variant(int nf, double h, const T *f, const T *u, 
         return;
     }
     if ((variant >= 2 && variant <= 4) || variant >= 7) {   // z-march over 16 x 8 or 32 x 8 coarse columns
-        constexpr int chunk[kRrVariants] = {0, 0, 4, 8, 16, 0, 0, 0, 128, 64, 16, 32};
+        constexpr int chunk[kRrVariants] = {0, 0, 4, 8, 16, 0, 0, 0, 0, 64, 0, 0};
         launch_rr_march<T>(nf, h, f, u, fc, uc0, uc1, variant >= 7, chunk[variant], s, nb, zu);
         return;
     }

@@ -25,8 +25,17 @@
 // 129^3 19.5 -> 12.4 (15.6 -> 9.9), 257^3 85.5 -> 61.8 (49.0 -> 31.5), 513^3
 // 520 -> 503 (294 -> 291) us.
 //
+// Chunks: without one given (kc 0), a column is cut until every CU has a workgroup
+// (FP32: two).  More of them only form the planes between chunks twice: 32 x 8
+// columns at 257^3, whole, 128, 64, 32 and 16 planes: 182, 181, 100, 62 and 63 us (FP32 122,
+// 120, 65, 38 and 31), at 513^3 511, 578, 686, 669 and 664 (308, 306, 334, 365 and
+// 370).  So from 513^3 up, where whole columns fill the chip, a shorter chunk is
+// not taken either (16 x 8 columns in 4, 8 and 16 planes 879, 743 and 685 us, whole 570).
+//
 // No value is masked: what is loaded outside the grid (clamped addresses) or
 // formed on the ring only enters residuals that no interior coarse node reads.
+#include <algorithm>
+
 #include "common.h"
 
 namespace qm {
@@ -191,8 +200,13 @@ template <typename T, int CX, int CY, int NT>
 void launch_tiles(int nf, double h, const T *f, const T *u, T *fc, T *uc0, T *uc1, int kc, hipStream_t s, int nb, int zu)
 {
     const int nc = (nf + 1) / 2;
-    if (kc <= 0 || kc > nc - 2) kc = nc - 2;
-    const int tx = (nc - 1 + CX - 1) / CX, ty = (nc - 1 + CY - 1) / CY, tzc = (nc - 2 + kc - 1) / kc;
+    const int tx = (nc - 1 + CX - 1) / CX, ty = (nc - 1 + CY - 1) / CY;
+    // the shortest chunk that leaves no more workgroups than one (FP32: two) for each of the 256 CUs
+    const long long want = sizeof(T) == 8 ? 256 : 512, tiles = (long long)tx * ty * nb;
+    const int fill = (int)((nc - 2) / ((want + tiles - 1) / tiles)) + 1;
+    if (kc <= 0 || nf >= 513) kc = std::max(kc, fill);
+    kc = std::min(kc, nc - 2);
+    const int tzc = (nc - 2 + kc - 1) / kc;
     hipLaunchKernelGGL((rr_march_k<T, CX, CY, NT>), dim3((unsigned)((size_t)tx * ty * tzc * nb)), dim3(NT), 0, s, nf,
                        T(1.0 / (h * h)), f, u, fc, uc0, uc1, tx, ty, tzc, kc, zu);
 }

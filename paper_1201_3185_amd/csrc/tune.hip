@@ -127,6 +127,10 @@ qumond_status tune_rr(int n, int reps, hipStream_t s, double us[qm::kRrVariants]
     (void)hipEventCreate(&e1);
     const double h = 1.0 / (n - 1);
     for (int v = 0; v < qm::kRrVariants; ++v) {
+        if (qm::is_rr_alias(v)) {
+            us[v] = us[7];
+            continue;
+        }
         qm::launch_residual_restrict_variant<T>(n, h, f, u, fc, c0, c1, v, s);
         std::vector<float> t;
         for (int r = 0; r < reps; ++r) {
