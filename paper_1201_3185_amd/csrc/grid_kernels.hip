@@ -1327,7 +1327,7 @@ static void rbgs_defaults()
 }
 
 static SmootherShape g_rbgs2_shape[2][11];
-static int g_use_fused[2][11] = {{1, 1, 1, 1, 1, 1, 1, 0, 0, 0, 0}, {1, 1, 1, 1, 1, 1, 1, 0, 0, 0, 0}};
+static int g_use_fused[2][11] = {{1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1}, {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1}};
 
 template <typename T>
 int &use_fused(int n)
@@ -1353,7 +1353,16 @@ int &split_prolong(int n)
 
 // One flag for both precisions: the defaults of the whole table are written
 // once, so an entry set for one precision is never reset by the first use of
-// the other.
+// the other.  By default a level runs its pairs of sweeps as one launch of the
+// shape that was the fastest of all at its size, in both precisions (FP64 us of a
+// pair, against 32x8 columns in 8- and 16-plane chunks up to 65^3 and two single
+// sweeps above): 33^3 4^3 bricks 7.6 against 25.7; 65^3 skewed 32x8 columns in
+// 4-plane chunks 9.4 against 39.6; from 129^3 skewed 64x16 columns, in 8-plane
+// chunks 16.6 against 41.9, at 257^3 in 64-plane chunks 85 against 273, and whole,
+// where they fill the chip, at 513^3 593 against 1646, at 1025^3 5.8 against 14.2 ms.
+// With these and the restriction's defaults the steps of a context for which no
+// table is loaded take what they take with the shipped one (513^3 166 -> 49.5 ms,
+// eleven 257^3 boxes 271 -> 92.7, four 129^3 boxes 28.8 -> 10.3, 65^3 5.6 -> 2.0).
 static bool g_rbgs2_init = false;
 
 template <typename T>
@@ -1363,10 +1372,10 @@ SmootherShape &rbgs2_shape(int n)
         for (int t = 0; t < 2; ++t)
             for (int J = 0; J <= 10; ++J) {
                 SmootherShape &sh = g_rbgs2_shape[t][J];
-                if (J <= 5) sh = {0, 8};
-                else if (J == 6) sh = {0, 16};
-                else if (J == 7) sh = {1, 16};
-                else sh = {1, 64};
+                if (J <= 4) sh = {0, 8};
+                else if (J == 5) sh = {3, 0};
+                else if (J == 6) sh = {kSkew32Variant, 4};
+                else sh = {kSkewVariant, J == 7 ? 8 : (J == 8 ? 64 : 0)};
             }
         g_rbgs2_init = true;
     }
@@ -1612,8 +1621,12 @@ residual_restrict_tile_k(int nf, T ih2, const T *__restrict__ f, const T *__rest
 // gather, 1: 8x8x4 LDS tile, 2/3/4: z-march of 16x8 columns over chunks of 4/8/16
 // coarse planes, 5: 4x4x4, 6: 4x4x2 LDS tiles, 7: z-march of 32x8 columns in chunks
 // that fill the chip, 9: over 64 planes; 8, 10, 11: as 7), per precision; set by the
-// autotuner, gather by default.
-static int g_rr_variant[2][11] = {{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}};
+// autotuner.  By default the fastest of all at each size (us, against the gather;
+// FP32 in brackets): 33^3 the 4x4x2 tiles 6.4 against 10.0 (6.2, 6.8), 65^3 the march
+// 8.1 against 10.5 (the gather 6.9, the march 7.3), 129^3 16x8 columns in 4-plane
+// chunks 12.4 against 29.7 (9.8, 17.2), above the march of 32x8 columns: 257^3 62
+// against 279 (32, 88), 513^3 511 against 2130 (307, 803), 1025^3 5.9 against 15.3 ms.
+static int g_rr_variant[2][11] = {{0, 0, 0, 0, 0, 6, 7, 2, 7, 7, 7}, {0, 0, 0, 0, 0, 6, 0, 2, 7, 7, 7}};
 
 template <typename T>
 int &rr_variant(int nf)
