@@ -45,13 +45,12 @@ qumond_status qumond_tune_get(int32_t n, int32_t fp32, int32_t *variant, int32_t
 qumond_status qumond_tune_set_corr(int32_t n, int32_t fp32, int32_t variant, int32_t kchunk);
 qumond_status qumond_tune_get_corr(int32_t n, int32_t fp32, int32_t *variant, int32_t *kchunk);
 
-/* The same for the fused two-sweep smoother (variant 0 = 32x8, 1 = 64x4
- * z-march, 2 = 8^3, 3 = 4^3, 4 = 6^3 bricks, 5 = 64x16, 6 = 64x8, 7 = 32x16
- * z-march with one thread per pair of tile nodes and loads two steps
- * ahead, 8 = 64x16, 9 = 32x8 and 10 = 32x16 marches with the four half-sweeps
+/* The same for the fused two-sweep smoother (variant 2 = 8^3, 3 = 4^3, 4 = 6^3
+ * bricks, 8 = 64x16, 9 = 32x8 and 10 = 32x16 marches with the four half-sweeps
  * skewed one plane apart, which apply the coarse-grid correction in the same
  * launch from coarse planes staged in LDS; their chunks are even and at least
- * 4, other values are rounded up).  Bricks ignore kchunk. */
+ * 4, other values are rounded up).  Bricks ignore kchunk.  0, 1 and 6 are 9, 5 is
+ * 8 and 7 is 10: marches that were slower at every size. */
 qumond_status qumond_tune_set_fused(int32_t n, int32_t fp32, int32_t variant, int32_t kchunk);
 qumond_status qumond_tune_get_fused(int32_t n, int32_t fp32, int32_t *variant, int32_t *kchunk);
 

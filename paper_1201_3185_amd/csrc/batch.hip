@@ -293,11 +293,9 @@ hipError_t tune_class(qumond_batch *B, Class &C, int reps)
             const int nvar = fz ? qm::kFusedVariants : qm::kSmootherVariants;
             for (int v = 0; v < nvar; ++v)
                 for (int kc : kTuneChunks) {
+                    if (fz && qm::is_fused_alias(v)) continue;
                     if (kc != 0 && kc >= n - 2) continue;
                     if (qm::is_brick_variant(v, fz != 0) && kc != 0) continue;
-                    // the other two-sweep marches lose to the skewed ones at every level (129^3, 257^3 and
-                    // 513^3 in FP32: 36, 100 and 700 us or more against 17, 51 and 409)
-                    if (fz && !qm::is_brick_variant(v, true) && v < qm::kSkewVariant) continue;
                     if (fz && kc != 0 && kc < 4) continue;   // the two-sweep march needs 4-plane chunks
                     const int nzc = kc ? (n - 2 + kc - 1) / kc : 1;
                     if (nzc > zmax) continue;

@@ -137,10 +137,10 @@ constexpr int kRrVariants = 12;   // residual restriction: gather, 8x8x4 LDS til
 inline bool is_rr_alias(int v) { return v == 8 || v == 10 || v == 11; }
 // bricks hold their whole block in LDS and take no z-chunk
 inline bool is_brick_variant(int v, bool fused) { return fused ? (v >= 2 && v <= 4) : (v == 5 || v == 9 || v == 10); }
-constexpr int kFusedVariants = 11;  // two sweeps: 0: 32x8, 1: 64x4 z-march, 2: 8^3, 3: 4^3, 4: 6^3 bricks,
-                                    // 5: 64x16, 6: 64x8, 7: 32x16 pair z-march with loads two steps ahead,
-                                    // 8: 64x16, 9: 32x8, 10: 32x16 columns with the four half-sweeps skewed
-                                    // (rbgs2_skew.hip; kchunk 0: whole columns, else an even chunk >= 4)
+constexpr int kFusedVariants = 11;  // two sweeps: 2: 8^3, 3: 4^3, 4: 6^3 bricks, 8: 64x16, 9: 32x8, 10: 32x16
+                                    // columns with the four half-sweeps skewed (rbgs2_skew.hip; kchunk 0: whole
+                                    // columns, else an even chunk >= 4); 0, 1, 6: as 9, 5: as 8, 7: as 10
+inline bool is_fused_alias(int v) { return v < 2 || (v >= 5 && v <= 7); }
 constexpr int kSkewVariant = 8, kSkew32Variant = 9, kSkew32x16Variant = 10;
 // Every grid launcher takes nb, the number of problems stored back to back
 // (problem p of a level with n points per side at offset p n^3); nb = 1 is the
@@ -158,9 +158,8 @@ template <typename T> SmootherShape &rbgs_shape(int n);   // the table entry use
 // variant below 0 (the default) means the level's plain-sweep shape.
 template <typename T> SmootherShape &rbgs_corr_shape(int n);
 template <typename T> SmootherShape rbgs_corr_effective(int n);
-// Two sweeps in one launch (variants 0: 32x8, 1: 64x4 z-march, 2: 8^3 bricks);
-// with uc != NULL the correction u += P uc (uc on the next coarser level) is
-// applied first.
+// Two sweeps in one launch; with uc != NULL (then uin too) the correction u += P uc
+// (uc on the next coarser level) is applied first.  A null uin is a zero iterate.
 template <typename T> void launch_rbgs2(int n, double h, const T *f, const T *uin, T *uout, const T *uc,
                                        hipStream_t s, int nb = 1);
 template <typename T> void launch_rbgs2_shape(int n, double h, const T *f, const T *uin, T *uout, const T *uc,
@@ -169,8 +168,8 @@ template <typename T> SmootherShape &rbgs2_shape(int n);
 // ---- rbgs2_skew.hip
 // Two sweeps uin -> uout in one column march with the four half-sweeps skewed
 // one plane apart (same bits as two single sweeps); uin null is a zero
-// iterate; with uc != NULL the correction u += P uc (uc on the next coarser
-// level) is applied first, in the same launch (same bits as a prolong-add).
+// iterate; with uc != NULL (then uin too) the correction u += P uc (uc on the next
+// coarser level) is applied first, in the same launch (same bits as a prolong-add).
 // tile 0: 64x16, 1: 32x8, 2: 32x16 columns; kchunk: planes a workgroup marches (0: the whole column; odd values are rounded up).
 template <typename T> void launch_rbgs2_skew(int n, double h, const T *f, const T *uin, T *uout, hipStream_t s, int nb,
                                             const T *uc = nullptr, int tile = 0, int kchunk = 0);

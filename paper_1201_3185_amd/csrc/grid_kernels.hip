@@ -950,354 +950,24 @@ static void brick_launch(int n, double h, const T *f, const T *uin, T *uout, con
 }
 
 // ----------------------------------------------------- two fused sweeps
-//
-// Two red-black sweeps (A then B) in one pass: four stages one z plane
-// apart run behind each other in the march, each on a ring one node narrower
-// than the stage before (red A on the tile plus three nodes, black A plus two,
-// red B plus one, black B on the tile), so every stage finds the values it
-// needs in LDS.  A plane's LDS copy is updated in place: each stage writes one
-// colour and reads only the other, whose newest values are the ones the
-// sequential sweeps would read.  Each node update is the same expression as in
-// rbgs_zmarch, so the result equals two separate sweeps bit for bit.  With
-// PROLONG the coarse-grid correction u += P uc is applied to every interior
-// node as its plane is loaded (the post-smoothing of a V-cycle).
-template <typename T, int TX, int TY, bool PROLONG>
-__global__ void __launch_bounds__(TX *TY)
-rbgs2_zmarch(const T *__restrict__ uin, T *__restrict__ uout, const T *__restrict__ f, int n, T h2, int kchunk,
-             const T *__restrict__ uc, int nc, int nzc)
-{
-#pragma clang fp contract(off)
-    constexpr int R = 4;                         // ring of the LDS planes
-    constexpr int PX = TX + 2 * R, PY = TY + 2 * R, NT = TX * TY;
-    constexpr int PL = PX * PY;
-    constexpr int FX = TX + 6, FY = TY + 6, FL = FX * FY;   // f on the ring-3 region
-    constexpr int NS = 7, NF = 5;
-    constexpr int NL = (PL + NT - 1) / NT, NFL = (FL + NT - 1) / NT;
-    __shared__ T pl[NS][PL];
-    __shared__ T fp[NF][FL];
-    const T sixth = T(1) / T(6);
-    const int tid = threadIdx.x;
-    const unsigned tl = xcd_tile(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z),
-                                 gridDim.x * gridDim.y * gridDim.z);
-    const int bx = tl % gridDim.x, by = (tl / gridDim.x) % gridDim.y, bzz = tl / (gridDim.x * gridDim.y);
-    const int i0 = 1 + bx * TX, j0 = 1 + by * TY;
-    const int pb = bzz / nzc;
-    const int kb = 1 + (bzz - pb * nzc) * kchunk;
-    if (kb > n - 2) return;
-    const int ke = min(kb + kchunk - 1, n - 2);
-    const size_t nn = (size_t)n * n;
-    // a null uin (zero iterate) stays null: only a real array is offset
-    if (uin) uin += (size_t)pb * nn * n;
-    uout += (size_t)pb * nn * n;
-    f += (size_t)pb * nn * n;
-    if (PROLONG) uc += (size_t)pb * nc * nc * nc;
 
-    int goff[NL], gi[NL], gj[NL];
-#pragma unroll
-    for (int r = 0; r < NL; ++r) {
-        const int t = tid + r * NT;
-        const int a = t % PX, b = t / PX;
-        gi[r] = i0 - R + a;
-        gj[r] = j0 - R + b;
-        goff[r] = (t < PL && gi[r] >= 0 && gi[r] < n && gj[r] >= 0 && gj[r] < n) ? gi[r] + n * gj[r] : -1;
-    }
-    int foff[NFL];
-#pragma unroll
-    for (int r = 0; r < NFL; ++r) {
-        const int t = tid + r * NT;
-        const int a = t % FX, b = t / FX;
-        const int i = i0 - 3 + a, j = j0 - 3 + b;
-        foff[r] = (t < FL && i >= 1 && i <= n - 2 && j >= 1 && j <= n - 2) ? i + n * j : -1;
-    }
-    T v[NL], w[NFL];
-    auto prefetch_u = [&](int k) {
-        const T *src = uin ? uin + (size_t)k * nn : nullptr;   // null: a zero iterate, read from nowhere
-        const bool inner_plane = k >= 1 && k <= n - 2;
-#pragma unroll
-        for (int r = 0; r < NL; ++r) {
-            T x = goff[r] >= 0 ? (src ? src[goff[r]] : T(0)) : T(0);
-            if (PROLONG && inner_plane && goff[r] >= 0 && gi[r] >= 1 && gi[r] <= n - 2 && gj[r] >= 1 && gj[r] <= n - 2)
-                x += prolong_at(nc, uc, gi[r], gj[r], k);
-            v[r] = x;
-        }
-    };
-    auto commit_u = [&](int k) {
-        T *P = pl[k % NS];
-#pragma unroll
-        for (int r = 0; r < NL; ++r) {
-            const int t = tid + r * NT;
-            if (t < PL) P[t] = v[r];
-        }
-    };
-    auto prefetch_f = [&](int k) {
-        const T *src = f + (size_t)k * nn;
-#pragma unroll
-        for (int r = 0; r < NFL; ++r) w[r] = foff[r] >= 0 ? src[foff[r]] : T(0);
-    };
-    auto commit_f = [&](int k) {
-        T *F = fp[k % NF];
-#pragma unroll
-        for (int r = 0; r < NFL; ++r) {
-            const int t = tid + r * NT;
-            if (t < FL) F[t] = w[r];
-        }
-    };
-    // one colour of plane k on the tile plus `ring` nodes
-    auto stage = [&](int k, int ring, int colour) {
-        T *P = pl[k % NS];
-        const T *Pm = pl[(k + NS - 1) % NS];
-        const T *Pp = pl[(k + 1) % NS];
-        const T *F = fp[k % NF];
-        const int hw = (TX + 2 * ring) / 2, rows = TY + 2 * ring, a0 = R - ring;
-        for (int t = tid; t < hw * rows; t += NT) {
-            const int b = a0 + t / hw;
-            const int j = j0 - R + b;
-            const int ia0 = i0 - R + a0;
-            const int a = a0 + (((ia0 + j + k) & 1) == colour ? 0 : 1) + 2 * (t % hw);
-            const int i = i0 - R + a;
-            if (i < 1 || i > n - 2 || j < 1 || j > n - 2) continue;
-            const int c = b * PX + a;
-            const T s = P[c - 1] + P[c + 1] + P[c - PX] + P[c + PX] + Pm[c] + Pp[c];
-            P[c] = (s - h2 * F[(b - 1) * FX + (a - 1)]) * sixth;
-        }
-    };
-    auto store = [&](int k) {
-        const T *P = pl[k % NS];
-        for (int t = tid; t < TX * TY; t += NT) {
-            const int a = R + t % TX, b = R + t / TX;
-            const int i = i0 - R + a, j = j0 - R + b;
-            if (i > n - 2 || j > n - 2) continue;
-            uout[(size_t)k * nn + i + (size_t)n * j] = P[b * PX + a];
-        }
-    };
-    auto in_u = [&](int k) { return k >= max(0, kb - 4) && k <= min(n - 1, ke + 4); };
-    auto in_f = [&](int k) { return k >= max(1, kb - 3) && k <= min(n - 2, ke + 3); };
-    auto in_stage = [&](int k, int lag) { return k >= max(1, kb - lag) && k <= min(n - 2, ke + lag); };
-
-    if (in_u(kb - 4)) prefetch_u(kb - 4);
-    if (in_f(kb - 5)) prefetch_f(kb - 5);
-    for (int k = kb - 8; k <= ke; ++k) {
-        if (in_u(k + 4)) commit_u(k + 4);
-        if (in_f(k + 3)) commit_f(k + 3);
-        if (in_u(k + 5)) prefetch_u(k + 5);
-        if (in_f(k + 4)) prefetch_f(k + 4);
-        __syncthreads();
-        if (in_stage(k + 3, 3)) stage(k + 3, 3, 0);      // red, sweep A
-        __syncthreads();
-        if (in_stage(k + 2, 2)) stage(k + 2, 2, 1);      // black, sweep A
-        __syncthreads();
-        if (in_stage(k + 1, 1)) stage(k + 1, 1, 0);      // red, sweep B
-        __syncthreads();
-        if (k >= kb) {
-            stage(k, 0, 1);                              // black, sweep B
-            __syncthreads();
-            store(k);
-        }
-    }
-}
-
-// The two-sweep march with one thread per pair of tile nodes and every load
-// two steps ahead (u plane k+6 and f plane k+5 are requested in step k, two
-// register sets alternating between even and odd steps), for large levels
-// where the fused launch should move u and f once for two sweeps.  Six LDS
-// planes of u (tile + four-node ring: step k reads planes k-1..k+4, and the
-// store of plane k+4 at the start of step k takes the slot of plane k-2) and
-// four of f (planes k..k+3 on the three-node ring).  The four stages, their
-// regions and every node update are those of rbgs2_zmarch, so the bits are
-// too; with PROLONG the correction u += P uc is prolong_at's, added as u is
-// loaded.
-template <typename T, int TX, int TY, bool PROLONG>
-__global__ void __launch_bounds__(TX *TY / 2)
-rbgs2_zmarch_deep(const T *__restrict__ uin, T *__restrict__ uout, const T *__restrict__ f, int n, T h2, int kchunk,
-                  const T *__restrict__ uc, int nc, int nzc)
-{
-#pragma clang fp contract(off)
-    constexpr int R = 4;
-    constexpr int PX = TX + 2 * R, PY = TY + 2 * R, NT = TX * TY / 2;
-    constexpr int PL = PX * PY;
-    constexpr int FX = TX + 6, FY = TY + 6, FL = FX * FY;
-    constexpr int NS = 6, NF = 4;
-    constexpr int NL = (PL + NT - 1) / NT, NFL = (FL + NT - 1) / NT;
-    __shared__ T pl[NS][PL];
-    __shared__ T fp[NF][FL];
-    const T sixth = T(1) / T(6);
-    const int tid = threadIdx.x;
-    const unsigned tl = xcd_tile(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z),
-                                 gridDim.x * gridDim.y * gridDim.z);
-    const int bx = tl % gridDim.x, by = (tl / gridDim.x) % gridDim.y, bzz = tl / (gridDim.x * gridDim.y);
-    const int i0 = 1 + bx * TX, j0 = 1 + by * TY;
-    const int pb = bzz / nzc;
-    const int kb = 1 + (bzz - pb * nzc) * kchunk;
-    if (kb > n - 2) return;
-    const int ke = min(kb + kchunk - 1, n - 2);
-    const size_t nn = (size_t)n * n;
-    if (uin) uin += (size_t)pb * nn * n;   // a null uin (zero iterate) stays null
-    uout += (size_t)pb * nn * n;
-    f += (size_t)pb * nn * n;
-    if (PROLONG) uc += (size_t)pb * nc * nc * nc;
-
-    int goff[NL], gij[NL];
-#pragma unroll
-    for (int r = 0; r < NL; ++r) {
-        const int t = tid + r * NT;
-        const int a = t % PX, b = t / PX;
-        const int i = i0 - R + a, j = j0 - R + b;
-        goff[r] = (t < PL && i >= 0 && i < n && j >= 0 && j < n) ? i + n * j : -1;
-        gij[r] = (goff[r] >= 0 && i >= 1 && i <= n - 2 && j >= 1 && j <= n - 2) ? (i | (j << 16)) : -1;
-    }
-    int foff[NFL];
-#pragma unroll
-    for (int r = 0; r < NFL; ++r) {
-        const int t = tid + r * NT;
-        const int a = t % FX, b = t / FX;
-        const int i = i0 - 3 + a, j = j0 - 3 + b;
-        foff[r] = (t < FL && i >= 1 && i <= n - 2 && j >= 1 && j <= n - 2) ? i + n * j : -1;
-    }
-    auto fetch_u = [&](int k, T *vv) {
-        const T *src = uin ? uin + (size_t)k * nn : nullptr;
-        const bool inner_plane = k >= 1 && k <= n - 2;
-#pragma unroll
-        for (int r = 0; r < NL; ++r) {
-            T x = goff[r] >= 0 ? (src ? src[goff[r]] : T(0)) : T(0);
-            if (PROLONG && inner_plane && gij[r] >= 0) x += prolong_at(nc, uc, gij[r] & 0xffff, gij[r] >> 16, k);
-            vv[r] = x;
-        }
-    };
-    auto commit_u = [&](int k, const T *vv) {
-        T *P = pl[k % NS];
-#pragma unroll
-        for (int r = 0; r < NL; ++r) {
-            const int t = tid + r * NT;
-            if (t < PL) P[t] = vv[r];
-        }
-    };
-    auto fetch_f = [&](int k, T *ww) {
-        const T *src = f + (size_t)k * nn;
-#pragma unroll
-        for (int r = 0; r < NFL; ++r) ww[r] = foff[r] >= 0 ? src[foff[r]] : T(0);
-    };
-    auto commit_f = [&](int k, const T *ww) {
-        T *F = fp[k % NF];
-#pragma unroll
-        for (int r = 0; r < NFL; ++r) {
-            const int t = tid + r * NT;
-            if (t < FL) F[t] = ww[r];
-        }
-    };
-    auto stage = [&](int k, int ring, int colour) {   // one colour of plane k on the tile plus `ring` nodes
-        T *P = pl[k % NS];
-        const T *Pm = pl[(k + NS - 1) % NS];
-        const T *Pp = pl[(k + 1) % NS];
-        const T *F = fp[k % NF];
-        const int hw = (TX + 2 * ring) / 2, rows = TY + 2 * ring, a0 = R - ring;
-        for (int t = tid; t < hw * rows; t += NT) {
-            const int b = a0 + t / hw;
-            const int j = j0 - R + b;
-            const int ia0 = i0 - R + a0;
-            const int a = a0 + (((ia0 + j + k) & 1) == colour ? 0 : 1) + 2 * (t % hw);
-            const int i = i0 - R + a;
-            if (i < 1 || i > n - 2 || j < 1 || j > n - 2) continue;
-            const int c = b * PX + a;
-            const T sum = P[c - 1] + P[c + 1] + P[c - PX] + P[c + PX] + Pm[c] + Pp[c];
-            P[c] = (sum - h2 * F[(b - 1) * FX + (a - 1)]) * sixth;
-        }
-    };
-    auto store = [&](int k) {
-        const T *P = pl[k % NS];
-        for (int t = tid; t < TX * TY; t += NT) {
-            const int a = R + t % TX, b = R + t / TX;
-            const int i = i0 - R + a, j = j0 - R + b;
-            if (i > n - 2 || j > n - 2) continue;
-            uout[(size_t)k * nn + i + (size_t)n * j] = P[b * PX + a];
-        }
-    };
-    auto in_u = [&](int k) { return k >= max(0, kb - 4) && k <= min(n - 1, ke + 4); };
-    auto in_f = [&](int k) { return k >= max(1, kb - 3) && k <= min(n - 2, ke + 3); };
-    auto in_stage = [&](int k, int lag) { return k >= max(1, kb - lag) && k <= min(n - 2, ke + lag); };
-
-    // step k stores u plane k+4 and f plane k+3 and requests u plane k+6 and
-    // f plane k+5; set A serves the steps of kb's parity
-    const int k0 = kb - 8;
-    T uA[NL], uB[NL], fA[NFL], fB[NFL];
-#pragma unroll
-    for (int r = 0; r < NL; ++r) uA[r] = uB[r] = T(0);
-#pragma unroll
-    for (int r = 0; r < NFL; ++r) fA[r] = fB[r] = T(0);
-    if (in_u(k0 + 4)) fetch_u(k0 + 4, uA);
-    if (in_f(k0 + 3)) fetch_f(k0 + 3, fA);
-    if (in_u(k0 + 5)) fetch_u(k0 + 5, uB);
-    if (in_f(k0 + 4)) fetch_f(k0 + 4, fB);
-    auto step = [&](int k, T *uX, T *fX) {
-        if (in_u(k + 4)) commit_u(k + 4, uX);
-        if (in_f(k + 3)) commit_f(k + 3, fX);
-        if (in_u(k + 6)) fetch_u(k + 6, uX);
-        if (in_f(k + 5)) fetch_f(k + 5, fX);
-        __syncthreads();
-        if (in_stage(k + 3, 3)) stage(k + 3, 3, 0);      // red, sweep A
-        __syncthreads();
-        if (in_stage(k + 2, 2)) stage(k + 2, 2, 1);      // black, sweep A
-        __syncthreads();
-        if (in_stage(k + 1, 1)) stage(k + 1, 1, 0);      // red, sweep B
-        __syncthreads();
-        if (k >= kb) {
-            stage(k, 0, 1);                              // black, sweep B
-            __syncthreads();
-            store(k);
-        }
-    };
-    for (int k = k0; k <= ke; k += 2) {
-        step(k, uA, fA);
-        if (k + 1 <= ke) step(k + 1, uB, fB);
-    }
-}
-
-template <typename T, int TX, int TY>
-static void rbgs2_deep_launch(int n, double h, const T *f, const T *uin, T *uout, int kchunk, const T *uc, int nb,
-                              hipStream_t s)
-{
-    const int m = n - 2;
-    const int nzc = (m + kchunk - 1) / kchunk;
-    dim3 grid((m + TX - 1) / TX, (m + TY - 1) / TY, nzc * nb);
-    if (uc)
-        hipLaunchKernelGGL((rbgs2_zmarch_deep<T, TX, TY, true>), grid, dim3(TX * TY / 2), 0, s, uin, uout, f, n,
-                           T(h * h), kchunk, uc, (n + 1) / 2, nzc);
-    else
-        hipLaunchKernelGGL((rbgs2_zmarch_deep<T, TX, TY, false>), grid, dim3(TX * TY / 2), 0, s, uin, uout, f, n,
-                           T(h * h), kchunk, uc, (n + 1) / 2, nzc);
-}
-
-template <typename T, int TX, int TY>
-static void rbgs2_launch(int n, double h, const T *f, const T *uin, T *uout, int kchunk, const T *uc, int nb,
-                         hipStream_t s)
-{
-    const int m = n - 2;
-    const int nzc = (m + kchunk - 1) / kchunk;
-    dim3 grid((m + TX - 1) / TX, (m + TY - 1) / TY, nzc * nb);
-    if (uc)
-        hipLaunchKernelGGL((rbgs2_zmarch<T, TX, TY, true>), grid, dim3(TX * TY), 0, s, uin, uout, f, n, T(h * h), kchunk,
-                           uc, (n + 1) / 2, nzc);
-    else
-        hipLaunchKernelGGL((rbgs2_zmarch<T, TX, TY, false>), grid, dim3(TX * TY), 0, s, uin, uout, f, n, T(h * h),
-                           kchunk, uc, (n + 1) / 2, nzc);
-}
-
+// Indexes 0, 1, 5, 6 and 7 were marches with the half-sweeps in LDS planes of both
+// colours.  They lost to the skewed ones at every size from 5^3 to 513^3 (best chunk of
+// each, FP64 us of a pair at 33^3, 129^3 and 513^3: 18.3, 39.9 and 1639 against 7.5,
+// 16.9 and 592) and are the skewed columns of their size.
 template <typename T>
 void launch_rbgs2_shape(int n, double h, const T *f, const T *uin, T *uout, const T *uc, SmootherShape sh, hipStream_t s,
                         int nb)
 {
-    const int kc = sh.kchunk > 0 ? sh.kchunk : n;
     switch (sh.variant) {
-    case 0: rbgs2_launch<T, 32, 8>(n, h, f, uin, uout, kc, uc, nb, s); break;
     case 2: brick_launch<T, 2>(n, h, f, uin, uout, uc, nb, s); break;
     case 3: brick_launch<T, 2, 4>(n, h, f, uin, uout, uc, nb, s); break;
     case 4: brick_launch<T, 2, 6>(n, h, f, uin, uout, uc, nb, s); break;
-    case 5: rbgs2_deep_launch<T, 64, 16>(n, h, f, uin, uout, kc, uc, nb, s); break;
-    case 6: rbgs2_deep_launch<T, 64, 8>(n, h, f, uin, uout, kc, uc, nb, s); break;
-    case 7: rbgs2_deep_launch<T, 32, 16>(n, h, f, uin, uout, kc, uc, nb, s); break;
+    case 5:
     case kSkewVariant: launch_rbgs2_skew<T>(n, h, f, uin, uout, s, nb, uc, 0, sh.kchunk); break;
+    case 7:
     case kSkew32x16Variant: launch_rbgs2_skew<T>(n, h, f, uin, uout, s, nb, uc, 2, sh.kchunk); break;
-    case kSkew32Variant: launch_rbgs2_skew<T>(n, h, f, uin, uout, s, nb, uc, 1, sh.kchunk); break;
-    default: rbgs2_launch<T, 64, 4>(n, h, f, uin, uout, kc, uc, nb, s); break;
+    default: launch_rbgs2_skew<T>(n, h, f, uin, uout, s, nb, uc, 1, sh.kchunk); break;
     }
 }
 
@@ -1355,8 +1025,8 @@ int &split_prolong(int n)
 // once, so an entry set for one precision is never reset by the first use of
 // the other.  By default a level runs its pairs of sweeps as one launch of the
 // shape that was the fastest of all at its size, in both precisions (FP64 us of a
-// pair, against 32x8 columns in 8- and 16-plane chunks up to 65^3 and two single
-// sweeps above): 33^3 4^3 bricks 7.6 against 25.7; 65^3 skewed 32x8 columns in
+// pair, against a march of 32x8 columns in 8- and 16-plane chunks up to 65^3 and two
+// single sweeps above): up to 33^3 4^3 bricks 7.6 against 25.7; 65^3 skewed 32x8 columns in
 // 4-plane chunks 9.4 against 39.6; from 129^3 skewed 64x16 columns, in 8-plane
 // chunks 16.6 against 41.9, at 257^3 in 64-plane chunks 85 against 273, and whole,
 // where they fill the chip, at 513^3 593 against 1646, at 1025^3 5.8 against 14.2 ms.
@@ -1372,8 +1042,7 @@ SmootherShape &rbgs2_shape(int n)
         for (int t = 0; t < 2; ++t)
             for (int J = 0; J <= 10; ++J) {
                 SmootherShape &sh = g_rbgs2_shape[t][J];
-                if (J <= 4) sh = {0, 8};
-                else if (J == 5) sh = {3, 0};
+                if (J <= 5) sh = {3, 0};
                 else if (J == 6) sh = {kSkew32Variant, 4};
                 else sh = {kSkewVariant, J == 7 ? 8 : (J == 8 ? 64 : 0)};
             }

@@ -333,11 +333,8 @@ static void skew_launch(int n, double h, const T *f, const T *uin, T *uout, hipS
     const int nchunk = (n - 1 + kc - 1) / kc;
     const dim3 grid((m + TX - 1) / TX, (m + TY - 1) / TY, nb * nchunk);
     const int nc = (n + 1) / 2;
-    if (uc && uin)
+    if (uc)
         hipLaunchKernelGGL((rbgs2_skew_k<T, TX, TY, NT, false, true>), grid, dim3(NT), 0, s, uin, uout, f, n, T(h * h),
-                           uc, nc, kc, nchunk);
-    else if (uc)
-        hipLaunchKernelGGL((rbgs2_skew_k<T, TX, TY, NT, true, true>), grid, dim3(NT), 0, s, uin, uout, f, n, T(h * h),
                            uc, nc, kc, nchunk);
     else if (uin)
         hipLaunchKernelGGL((rbgs2_skew_k<T, TX, TY, NT, false, false>), grid, dim3(NT), 0, s, uin, uout, f, n, T(h * h),

@@ -64,6 +64,7 @@ qumond_status tune_one(int n, int reps, hipStream_t s, double &best_us, bool fus
     const int nvar = fused ? qm::kFusedVariants : qm::kSmootherVariants;
     for (int v = 0; v < nvar; ++v)
         for (int kc : kChunks) {
+            if (fused && qm::is_fused_alias(v)) continue;
             if (kc != 0 && kc >= n - 2) continue;
             if (qm::is_brick_variant(v, fused) && kc != 0) continue;
             if (fused && kc != 0 && kc < 4) continue;   // the two-sweep march needs 4-plane chunks
