@@ -240,17 +240,25 @@ __device__ __forceinline__ void choose_form(const DepositArgs &A, const TileGrid
 {
     __shared__ unsigned seen[kMaxTiles / 32];   // a bit per tile
     __shared__ unsigned beyond, tiles;
+    constexpr int NS = kSample / kStartThreads;
+    double sx[NS], sy[NS], sz[NS];               // all in flight before the LDS is cleared
+#pragma unroll
+    for (int r = 0; r < NS; ++r) {
+        const unsigned i = threadIdx.x + kStartThreads * r;
+        // a place of its own in every run: lists have periods
+        const float at = ((float)(i * 2654435769u) * 0x1p-32f) * ((float)np / kSample);
+        const int p = min((int)((long long)i * np / kSample) + (int)at, np - 1);
+        sx[r] = x[p];
+        sy[r] = y[p];
+        sz[r] = z[p];
+    }
     for (int e = threadIdx.x; e < kMaxTiles / 32; e += kStartThreads) seen[e] = 0;
     if (threadIdx.x == 0) beyond = tiles = 0;
     __syncthreads();
     unsigned out = 0;
 #pragma unroll
-    for (int r = 0; r < kSample / kStartThreads; ++r) {
-        const unsigned i = threadIdx.x + kStartThreads * r;
-        // a place of its own in every run: lists have periods
-        const double at = ((double)i + (double)(i * 2654435769u) * 0x1p-32) * ((double)np / kSample);
-        const int p = min((int)at, np - 1);
-        const double px = x[p], py = y[p], pz = z[p];
+    for (int r = 0; r < NS; ++r) {
+        const double px = sx[r], py = sy[r], pz = sz[r];
         bool in0;
         const int bin = tile_of(A, T, px, py, pz, in0);
         if (bin >= 0) atomicOr(&seen[bin >> 5], 1u << (bin & 31));
@@ -558,9 +566,11 @@ bool deposit_sorts(int n, int nbox, int64_t np)
     return n >= 129 && np >= 250000 && tile_grid(n, nbox).nbin <= kMaxTiles;
 }
 
-// Where a sample decides between the forms.  It costs 4 us and the launches that
-// end at once, more than it can save below 1e6 particles on at most 257^3 (250 000
-// of the sets above: the sorted form takes at most 7 % longer there).
+// Where a sample decides between the forms.  It costs up to 3 us (disks, one box:
+// 1e6 particles on 257^3 126 -> 129 us; in three boxes the launches saved outweigh
+// it, 3e6 particles 425 -> 419), and in the window form two launches that end at
+// once: more than it can save below 1e6 particles on at most 257^3 (250 000 of the
+// sets above: the sorted form takes at most 7 % longer there).
 static int deposit_samples(int n, int np) { return n > 257 || np >= 1000000; }
 
 constexpr int64_t kSortSlice = 1 << 26;   // particles sorted at a time
