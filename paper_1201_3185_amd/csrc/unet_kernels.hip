@@ -138,20 +138,27 @@ conv3d_fwd_k(Tensor x, int cin, const __bf16 *__restrict__ wt, int kpad, const f
 // Within a chunk of cc channels the K-steps of 32 cover 32 / cc taps at a time,
 // in the same (tap, channel) order as conv3d_fwd_k.
 //
-// A workgroup takes a run of tiles.  What bounds it is latency, then the LDS
-// reads (one per MFMA at 16 output channels): all loads of a chunk are in flight
-// at once, during the MFMAs of the chunk or tile before (a loop of load and
-// store had waited for each of its ten loads in turn); weights come a group of
-// taps ahead, or stay in registers for the run (16 and 8 input channels); with 32
-// channels an input row is read once for the up to three dy that meet it; and
-// output channels are the rows of the product, so a lane stores four of them at
-// once.  Before -> now, same bits: 48 -> 16 channels at 129^3 451 -> 230 us, 16 ->
-// 16 180 -> 87, 8 -> 16 104 -> 49, 96 -> 32 at 65^3 164 -> 134, 64 -> 64 at 17^3 55 -> 21.
+// What bounds it is latency, then the LDS reads (one per MFMA at 16 output channels):
+// all loads of a chunk are in flight at once (a loop of load and store had waited
+// for each of its ten loads in turn); weights come a tap or a group of taps ahead,
+// or stay in registers (16 and 8 input channels); and output channels are the rows
+// of the product, so a lane stores four of them at once.  NB blocks of 16 output
+// channels share a staged tile.
+//
+// AHEAD: a workgroup takes a run of tiles and loads the next chunk or tile during
+// the MFMAs of this one.  That pays with 8, 16 and 48 input channels.  In whole
+// chunks of 32 the registers of those loads cost a wavefront per SIMD, which is
+// worth more: a tile per workgroup, NB up to 4 (32 -> 32 channels at 97^3 with runs
+// 105 us at best, without 93; 64 -> 64 531 and 492; 96 -> 32 358 and 277).
+//
+// The first form, one tile per workgroup for all channels with every load waited for
+// -> now, same bits: 48 -> 16 channels at 129^3 417 -> 210 us, 16 -> 16 180 -> 87, 8 -> 16
+// 104 -> 49, 96 -> 32 at 65^3 151 -> 99, 32 -> 64 at 97^3 217 -> 166, 64 -> 64 512 -> 492.
 constexpr int kTileX = 16, kTileY = 4, kTileZ = 4;
 constexpr int kInX = kTileX + 2, kInY = kTileY + 2, kInZ = kTileZ + 2, kInV = kInX * kInY * kInZ;
 
-template <int NB, int C0>
-__global__ void __launch_bounds__(256, 3)
+template <int NB, int C0, bool AHEAD>
+__global__ void __launch_bounds__(256, AHEAD && C0 == 32 && NB > 1 ? 2 : 3)
 conv3d_fwd_lds_k(Tensor x, int cin, const __bf16 *__restrict__ wt, int kpad, const float *__restrict__ bias, Tensor y,
                  int relu, int tx, int ty, int tiles, int per)
 {
@@ -248,6 +255,35 @@ conv3d_fwd_lds_k(Tensor x, int cin, const __bf16 *__restrict__ wt, int kpad, con
                 for (int b = 0; b < NB; ++b) w[0][e][b] = w[1][e][b];
         }
     };
+    // ... a tap at a time, its rows and weights one tap ahead, in a third of the registers
+    auto chunk32_taps = [&](int cb) {
+        const __bf16 *wp = wrow + cb + 8 * g;
+        auto weights = [&](int tap, bf16x8 *w) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) w[b] = frag(wp + (size_t)(b * 16) * kpad + tap * cin);
+        };
+        auto rows = [&](const __bf16 *p, int t, bf16x8 *a) {   // of tap t = dx + 3 dy
+#pragma unroll
+            for (int y = 0; y < RB; ++y) a[y] = frag(p + (t % 3 + kInX * (t / 3 + y)) * kPitch);
+        };
+        bf16x8 w[2][NB], a[2][RB];
+        weights(0, w[0]);
+#pragma unroll 1
+        for (int dz = 0; dz < 3; ++dz) {
+            const __bf16 *p = mine + kInX * kInY * dz * kPitch + 8 * g;
+            rows(p, 0, a[0]);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                if (t < 8) rows(p, t + 1, a[(t + 1) & 1]);
+                weights(min(9 * dz + t + 1, 26), w[(t + 1) & 1]);
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) mac(rb, a[t & 1][rb], w[t & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) w[0][b] = w[1][b];     // nine taps, two sets
+        }
+    };
     // 16 or 8 channels: 2 or 4 taps per K-step, by the lane's quarter; the last
     // step's taps beyond 26 count as zeros
     auto chunk_small = [&](auto CC, int cb, auto &&weight) {
@@ -301,23 +337,30 @@ conv3d_fwd_lds_k(Tensor x, int cin, const __bf16 *__restrict__ wt, int kpad, con
 #pragma unroll
         for (int st = 0; st < KS; ++st) get(st, kept[st]);
     }
-    fetch(t, 0);
+    if constexpr (AHEAD) fetch(t, 0);
     for (; t < tend; ++t) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int b = 0; b < NB; ++b) acc[rb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int cb = 0; cb < cin; cb += C0) {
+            if constexpr (!AHEAD) fetch(t, cb);
             __syncthreads();             // the fragments of the chunk before are read
             commit();
             __syncthreads();
-            if (cb + C0 < cin) fetch(t, cb + C0);
-            else if (t + 1 < tend) fetch(t + 1, 0);
+            if constexpr (AHEAD) {
+                if (cb + C0 < cin) fetch(t, cb + C0);
+                else if (t + 1 < tend) fetch(t + 1, 0);
+            }
             if constexpr (C0 == 32) {
-                const int cc = min(C0, cin - cb);
-                const std::integral_constant<int, 16> c16;
-                if (cc == 32) chunk32(cb);
-                else chunk_small(c16, cb, from_memory(c16, cb));    // the rest of 48 channels
+                if constexpr (!AHEAD) {                // whole chunks alone
+                    chunk32_taps(cb);
+                } else {
+                    const int cc = min(C0, cin - cb);
+                    const std::integral_constant<int, 16> c16;
+                    if (cc == 32) chunk32(cb);
+                    else chunk_small(c16, cb, from_memory(c16, cb));    // the rest of 48 channels
+                }
             } else {
                 const std::integral_constant<int, C0> c0;
                 if constexpr (KEEP) {
@@ -357,25 +400,73 @@ conv3d_fwd_lds_k(Tensor x, int cin, const __bf16 *__restrict__ wt, int kpad, con
     }
 }
 
+struct ConvTiles {
+    int tx, ty, tiles;
+    explicit ConvTiles(int n) : tx((n + kTileX - 1) / kTileX), ty((n + kTileY - 1) / kTileY)
+    {
+        tiles = tx * ty * ((n + kTileZ - 1) / kTileZ);
+    }
+    // tiles a workgroup of NB blocks takes in turn, where fit of them are on the chip at once
+    int run(int groups, int fit) const { return (tiles * groups + fit - 1) / fit; }
+};
+
+template <int NB, int C0, bool AHEAD>
+static void conv_lds_launch(const ConvTiles &t, int per, Tensor x, int cin, const __bf16 *wt, int kpad, int cout,
+                            const float *bias, Tensor y, int relu, hipStream_t s)
+{
+    const dim3 grid((unsigned)((t.tiles + per - 1) / per), (unsigned)(cout / (16 * NB)));
+    hipLaunchKernelGGL((conv3d_fwd_lds_k<NB, C0, AHEAD>), grid, dim3(256), 0, s, x, cin, wt, kpad, bias, y, relu, t.tx, t.ty,
+                       t.tiles, per);
+}
+
+// Whole chunks of 32 input channels: as many blocks of output channels share a staged
+// tile as leave 1.5 workgroups per CU (64 -> 64 at 33^3 with NB = 1, 2 and 4 43, 33
+// and 35 us, 49^3 98, 89 and 85, 97^3 563, 522 and 489; 32 -> 32 at 41^3 12.8 and 13.9 with NB
+// = 1 and 2, 49^3 21 and 18.7).
+static void conv_lds32(Tensor x, int cin, const __bf16 *wt, int kpad, int cout, const float *bias, Tensor y, int relu,
+                       hipStream_t s)
+{
+    const ConvTiles t(y.n);
+    const int nb = cout / 16, want = 384;
+    auto shared = [&](int k) { return nb % k == 0 && t.tiles * (nb / k) >= want; };
+    if (shared(4)) conv_lds_launch<4, 32, false>(t, 1, x, cin, wt, kpad, cout, bias, y, relu, s);
+    else if (shared(3)) conv_lds_launch<3, 32, false>(t, 1, x, cin, wt, kpad, cout, bias, y, relu, s);
+    else if (shared(2)) conv_lds_launch<2, 32, false>(t, 1, x, cin, wt, kpad, cout, bias, y, relu, s);
+    else conv_lds_launch<1, 32, false>(t, 1, x, cin, wt, kpad, cout, bias, y, relu, s);
+}
+
+// 48 input channels.  A workgroup's run of tiles costs its length times 4, 5, 7 or 9 for
+// NB = 1 to 4 (768 workgroups of the first fit the CUs, 512 of the others), so the
+// shortest is taken: 48 -> 48 channels at 49^3 47 us with NB = 1, 53 with 3, at 97^3 285 against
+// 226; 48 -> 64 at 33^3 26, 21 and 24 with NB = 1, 2 and 4, at 97^3 408, 330 and 306.
+static void conv_lds48(Tensor x, int cin, const __bf16 *wt, int kpad, int cout, const float *bias, Tensor y, int relu,
+                       hipStream_t s)
+{
+    const ConvTiles t(y.n);
+    const int nb = cout / 16, weight[5] = {0, 4, 5, 7, 9};
+    int best = 1, per[5] = {0, t.run(nb, 768)};
+    for (int k = 2; k <= 4; ++k) {
+        if (nb % k) continue;
+        per[k] = t.run(nb / k, 512);
+        if (per[k] * weight[k] < per[best] * weight[best]) best = k;
+    }
+    switch (best) {
+    case 2: conv_lds_launch<2, 32, true>(t, per[2], x, cin, wt, kpad, cout, bias, y, relu, s); break;
+    case 3: conv_lds_launch<3, 32, true>(t, per[3], x, cin, wt, kpad, cout, bias, y, relu, s); break;
+    case 4: conv_lds_launch<4, 32, true>(t, per[4], x, cin, wt, kpad, cout, bias, y, relu, s); break;
+    default: conv_lds_launch<1, 32, true>(t, per[1], x, cin, wt, kpad, cout, bias, y, relu, s);
+    }
+}
+
 template <int NB>
 static void conv_lds(Tensor x, int cin, const __bf16 *wt, int kpad, int cout, const float *bias, Tensor y, int relu,
                      hipStream_t s)
 {
-    const int tx = (y.n + kTileX - 1) / kTileX, ty = (y.n + kTileY - 1) / kTileY, tz = (y.n + kTileZ - 1) / kTileZ;
-    const int tiles = tx * ty * tz, groups = cout / (16 * NB);
-    // as many workgroups as fit the CUs' LDS (51.8, 31.1 and 10.4 KB), each with a run of tiles whose loads it overlaps
-    const int fit = cin >= 32 ? 768 : (cin == 16 ? 1280 : 1536);
-    const int per = (tiles * groups + fit - 1) / fit;
-    const dim3 grid((unsigned)((tiles + per - 1) / per), (unsigned)groups);
-    if (cin >= 32)
-        hipLaunchKernelGGL((conv3d_fwd_lds_k<1, 32>), grid, dim3(256), 0, s, x, cin, wt, kpad, bias, y, relu, tx, ty,
-                           tiles, per);
-    else if (cin == 16)
-        hipLaunchKernelGGL((conv3d_fwd_lds_k<NB, 16>), grid, dim3(256), 0, s, x, cin, wt, kpad, bias, y, relu, tx, ty,
-                           tiles, per);
-    else
-        hipLaunchKernelGGL((conv3d_fwd_lds_k<NB, 8>), grid, dim3(256), 0, s, x, cin, wt, kpad, bias, y, relu, tx, ty,
-                           tiles, per);
+    // as many workgroups as fit the CUs' LDS (31.1 and 10.4 KB), each with a run of tiles whose loads it overlaps
+    const ConvTiles t(y.n);
+    const int per = t.run(cout / (16 * NB), cin == 16 ? 1280 : 1536);
+    if (cin == 16) conv_lds_launch<NB, 16, true>(t, per, x, cin, wt, kpad, cout, bias, y, relu, s);
+    else conv_lds_launch<NB, 8, true>(t, per, x, cin, wt, kpad, cout, bias, y, relu, s);
 }
 
 template <int NB>
@@ -386,13 +477,15 @@ static void conv_fwd_nb(Tensor x, int cin, const __bf16 *wt, int kpad, const flo
     // 96 and 128 output channels keep the order of conv3d_fwd_k, all channels of a tap before the next tap, which
     // the tile kernel follows up to 32 input channels
     if (stride == 1 && (cin == 8 || cin == 16 || cin == 32 || (NB <= 4 && (cin % 32 == 0 || cin == 48)))) {
-        const int blocks = ((y.n + kTileX - 1) / kTileX) * ((y.n + kTileY - 1) / kTileY) * ((y.n + kTileZ - 1) / kTileZ);
-        // One block of output channels per workgroup from 32 input channels up: two need 174 registers, two
-        // wavefronts per SIMD instead of three (96 -> 32 at 65^3: 153 us against 134).  With fewer input channels
-        // up to three blocks share a staged tile where that leaves two workgroups per CU.
-        const int want = 512;
-        if (NB % 3 == 0 && cin < 32 && blocks * (NB / 3) >= want) conv_lds<3>(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
-        else if (NB % 2 == 0 && cin < 32 && blocks * (NB / 2) >= want) conv_lds<2>(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
+        if (cin >= 32) {
+            if (cin == 48) conv_lds48(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
+            else conv_lds32(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
+            return;
+        }
+        // With 16 and 8 input channels up to three blocks share a staged tile where that leaves two workgroups per CU.
+        const int blocks = ConvTiles(y.n).tiles, want = 512;
+        if (NB % 3 == 0 && blocks * (NB / 3) >= want) conv_lds<3>(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
+        else if (NB % 2 == 0 && blocks * (NB / 2) >= want) conv_lds<2>(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
         else conv_lds<1>(x, cin, wt, kpad, 16 * NB, bias, y, relu, s);
         return;
     }
