@@ -43,14 +43,14 @@ __device__ __forceinline__ bool cic_cell(const BoxGeom &g, int n, double px, dou
     return true;
 }
 
-// A workgroup's share; W: kWin words of LDS.
+// A workgroup's share; W and cnt_sh: LDS.
 __device__ __forceinline__ void window_share(const DepositArgs &A, const double *__restrict__ x,
                                              const double *__restrict__ y, const double *__restrict__ z,
                                              const double *__restrict__ m, int64_t np, int64_t per_block,
-                                             unsigned long long *__restrict__ inside_count, unsigned long long *W)
+                                             unsigned long long *__restrict__ inside_count,
+                                             unsigned long long (&W)[kWin], unsigned int &cnt_sh)
 {
 #pragma clang fp contract(off)
-    __shared__ unsigned int cnt_sh;
     const int64_t p0 = (int64_t)blockIdx.x * per_block;
     const int64_t p1 = min(np, p0 + per_block);
     if (threadIdx.x == 0) cnt_sh = 0;
@@ -74,8 +74,12 @@ __device__ __forceinline__ void window_share(const DepositArgs &A, const double 
                     for (int a = 0; a < 2; ++a) {
                         const double wt = (w[0][a] * w[1][bb]) * w[2][c];
                         const unsigned long long qv = (unsigned long long)__double2ll_rn((wt * pm) * A.scale);
-                        if (inwin) atomicAdd(&W[(lx + a) + kWinX * ((ly + bb) + kWinY * (lz + c))], qv);
-                        else atomicAdd(q + id3(A.n, ic[0] + a, ic[1] + bb, ic[2] + c), qv);
+                        // a scope of its own keeps the two apart: of one, they became one flat atomic
+                        if (inwin)
+                            __hip_atomic_fetch_add(&W[(lx + a) + kWinX * ((ly + bb) + kWinY * (lz + c))], qv,
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        else
+                            atomicAdd(q + id3(A.n, ic[0] + a, ic[1] + bb, ic[2] + c), qv);
                     }
         }
         __syncthreads();
@@ -95,7 +99,8 @@ deposit_window_k(DepositArgs A, const double *__restrict__ x, const double *__re
                  unsigned long long *__restrict__ inside_count)
 {
     __shared__ unsigned long long W[kWin];
-    window_share(A, x, y, z, m, np, per_block, inside_count, W);
+    __shared__ unsigned int cnt_sh;
+    window_share(A, x, y, z, m, np, per_block, inside_count, W, cnt_sh);
 }
 
 // Node e of box b's window over the slabs g0 .. g1 - 1.
@@ -323,9 +328,8 @@ template <int MAXBIN>
 __device__ __forceinline__ void tile_count(const DepositArgs &A, const TileGrid &T, const double *__restrict__ x,
                                            const double *__restrict__ y, const double *__restrict__ z, int np,
                                            int per_block, unsigned *__restrict__ hist, unsigned *__restrict__ total,
-                                           unsigned long long *__restrict__ inside_count, unsigned *H)
+                                           unsigned long long *__restrict__ inside_count, unsigned *H, unsigned &cnt_sh)
 {
-    __shared__ unsigned cnt_sh;
     for (int e = threadIdx.x; e < T.nbin; e += 1024) H[e] = 0;
     if (threadIdx.x == 0) cnt_sh = 0;
     __syncthreads();
@@ -357,10 +361,11 @@ deposit_first_k(DepositArgs A, TileGrid T, const double *__restrict__ x, const d
 {
     static_assert(MAXBIN <= 2 * kWin, "the histogram lies in the window's LDS");
     __shared__ unsigned long long W[kWin];
+    __shared__ unsigned cnt_sh;
     if (!sorted || *sorted)
-        tile_count<MAXBIN>(A, T, x, y, z, np, per_block, hist, total, inside_count, reinterpret_cast<unsigned *>(W));
+        tile_count<MAXBIN>(A, T, x, y, z, np, per_block, hist, total, inside_count, reinterpret_cast<unsigned *>(W), cnt_sh);
     else
-        window_share(A, x, y, z, m, np, per_block, inside_count, W);
+        window_share(A, x, y, z, m, np, per_block, inside_count, W, cnt_sh);
 }
 
 // One workgroup: start[bin] = particles before the bin, next[bin] the same (the
