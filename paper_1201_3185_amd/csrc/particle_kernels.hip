@@ -835,6 +835,7 @@ __device__ __forceinline__ bool in_box(const BoxGeom &G, int n, double px, doubl
 // the other.  Same operations in the same order.  Bound by the cache lines a
 // point touches: 4e6 points in two 257^3 boxes 677 -> 262 us, 1e7 on 513^3 1628
 // -> 638 us; the curve of 60 radii and 16 azimuths 7.7 -> 5.0 us.
+// On 5^3, with 8 such cells of 64, a wavefront goes through both forms: there the general one alone.
 __device__ __forceinline__ void box_accel(const BoxGeom &G, int n, const double *__restrict__ P, double px, double py,
                                           double pz, double acc[3])
 {
@@ -853,7 +854,7 @@ __device__ __forceinline__ void box_accel(const BoxGeom &G, int n, const double 
     }
     const double inv2h = 0.5 * G.inv_h;
     acc[0] = acc[1] = acc[2] = 0.0;
-    if (min(min(ic[0], ic[1]), ic[2]) >= 1 && max(max(ic[0], ic[1]), ic[2]) <= n - 3) {
+    if (n > 5 && min(min(ic[0], ic[1]), ic[2]) >= 1 && max(max(ic[0], ic[1]), ic[2]) <= n - 3) {
         const size_t sy = (size_t)n, sz = (size_t)n * n;
         const double *c0 = P + id3(n, ic[0], ic[1], ic[2]);
         auto at = [&](const double *p) { return *reinterpret_cast<const pair_t *>(p); };
