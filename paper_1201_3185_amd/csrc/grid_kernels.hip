@@ -1600,7 +1600,8 @@ __device__ __forceinline__ void block_sum3(double *sh, double &a, double &b, dou
 // resid_to_f32_k forms, saving that pass).  A thread owns one column: its z neighbours stay in
 // registers, the x and y ones come from an LDS plane of the tile and its ring,
 // which is written a step before (two planes, one barrier a step).  A plane of u
-// is requested three steps before use, one of f two; the loads come after all
+// and one of f are requested four steps before the step that takes them up (step k
+// loads u of plane k + 6 and f of plane k + 4); the loads come after all
 // uses of the registers they fill, and nothing is masked on its way in: what is
 // clamped into the grid enters no interior node's residual.  Each lane sums its
 // own column; the order depends only on n and the launch shape, which the
@@ -1653,7 +1654,7 @@ resid_norms_zmarch_k(int n, double ih2, const T *__restrict__ f, const T *__rest
         struct set {
             T u, h, f;   // own and ring node of plane k + 2, f of plane k
         };
-        const T *pu = u + (size_t)(kb - 1) * nn, *pf = f + (size_t)kb * nn;
+        const T *pu = u + (size_t)(kb - 1) * nn;
         T wm = at(pu, off), w0 = at(pu + nn, off), wp = at(pu + 2 * nn, off);
         const T h0 = at(pu + nn, hoff);
         T hp = at(pu + 2 * nn, hoff);
@@ -1662,7 +1663,7 @@ resid_norms_zmarch_k(int n, double ih2, const T *__restrict__ f, const T *__rest
             return set{at(g, off), at(g, hoff), at(f + (size_t)min(k - 2, n - 1) * nn, off)};
         };
         // The store of r32: every lane issues it (the idle ones out of the buffer's
-        // range, which drops them), also once before the loop, so that the waits
+        // range, which drops them), also three times before the loop, so that the waits
         // for the loads count it, where they would wait for a store in a branch.
         auto put = [&](int k, float v, unsigned o) {
             const __amdgpu_buffer_rsrc_t plane =

@@ -159,8 +159,8 @@ void launch_deposit(const DepositArgs &a, const double *x, const double *y, cons
 // cell tile of the finest box that holds them, so that a workgroup takes
 // particles of one tile and adds all their corners, on that box and on every
 // coarser one, in LDS: in a box twice as large the tile is a block of half the
-// cells per axis, and the blocks of all boxes together hold at most 11 888 nodes
-// (95 KB).  Only the nodes a workgroup has touched go to the grids with global
+// cells per axis, and the blocks of all boxes together hold at most 11 645 nodes
+// (93 KB).  Only the nodes a workgroup has touched go to the grids with global
 // atomics, once per kSegment particles or more.  The weights, their rounding
 // and the integer sums are those of the window form, so the grids are the same
 // integers whatever the order.
@@ -174,15 +174,25 @@ void launch_deposit(const DepositArgs &a, const double *x, const double *y, cons
 //   4. tile_deposit_k: segments from a queue.
 // It is bound by its passes over the particles (24 + 32 + 32 + 32 B each) and by
 // the eight rounded weights per particle and box.  Deposit calls (with clearing
-// q and forming the right-hand side), window form -> sorted: 1e7 particles on
-// 513^3 3363 -> 1075 us, 2e7 in eleven 257^3 boxes 21.5 -> 3.0 ms, 3e6 in three
-// 257^3 boxes 1698 -> 422 us, 1e6 in four 129^3 boxes 351 -> 144 us.
+// q and forming the right-hand side), window form -> sorted, of disks as wide as the
+// finest box: 1e7 particles on 513^3 3944 -> 1111 us, in eleven 257^3 boxes 9.0 -> 2.0
+// ms, 1e6 in three 257^3 boxes 985 -> 319 us, in four 129^3 boxes 526 -> 128 us.  1e7
+// particles within a few cells of 129^3 are the window form's: sorted 323 us, now 156.
 
 constexpr int kTileXY = 32, kTileZ = 8;
 constexpr int kSortBlocks = kDepositMaxBlocks;   // the window form in these launches fills as many slabs
 constexpr int kSegment = 4096;
-constexpr int kWinAll = 11904;       // nodes of one tile's blocks on all boxes, at most
+constexpr int kWinAll = 11904;       // room for one tile's blocks on all boxes
 constexpr int kWinOne = 33 * 33 * 9;
+
+constexpr int blocks_of_all_boxes()
+{
+    int nodes = 0;
+    for (int b = 0, xy = kTileXY, z = kTileZ; b < kMaxBox; ++b, xy = xy > 1 ? xy / 2 : 1, z = z > 1 ? z / 2 : 1)
+        nodes += (xy + 1) * (xy + 1) * (z + 1);
+    return nodes;
+}
+static_assert(blocks_of_all_boxes() == 11645 && blocks_of_all_boxes() <= kWinAll, "a tile's blocks fit");
 
 struct TileGrid {
     int cxy, cz;      // cells per tile

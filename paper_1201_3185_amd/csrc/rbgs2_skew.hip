@@ -37,8 +37,8 @@
 // the correction 77 -> 68), FP64 257^3 90 -> 88 (110 -> 107).  Requesting planes
 // four steps ahead gained nothing.  FP64 pairs, before -> now (with
 // the correction): 513^3 726 -> 595 (862 -> 697) us; 257^3, there two single
-// sweeps, 203 -> 88 (235 -> 107) us in 64-plane chunks; 129^3 45 -> 19 (59 -> 26)
-// us in 8-plane chunks; 65^3, there 8^3 bricks, 18 -> 11 (26 -> 14) us.  64x16
+// sweeps, 203 -> 88 (235 -> 107) us in 64-plane chunks; 129^3 45 -> 17 (59 -> 23)
+// us in 8-plane chunks; 65^3, there 8^3 bricks, 18 -> 9 (26 -> 11) us.  64x16
 // columns waste least on the ring (1.7 nodes per node of the tile; 1.9 at 32x16,
 // 2.5 at 32x8) and win from 129^3 up; the small ones fill the chip at 65^3.
 #include "common.h"
@@ -301,8 +301,8 @@ rbgs2_skew_k(const T *__restrict__ uin, T *__restrict__ uout, const T *__restric
         __syncthreads();
     };
     // whole pairs of steps: no branch inside a loop; those with every plane inside
-    // check none (not with the correction: a second copy of its step spills, 813
-    // against 718 us at 513^3 in FP64)
+    // check none (not with the correction: a second copy of its step spills, 813 us
+    // at 513^3 in FP64 against 697)
     const int sa = PROLONG ? smax : max(K0 + 3, s0 + 2), sb = min(n - 3, smax - 1);
     int s = s0;
     for (; s < sa && s + 1 <= smax; s += 2) {
