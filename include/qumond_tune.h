@@ -58,8 +58,8 @@ qumond_status qumond_tune_get_fused(int32_t n, int32_t fp32, int32_t *variant, i
  * thread per coarse node gathering its 27 fine residuals, 1 = LDS tile of the
  * fine block, 2, 3, 4 = z-march of 16x8 coarse columns over chunks of 4, 8, 16
  * coarse planes, 5 = 4x4x4, 6 = 4x4x2 coarse LDS tiles, 7 = z-march of 32x8
- * coarse columns, cut in z until every compute unit has a workgroup, 9 = the same
- * over chunks of 64 coarse planes; 8, 10 and 11 are 7 (they were marches of whole
+ * coarse columns, cut in z until every compute unit has a workgroup, 9, 10 = the same
+ * over chunks of 64, 16 coarse planes; 8 and 11 are 7 (they were marches of whole
  * columns, which saved tables ask for at 513^3).  From 513^3 up no march is cut
  * shorter than 7 is.  Identical results; the autotuner picks the fastest.
  * Errors: variant outside 0..11 -> QUMOND_ERR_INVALID. */

@@ -132,9 +132,9 @@ struct SmootherShape {
 constexpr int kSmootherVariants = 16;
 constexpr int kRrVariants = 12;   // residual restriction: gather, 8x8x4 LDS tile, z-march of 16x8 columns over
                                   // 4/8/16-plane chunks, 4x4x4 and 4x4x2 LDS tiles, z-march of 32x8 columns:
-                                  // 7 in chunks that fill the chip, 9 over 64-plane chunks
-// 8, 10 and 11 are 7: tables saved when they were whole columns keep their speed
-inline bool is_rr_alias(int v) { return v == 8 || v == 10 || v == 11; }
+                                  // 7 in chunks that fill the chip, 9 and 10 over 64- and 16-plane chunks
+// 8 and 11 are 7: tables saved when they were whole columns keep their speed
+inline bool is_rr_alias(int v) { return v == 8 || v == 11; }
 // bricks hold their whole block in LDS and take no z-chunk
 inline bool is_brick_variant(int v, bool fused) { return fused ? (v >= 2 && v <= 4) : (v == 5 || v == 9 || v == 10); }
 constexpr int kFusedVariants = 11;  // two sweeps: 2: 8^3, 3: 4^3, 4: 6^3 bricks, 8: 64x16, 9: 32x8, 10: 32x16

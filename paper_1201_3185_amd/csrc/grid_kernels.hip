@@ -1289,7 +1289,7 @@ residual_restrict_tile_k(int nf, T ih2, const T *__restrict__ f, const T *__rest
 // Which residual-restriction kernel a fine level of n points uses (0: per-node
 // gather, 1: 8x8x4 LDS tile, 2/3/4: z-march of 16x8 columns over chunks of 4/8/16
 // coarse planes, 5: 4x4x4, 6: 4x4x2 LDS tiles, 7: z-march of 32x8 columns in chunks
-// that fill the chip, 9: over 64 planes; 8, 10, 11: as 7), per precision; set by the
+// that fill the chip, 9, 10: over 64, 16 planes; 8, 11: as 7), per precision; set by the
 // autotuner.  By default the fastest of all at each size (us, against the gather;
 // FP32 in brackets): 33^3 the 4x4x2 tiles 6.4 against 10.0 (6.2, 6.8), 65^3 the march
 // 8.1 against 10.5 (the gather 6.9, the march 7.3), 129^3 16x8 columns in 4-plane
@@ -1319,7 +1319,7 @@ void launch_residual_restrict_variant(int nf, double h, const T *f, const T *u, 
         return;
     }
     if ((variant >= 2 && variant <= 4) || variant >= 7) {   // z-march over 16 x 8 or 32 x 8 coarse columns
-        constexpr int chunk[kRrVariants] = {0, 0, 4, 8, 16, 0, 0, 0, 0, 64, 0, 0};
+        constexpr int chunk[kRrVariants] = {0, 0, 4, 8, 16, 0, 0, 0, 0, 64, 16, 0};
         launch_rr_march<T>(nf, h, f, u, fc, uc0, uc1, variant >= 7, chunk[variant], s, nb, zu);
         return;
     }

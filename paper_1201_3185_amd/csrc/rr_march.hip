@@ -31,6 +31,9 @@
 // 120, 65, 38 and 31), at 513^3 511, 578, 686, 669 and 664 (308, 306, 334, 365 and
 // 370).  So from 513^3 up, where whole columns fill the chip, a shorter chunk is
 // not taken either (16 x 8 columns in 4, 8 and 16 planes 879, 743 and 685 us, whole 570).
+// Of many grids at once the chip's last, part-filled turn counts too: nine of 257^3 in
+// FP32 373 us in chunks of 64 planes, 358 in chunks of 16, which the tuning of a batch
+// finds.
 //
 // No value is masked: what is loaded outside the grid (clamped addresses) or
 // formed on the ring only enters residuals that no interior coarse node reads.
